@@ -185,11 +185,10 @@ bool pool_order_applies(const View& v, const std::vector<int32_t>& t0,
   return 9 * tiles >= 5 * v.NB * ngrp;
 }
 
-// Paged stream-in in pool order for more than 64 sequences: the owner map
-// of the whole call (one clearing launch, one building launch per group of
-// 64 sequences), then one launch over every (slab, pool block, head pair).
-int pool_order_stream_in(const View& v, int32_t l0, int32_t l1, const std::vector<int32_t>& t0,
-                         const std::vector<int32_t>& n, int64_t N, void* wire, hipStream_t st) {
+// The owner map of a whole call: one clearing launch, one building launch per
+// group of 64 sequences.
+int build_owner_map(const View& v, const std::vector<int32_t>& t0, const std::vector<int32_t>& n,
+                    hipStream_t st) {
   dv::OwnerArgs o;
   memset(&o, 0, sizeof o);
   o.owner = v.owner;
@@ -213,31 +212,143 @@ int pool_order_stream_in(const View& v, int32_t l0, int32_t l1, const std::vecto
     e = dv::launch_owner_build(o, st);
     if (e != hipSuccess) return hip_fail(e, "owner map launch");
   }
-  dv::PoolOrderArgs a;
+  return DV_OK;
+}
+
+// Fills a launch's sequence table for sequences [g0, g0 + nseq) of the call;
+// items(i) is the number of work items of sequence g0 + i.  Returns the sum
+// of the items (which the caller has checked to be below 2^31).
+template <int N, typename Items>
+int64_t fill_seqs(dv::SeqTable<N>* s, const std::vector<int32_t>& t0,
+                  const std::vector<int32_t>& n, int64_t g0, int nseq, Items items) {
+  int64_t total = 0, tok = 0;
+  for (int i = 0; i < N; ++i) {
+    s->item[i] = i < nseq ? (int32_t)total : INT32_MAX;
+    s->tok[i] = (int32_t)tok;
+    s->t0[i] = i < nseq ? t0[g0 + i] : 0;
+    if (i < nseq) {
+      total += items(i);
+      tok += n[g0 + i];
+    }
+  }
+  s->tok[N] = (int32_t)tok;
+  return total;
+}
+
+// Blocks of the table that hold tokens [t0, t0 + n).
+int64_t blocks_of(const View& v, int64_t t0, int64_t n) {
+  return n > 0 ? (t0 + n + v.bs - 1) / v.bs - t0 / v.bs : 0;
+}
+
+// The smallest power of two of tiles per workgroup for which the launch's
+// workgroups per slab, fill(steps) of them, have fewer than 2^32 lanes.
+template <typename Fill>
+int32_t steps_for(Fill fill, int64_t* tiles) {
+  int32_t steps = 1;
+  while ((*tiles = fill(steps)) >= (1ll << 32) / dv::kThreads) steps *= 2;
+  return steps;
+}
+
+// How a paged call moves: tiles over whole blocks in table order or in pool
+// order (paged_kernel), or over the range alone in wire order
+// (paged_runs_kernel).
+enum class Paged { kTable, kPool, kWire };
+
+// One launch over sequences [g0, g0 + nseq) of a call, their part of the
+// contiguous buffer at `wire`.  In pool order (the owner map built) it covers
+// the whole pool and all sequences of the call.
+template <int N>
+hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
+                              const std::vector<int32_t>& t0, const std::vector<int32_t>& n,
+                              int64_t g0, int nseq, int64_t w_slab, void* wire,
+                              hipStream_t st) {
+  const int64_t s_blk = v.H * v.bs * v.du, s_slab = v.NB * s_blk;
+  const dv::FastDiv d_ub = dv::fast_div((uint32_t)(v.bs * v.du));
+  int64_t tiles = 0;
+  if (how == Paged::kWire) {
+    dv::PagedRunArgs<N> a;
+    memset(&a, 0, sizeof a);
+    a.pool = v.base;
+    a.wire = wire;
+    a.bt = v.bt + g0 * v.max_blocks;
+    a.s_slab = s_slab;
+    a.s_blk = s_blk;
+    a.m = {2 * l0, 1, 0, 0, w_slab};
+    a.ub = (int32_t)(v.bs * v.du);
+    a.du = (int32_t)v.du;
+    a.heads = (int32_t)v.H;
+    a.num_blocks = (int32_t)v.NB;
+    a.max_blocks = (int32_t)v.max_blocks;
+    a.d_ub = d_ub;
+    a.steps = steps_for(
+        [&](int64_t steps) {
+          const int64_t tile = dv::kPagedTile * steps;
+          return fill_seqs(&a.s, t0, n, g0, nseq,
+                           [&](int i) { return (n[g0 + i] * v.H * v.du + tile - 1) / tile; });
+        },
+        &tiles);
+    return dv::launch_paged_runs<N>(dir, a, (uint32_t)tiles, 2 * nl, st);
+  }
+  dv::PagedArgs<N> a;
   memset(&a, 0, sizeof a);
   a.pool = v.base;
   a.wire = wire;
-  a.owner = v.owner;
-  a.s_slab = v.NB * v.H * v.bs * v.du;
-  a.s_blk = v.H * v.bs * v.du;
-  a.s_h = v.bs * v.du;
-  a.m = {2 * l0, 1, 0, 0, N * v.H * v.du};
+  a.bt = v.bt + g0 * v.max_blocks;
+  a.owner = how == Paged::kPool ? v.owner : nullptr;
+  a.s_slab = s_slab;
+  a.s_blk = s_blk;
+  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.ub = (int32_t)(v.bs * v.du);
   a.du = (int32_t)v.du;
   a.heads = (int32_t)v.H;
-  a.nseq = (int32_t)v.B;
-  a.max_blocks = (int32_t)v.max_blocks;
-  a.block_size = (int32_t)v.bs;
+  a.nseq = nseq;
   a.num_blocks = (int32_t)v.NB;
-  int64_t p = 0;
-  for (int64_t b = 0; b < v.B; ++b) {
-    a.t0[b] = t0[b];
-    a.n[b] = n[b];
-    a.p[b] = (int32_t)p;  // below 2^31: N is
-    p += n[b];
+  a.max_blocks = (int32_t)v.max_blocks;
+  a.d_ub = d_ub;
+  a.d_heads = dv::fast_div((uint32_t)v.H);
+  a.d_bs = dv::fast_div((uint32_t)v.bs);
+  a.d_max = dv::fast_div((uint32_t)v.max_blocks);
+  int64_t units = 0;  // the longest array that tiles number through
+  a.steps = steps_for(
+      [&](int64_t steps) {
+        const int64_t tile = dv::kPagedTile * steps;
+        units = 0;
+        const int64_t table = fill_seqs(&a.s, t0, n, g0, nseq, [&](int i) {
+          const int64_t f = blocks_of(v, t0[g0 + i], n[g0 + i]) * s_blk;
+          units = std::max(units, f);
+          return (f + tile - 1) / tile;
+        });
+        if (how != Paged::kPool) return table;
+        units = s_slab;
+        return (s_slab + tile - 1) / tile;
+      },
+      &tiles);
+  a.tiles = (int32_t)tiles;
+  a.d_tiles = dv::fast_div((uint32_t)tiles);
+  const bool wide = a.steps > 1 || units + dv::kPagedTile >= (1ll << 31) ||
+                    tiles * 2 * nl >= (1ll << 31);
+  return dv::launch_paged<N>(dir, a, wide, 2 * nl, st);
+}
+
+// A paged stream of runs longer than the short-run kernel's, in launches of
+// at most N sequences.
+template <int N>
+int run_paged(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
+              const std::vector<int32_t>& t0, const std::vector<int32_t>& n, int64_t w_slab,
+              void* wire, hipStream_t st) {
+  int64_t p = 0;  // tokens of all earlier launches
+  for (int64_t g0 = 0; g0 < v.B; g0 += N) {
+    const int nseq = (int)std::min<int64_t>(N, v.B - g0);
+    int64_t tok = 0;
+    for (int i = 0; i < nseq; ++i) tok += n[g0 + i];
+    if (tok == 0) continue;
+    const hipError_t e =
+        launch_paged_group<N>(dir, how, v, l0, nl, t0, n, g0, nseq, w_slab,
+                              static_cast<char*>(wire) + (uint64_t)p * v.H * v.du * 16, st);
+    if (e != hipSuccess) return hip_fail(e, "paged kernel launch");
+    p += tok;
   }
-  const int64_t ngrp = (v.H + dv::kPagedHeads - 1) / dv::kPagedHeads;
-  e = dv::launch_paged_pool_order(a, (uint32_t)(v.NB * ngrp), 2 * (uint32_t)(l1 - l0), st);
-  return hip_fail(e, "paged pool-order launch");
+  return DV_OK;
 }
 
 // Enqueue the pack (dir = kPack) or unpack of the validated ranges.  The wire
@@ -278,11 +389,31 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     }
   }
 
-  // Paged stream-in in pool order: up to 64 sequences through paged_kernel
-  // in the loop below, more through one launch over the whole call.
-  const bool pool_order = dir == dv::kUnpack && v.kind == DV_PAGED && !single && !small &&
-                          v.owner && pool_order_applies(v, t0, n, N);
-  if (pool_order && v.B > kSeqPerLaunch) return pool_order_stream_in(v, l0, l1, t0, n, N, wire, st);
+  bool flat = small;  // the short-run kernel
+  if (v.kind == DV_PAGED && !single && !small) {
+    // Tiles over whole blocks leave the lanes of tokens outside the range
+    // idle: where the range covers less than three quarters of its blocks,
+    // tiles over the range alone, and where those would not be three quarters
+    // full either (a few hundred units per sequence), the short-run kernel.
+    int64_t blocks = 0, tiles = 0;
+    for (int64_t b = 0; b < v.B; ++b) {
+      blocks += blocks_of(v, t0[b], n[b]);
+      tiles += (n[b] * v.H * v.du + dv::kPagedTile - 1) / dv::kPagedTile;
+    }
+    Paged how = 4 * N < 3 * blocks * v.bs ? Paged::kWire : Paged::kTable;
+    if (dir == dv::kUnpack && v.owner && pool_order_applies(v, t0, n, N)) {
+      const int rc = build_owner_map(v, t0, n, st);
+      if (rc != DV_OK) return rc;
+      if (how == Paged::kTable) how = Paged::kPool;
+    }
+    flat = how == Paged::kWire && 4 * w_slab < 3 * tiles * dv::kPagedTile && w_slab < (1ll << 31);
+    // More than 64 sequences go 256 to a launch while their tokens count
+    // below 2^31 (those of 64 always do).
+    if (!flat)
+      return v.B > kSeqPerLaunch && N < (1ll << 31)
+                 ? run_paged<dv::kSeqMany>(dir, how, v, l0, nl, t0, n, w_slab, wire, st)
+                 : run_paged<kSeqPerLaunch>(dir, how, v, l0, nl, t0, n, w_slab, wire, st);
+  }
 
   int64_t p_group = 0;  // tokens of all earlier launch groups
   for (int64_t g0 = 0; g0 < v.B; g0 += kSeqPerLaunch) {
@@ -352,7 +483,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
       continue;
     }
 
-    if (small) {
+    if (flat) {
       dv::SmallRunArgs a;
       memset(&a, 0, sizeof a);
       a.cache = v.base;
@@ -363,7 +494,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
       a.nseq = nseq;
       a.b0 = (int32_t)g0;
       a.r = r;
-      const int64_t units = ntok * v.H * v.du;  // below 2^31: checked above
+      const int64_t units = ntok * v.H * v.du;  // below 2^31: checked above (paged: w_slab is)
       hipError_t e;
       if (v.kind == DV_PAGED) {
         a.paged = 1;
@@ -401,49 +532,6 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
         }
       }
       if (e != hipSuccess) return hip_fail(e, "short-run kernel launch");
-      continue;
-    }
-
-    if (v.kind == DV_PAGED) {
-      dv::PagedArgs a;
-      memset(&a, 0, sizeof a);
-      a.pool = v.base;
-      a.wire = wire_g;
-      a.bt = v.bt;
-      a.s_slab = v.NB * v.H * v.bs * v.du;
-      a.s_blk = v.H * v.bs * v.du;
-      a.s_h = v.bs * v.du;
-      a.m = {2 * l0, 1, 0, 0, w_slab};
-      a.du = (int32_t)v.du;
-      a.heads = (int32_t)v.H;
-      a.nseq = nseq;
-      a.b0 = (int32_t)g0;
-      a.block_size = (int32_t)v.bs;
-      a.num_blocks = (int32_t)v.NB;
-      a.max_blocks = (int32_t)v.max_blocks;
-      a.r = r;
-      const int64_t ngrp = (v.H + dv::kPagedHeads - 1) / dv::kPagedHeads;
-      int64_t tiles = 0;
-      for (int i = 0; i < nseq; ++i)
-        if (r.n[i] > 0) tiles += ((r.t0[i] + r.n[i] + v.bs - 1) / v.bs - r.t0[i] / v.bs) * ngrp;
-      if (pool_order) {  // all sequences in this one group
-        dv::OwnerArgs o;
-        memset(&o, 0, sizeof o);
-        o.owner = v.owner;
-        o.bt = v.bt;
-        o.nseq = nseq;
-        o.block_size = (int32_t)v.bs;
-        o.num_blocks = (int32_t)v.NB;
-        o.max_blocks = (int32_t)v.max_blocks;
-        o.r = r;
-        hipError_t e = dv::launch_owner_clear(o, st);
-        if (e == hipSuccess) e = dv::launch_owner_build(o, st);
-        if (e != hipSuccess) return hip_fail(e, "owner map launch");
-        a.owner = v.owner;
-        tiles = v.NB * ngrp;  // below 2^31: checked by pool_order_applies
-      }
-      const hipError_t e = dv::launch_paged(dir, a, (uint32_t)tiles, 2 * nl, st);
-      if (e != hipSuccess) return hip_fail(e, "paged kernel launch");
       continue;
     }
 

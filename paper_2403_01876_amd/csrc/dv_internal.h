@@ -16,6 +16,39 @@ constexpr int kThreads = 256;
 
 enum Dir : int { kPack = 0, kUnpack = 1 };
 
+// Division by a launch constant d >= 1, exact for 0 <= n < 2^31: with l =
+// ceil(log2 d) and m = ceil(2^(31 + l) / d) (below 2^32), n / d = n * m >> (31
+// + l) (Granlund and Montgomery, "Division by invariant integers using
+// multiplication", PLDI 1994).  Doubling n first keeps d = 1 in the same form.
+struct FastDiv {
+  uint32_t m, l;
+  __host__ __device__ uint32_t div(uint32_t n) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __umulhi(n << 1, m) >> l;
+#else
+    return (uint32_t)(((uint64_t)(n << 1) * m) >> 32) >> l;
+#endif
+  }
+};
+inline FastDiv fast_div(uint32_t d) {
+  FastDiv f{0, 0};
+  while ((1ull << f.l) < d) ++f.l;
+  f.m = (uint32_t)(((1ull << (31 + f.l)) + d - 1) / d);
+  return f;
+}
+
+// The sequences of one launch (N of them at most: 64, or 256 for larger
+// batches), with the prefixes that place them computed on the host: a
+// workgroup finds its sequence with one ballot per 64 entries instead of
+// scanning the counts.
+constexpr int kSeqMany = 256;
+template <int N>
+struct SeqTable {
+  int32_t item[N];     // work items of all earlier sequences; INT32_MAX past the last
+  int32_t tok[N + 1];  // tokens of all earlier sequences
+  int32_t t0[N];       // first token of each sequence's range
+};
+
 struct SeqRanges {
   int32_t t0[kSeqPerLaunch];  // first token of each sequence's range
   int32_t n[kSeqPerLaunch];   // tokens in the range (0 = sequence skipped)
@@ -44,46 +77,50 @@ struct DenseRunArgs {
   SeqRanges r;
 };
 
-// Paged blocks: one workgroup per (slab, block, head pair).  Blocks are
-// taken in table order -- (sequence, logical block) -- or, when `owner` is
-// set, in pool order through the owner map (launches with all sequences in
-// one group, b0 = 0).
+// Paged blocks.  A slab of the pool is one array of units in (block, head,
+// token, group) order; a tile is kPagedTile consecutive units of it, or, in
+// table order, of the array its blocks would form if each sequence's blocks
+// stood in the table's order.  So a tile's pool side is contiguous up to block
+// boundaries and every lane holds a unit whatever the block's size.  With
+// `owner` set (pool order) a block's sequence comes from the owner map.
+template <int N>
 struct PagedArgs {
   void* pool;
-  void* wire;
-  const int32_t* bt;     // this microbatch's block table [batch][max_blocks]
+  void* wire;            // contiguous buffer advanced to this launch's first sequence
+  const int32_t* bt;     // rows of this launch's sequences [nseq][max_blocks]
   const int32_t* owner;  // pool order: [num_blocks] owner map, else null
   int64_t s_slab;        // pool units per slab (NB * heads * bs * du)
   int64_t s_blk;         // pool units per block (heads * bs * du)
-  int64_t s_h;           // pool units per head in a block (bs * du)
   SlabMap m;
-  int32_t du, heads, nseq, b0;
-  int32_t block_size, num_blocks, max_blocks, pad;
-  SeqRanges r;
+  int32_t ub;            // pool units per head in a block (bs * du)
+  int32_t du, heads, nseq;
+  int32_t num_blocks, max_blocks;
+  int32_t tiles;         // tiles per slab (the grid's width)
+  int32_t steps;         // wide launches: tiles a workgroup takes one after another
+  FastDiv d_ub, d_heads, d_bs, d_max, d_tiles;
+  SeqTable<N> s;
 };
+static_assert(sizeof(PagedArgs<kSeqMany>) <= 3584, "arguments stay well under 4 KB");
 
-// Sequences a pool-order stream-in covers in one launch: their ranges and
-// token prefixes travel in the arguments (3 KB).
-constexpr int kPoolSeqMax = 256;
-
-// Paged stream-in in pool order for calls of more than 64 sequences: one
-// workgroup per (slab, pool block, head pair) of the whole call; the owner
-// map names each block's (sequence, logical block), and the sequence's
-// range and exclusive token prefix (over the call, < 2^31) come from the
-// arrays below.
-struct PoolOrderArgs {
+// Paged runs in wire order: a tile is kPagedTile consecutive units of one
+// sequence's part of the contiguous buffer, (head, token, group) order.
+template <int N>
+struct PagedRunArgs {
   void* pool;
-  void* wire;             // the call's contiguous buffer
-  const int32_t* owner;   // [num_blocks] owner map
-  int64_t s_slab, s_blk, s_h;  // as PagedArgs
+  void* wire;
+  const int32_t* bt;
+  int64_t s_slab, s_blk;
   SlabMap m;
-  int32_t du, heads, nseq, max_blocks;
-  int32_t block_size, num_blocks, pad0, pad1;
-  int32_t t0[kPoolSeqMax];  // first token of each sequence's range
-  int32_t n[kPoolSeqMax];   // tokens in the range
-  int32_t p[kPoolSeqMax];   // tokens of all earlier sequences
+  int32_t ub, du, heads;
+  int32_t num_blocks, max_blocks;
+  int32_t steps;         // tiles a workgroup takes one after another (1 unless the grid
+                         // would pass 2^32 lanes)
+  FastDiv d_ub;
+  SeqTable<N> s;
 };
-static_assert(sizeof(PoolOrderArgs) <= 3584, "pool-order arguments stay well under 4 KB");
+
+// Sequences a pool-order stream-in covers.
+constexpr int kPoolSeqMax = kSeqMany;
 
 // Owner map of a paged table over the streamed ranges: owner[blk] =
 // b * max_blocks + j for each entry (b, j) whose logical block j holds a
@@ -173,10 +210,14 @@ constexpr size_t kKsplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do no
 // Launchers (dv_kernels.hip).  Each returns the hipError_t of its launch.
 hipError_t launch_dense_runs(int dir, const DenseRunArgs& a, uint32_t tiles_per_slab,
                              uint32_t nslabs, hipStream_t s);
-hipError_t launch_paged(int dir, const PagedArgs& a, uint32_t tiles_per_slab, uint32_t nslabs,
+// `wide`: some tile's first unit, or the number of the grid's workgroups, may
+// pass 2^31 (steps is 1 otherwise).
+template <int N>
+hipError_t launch_paged(int dir, const PagedArgs<N>& a, bool wide, uint32_t nslabs,
                         hipStream_t s);
-hipError_t launch_paged_pool_order(const PoolOrderArgs& a, uint32_t tiles_per_slab,
-                                   uint32_t nslabs, hipStream_t s);
+template <int N>
+hipError_t launch_paged_runs(int dir, const PagedRunArgs<N>& a, uint32_t tiles_per_slab,
+                             uint32_t nslabs, hipStream_t s);
 // Sets every entry of the owner map to -1.
 hipError_t launch_owner_clear(const OwnerArgs& a, hipStream_t s);
 // Fills the owner map from the table for sequences [b0, b0 + nseq).
@@ -200,13 +241,13 @@ hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nsla
 constexpr int kDenseUnroll = 2;
 constexpr int kDenseTile = kThreads * kDenseUnroll;
 
-// Heads per paged tile and 16-byte units per lane per pass (tiles are
-// counted on the host with kPagedHeads).  Measured on MI355X against 1, 4
-// and all heads per tile on the LLaMA-2-70B paged shape.  The kernel splits
-// a tile's flattened (head, unit) index with one comparison, which holds
-// for two heads only.
-constexpr int kPagedHeads = 2;
+// 16-byte units per paged tile: two per lane, 8 KB of one pool slab.
 constexpr int kPagedUnroll = 2;
+constexpr int kPagedTile = kThreads * kPagedUnroll;
+
+// The pool-order and grid-size rules of the host count tiles of two heads of
+// one block.
+constexpr int kPagedHeads = 2;
 
 // Pool-order scatters deal their (tile, slab) grid to the 8 XCDs in chunks
 // of this many consecutive tiles (8 pool blocks of one slab at 8 heads; 256

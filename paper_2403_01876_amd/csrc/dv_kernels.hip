@@ -39,6 +39,38 @@ __device__ __forceinline__ int owner_lane(int incl, int item) {
   return __popcll(__ballot(incl <= item));
 }
 
+// The sequence that holds work item `item` of a launch, uniform over the
+// wavefront: every lane compares the prefixes of its share of the sequences,
+// and the count of prefixes at or below the item names the sequence (empty
+// sequences share their successor's prefix, so the last one counted has it).
+struct Seq {
+  int b, k;      // index in the launch; the item's index in the sequence
+  int t0, n, p;  // first token, tokens, tokens of earlier sequences
+};
+template <int N>
+__device__ __forceinline__ Seq find_seq(const SeqTable<N>& s, int item) {
+  const int lane = lane_id();
+  Seq q;
+  if constexpr (N == 64) {
+    const int first = s.item[lane], t0 = s.t0[lane], p = s.tok[lane], p1 = s.tok[lane + 1];
+    q.b = __popcll(__ballot(first <= item)) - 1;
+    q.k = item - __builtin_amdgcn_readlane(first, q.b);
+    q.t0 = __builtin_amdgcn_readlane(t0, q.b);
+    q.p = __builtin_amdgcn_readlane(p, q.b);
+    q.n = __builtin_amdgcn_readlane(p1, q.b) - q.p;
+  } else {
+    int below = 0;
+#pragma unroll
+    for (int i = 0; i < N / 64; ++i) below += __popcll(__ballot(s.item[i * 64 + lane] <= item));
+    q.b = below - 1;
+    q.k = item - s.item[q.b];
+    q.t0 = s.t0[q.b];
+    q.p = s.tok[q.b];
+    q.n = s.tok[q.b + 1] - q.p;
+  }
+  return q;
+}
+
 // Workgroup IDs are dealt round-robin to the chip's 8 XCDs (each with its
 // own L2).  The bulk kernels re-deal the linearised (tile, slab) grid so each
 // XCD streams a contiguous range of it: workgroup `lin` runs on XCD lin % 8
@@ -64,18 +96,13 @@ __device__ __forceinline__ void xcd_tile(int* tile, int64_t* slab_row) {
 // deals workgroups in.  On MI355X it lifts the LLaMA-2-70B pool-order
 // scatter from 75 % to 77 % of HBM peak, where contiguous eighths (as
 // xcd_tile) cost it 2 points and cost the table-order gather 6.
-__device__ __forceinline__ void xcd_chunk_tile(int* tile, int64_t* slab_row) {
-  const uint64_t total = (uint64_t)gridDim.x * gridDim.y;
-  const uint64_t lin = blockIdx.x + (uint64_t)blockIdx.y * gridDim.x;
-  constexpr uint64_t C = kPoolChunk;
-  const uint64_t full = total / (8 * C) * (8 * C);
-  uint64_t t = lin;
-  if (lin < full) {
-    const uint64_t x = lin % 8, k = lin / 8;
-    t = ((k / C) * 8 + x) * C + k % C;
-  }
-  *tile = (int)(t % gridDim.x);
-  *slab_row = (int64_t)(t / gridDim.x);
+template <typename U>
+__device__ __forceinline__ U xcd_chunk(U lin, U total) {
+  constexpr U C = kPoolChunk;
+  const U full = total / (8 * C) * (8 * C);
+  if (lin >= full) return lin;
+  const U x = lin % 8, k = lin / 8;
+  return ((k / C) * 8 + x) * C + k % C;
 }
 
 // ---------------------------------------------------------------------------
@@ -135,150 +162,240 @@ __global__ void __launch_bounds__(kThreads) dense_runs_kernel(DenseRunArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Paged blocks: grid (tiles_per_slab, nslabs); a tile is the part of one
-// block of one sequence inside its token range, for kPagedHeads heads.  For
-// a fixed (slab, block) the pool holds the heads back to back, so the tile's
-// pool side is one contiguous piece; on the wire side each head's tokens are
-// contiguous.  Two heads of a 16-token, 128-dim block make an 8 KB tile, the
-// size the dense kernel streams best at.
+// Paged blocks: grid (tiles_per_slab, nslabs); a tile is kPagedTile units of
+// the slab's (block, head, token, group) order (see PagedArgs).
 //
-// Table order (owner == null): tiles enumerate (sequence, logical block,
-// head pair) and find the pool block through the table, so consecutive
-// workgroups read consecutive wire bytes.  Pool order (owner set, unpack
-// only): tiles enumerate (pool block, head pair) and find the sequence and
-// logical block through the owner map, so consecutive workgroups write
-// consecutive pool bytes -- on MI355X writes scattered by a random table
-// cost more than reads scattered the same way.
+// Table order (POOL false): the blocks stand in (sequence, logical block)
+// order and are found through the table, so consecutive workgroups touch
+// consecutive wire bytes.  Pool order (unpack only): they stand as in the
+// pool and the owner map names each one's (sequence, logical block), so
+// consecutive workgroups write consecutive pool bytes -- on MI355X writes
+// scattered by a random table cost more than reads scattered the same way.
+//
+// Bound by HBM once a workgroup's fixed cost (dispatch, its sequence, the
+// table entry) is spread over a whole tile.  Tiles of two heads of one block
+// left that cost on 2 KB for one KV head of a 1-byte cache (80 layers, 64
+// sequences of 128-4096 tokens, 2.77 GB): 2320 and 2350 us a gather and a
+// scatter, 2.4 TB/s; with tiles of 512 units across blocks 910 and 990 us, 6.1
+// and 5.6 TB/s.  Where a tile was whole before, the LLaMA-2-70B pool (eight
+// heads of a 2-byte cache, 5.54 GB): 1797 and 1801 us, 1841 and 1803 before.
+//
+// ONE: a tile never leaves its block (the block is a multiple of the tile),
+// so block, table entry and sequence are uniform over the workgroup.  WIDE:
+// unit numbers may pass 2^31, and a workgroup may take several tiles; kept
+// apart so that the ordinary kernels run straight down, with their arguments
+// fetched together.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs a) {
-  static_assert(kPagedHeads == 2, "the (head, unit) split below assumes two heads per tile");
+template <int D, bool POOL, bool ONE, bool WIDE, int N>
+__global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
+  static_assert(!POOL || D == kUnpack, "pool order is for stream-in");
+  static_assert(!(ONE && WIDE), "wide launches look every unit up");
   const int lane = lane_id();
-  const int bs = a.block_size;
-  const int ngrp = (a.heads + kPagedHeads - 1) / kPagedHeads;
-  int n = 0, t0 = 0, tiles = 0;
-  if (lane < a.nseq) {
-    n = a.r.n[lane];
-    t0 = a.r.t0[lane];
-    if (n > 0) tiles = ((t0 + n + bs - 1) / bs - t0 / bs) * ngrp;
-  }
-  const int tok_incl = wave_incl_scan(n);
-
+  const uint32_t ub = a.ub, heads = a.heads;
   // Table order keeps the hardware's round-robin dealing: pool blocks are
   // scattered by the block table anyway, and on MI355X every XCD-grouped
   // order measured was slower (by 2-8 %).  Pool order deals chunks of tiles.
-  int tile = blockIdx.x;
   int64_t y = blockIdx.y;
-  if (a.owner) xcd_chunk_tile(&tile, &y);
-  int b, j, grp, blk;
-  if (a.owner) {
-    blk = tile / ngrp;
-    grp = tile - blk * ngrp;
-    const int own = a.owner[blk];
-    if (own < 0) return;  // block not written by this call
-    b = own / a.max_blocks;
-    j = own - b * a.max_blocks;
-    if (b >= a.nseq) return;
-  } else {
-    const int incl = wave_incl_scan(tiles);
-    b = owner_lane(incl, tile);
-    const int tj = tile - __shfl(incl - tiles, b, 64);
-    grp = tj % ngrp;
-    j = __shfl(t0, b, 64) / bs + tj / ngrp;  // logical block
-    blk = a.bt[(int64_t)(a.b0 + b) * a.max_blocks + j];
-    if (blk < 0 || blk >= a.num_blocks) return;  // unmapped block: skipped
-  }
-  const int n_b = __shfl(n, b, 64);
-  const int t0_b = __shfl(t0, b, 64);
-  const int p_b = __shfl(tok_incl - n, b, 64);
-  const int s_lo = max(t0_b, j * bs);
-  const int s_hi = min(t0_b + n_b, (j + 1) * bs);
-  if (s_lo >= s_hi) return;
-
-  const int run = (s_hi - s_lo) * a.du;  // units per head in this tile
-  const int64_t slab = a.m.slab0 + y * a.m.slab_step;
-  const int64_t wslab = a.m.wslab0 + y * a.m.slab_step;
-  const int h0 = grp * kPagedHeads;
-  u32x4* pool = (u32x4*)a.pool + slab * a.s_slab + (int64_t)blk * a.s_blk +
-                (int64_t)h0 * a.s_h + (int64_t)(s_lo - j * bs) * a.du;
-  const int64_t w_h = (int64_t)n_b * a.du;  // wire units per head of this sequence
-  u32x4* wire = (u32x4*)a.wire + wslab * a.m.w_slab + (int64_t)p_b * a.heads * a.du +
-                (int64_t)h0 * w_h + (int64_t)(s_lo - t0_b) * a.du;
-
-  // Flattened (head, unit) index over the tile; loads unguarded as in the
-  // dense kernel (a lane past the end re-reads the last unit).  With two
-  // heads the index is below 2 * run, so one comparison names the head (an
-  // integer division here cost 3-4 % of the gather's bandwidth).
-  const int total = min(kPagedHeads, a.heads - h0) * run;
-  for (int base = 0; base < total; base += kPagedUnroll * kThreads) {
-    u32x4 v[kPagedUnroll];
-    int hh[kPagedUnroll], ee[kPagedUnroll];
-#pragma unroll
-    for (int i = 0; i < kPagedUnroll; ++i) {
-      const int idx = min(base + i * kThreads + (int)threadIdx.x, total - 1);
-      hh[i] = idx >= run ? 1 : 0;
-      ee[i] = idx - hh[i] * run;
-      v[i] = ld_nt((D == kPack) ? pool + hh[i] * a.s_h + ee[i] : wire + hh[i] * w_h + ee[i]);
+  uint32_t tile = blockIdx.x;
+  Seq q = {};
+  int first_blk = 0;  // of the sequence's logical blocks
+  int t0_l = 0, p_l = 0, p1_l = 0;
+  if constexpr (POOL) {
+    if constexpr (N == 64) {  // one sequence per lane, fetched beside the owner entry
+      t0_l = a.s.t0[lane];
+      p_l = a.s.tok[lane];
+      p1_l = a.s.tok[lane + 1];
     }
+    if constexpr (WIDE) {
+      const uint64_t t = xcd_chunk<uint64_t>(tile + (uint64_t)y * a.tiles,
+                                             (uint64_t)a.tiles * gridDim.y);
+      y = (int64_t)(t / (uint32_t)a.tiles);
+      tile = (uint32_t)(t - (uint64_t)y * a.tiles);
+    } else {
+      const uint32_t t = xcd_chunk<uint32_t>(tile + (uint32_t)y * a.tiles, a.tiles * gridDim.y);
+      y = a.d_tiles.div(t);
+      tile = t - (uint32_t)y * a.tiles;
+    }
+  } else {
+    q = find_seq(a.s, tile);
+    tile = q.k;
+    first_blk = a.d_bs.div(q.t0);
+  }
+  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y * a.m.slab_step) * a.s_slab;
+  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y * a.m.slab_step) * a.m.w_slab;
+
+  for (int step = 0; step < (WIDE ? a.steps : 1); ++step) {
+    // The tile's first unit: unit r0 of head h0 of block j0.
+    uint64_t f;
+    uint32_t j0, h0, r0;
+    if constexpr (WIDE) {
+      f = ((uint64_t)tile * a.steps + step) * kPagedTile;
+      const uint64_t hb = f / ub;
+      r0 = (uint32_t)(f - hb * ub);
+      j0 = (uint32_t)(hb / heads);
+      h0 = (uint32_t)(hb - (uint64_t)j0 * heads);
+    } else {
+      f = tile * kPagedTile;
+      const uint32_t hb = a.d_ub.div((uint32_t)f);
+      r0 = (uint32_t)f - hb * ub;
+      j0 = a.d_heads.div(hb);
+      h0 = hb - j0 * heads;
+    }
+    Seq u = q;  // ONE: the block's sequence
+    int blk1 = 0, j1 = 0;
+    if constexpr (ONE && POOL) {
+      blk1 = j0;
+      const int own = __builtin_amdgcn_readfirstlane(a.owner[blk1]);
+      if (own < 0) return;  // block not written by this call
+      u.b = a.d_max.div(own);
+      if (u.b >= a.nseq) return;
+      j1 = own - u.b * a.max_blocks;
+      if constexpr (N == 64) {
+        u.t0 = __builtin_amdgcn_readlane(t0_l, u.b);
+        u.p = __builtin_amdgcn_readlane(p_l, u.b);
+        u.n = __builtin_amdgcn_readlane(p1_l, u.b) - u.p;
+      } else {
+        u.t0 = a.s.t0[u.b];
+        u.p = a.s.tok[u.b];
+        u.n = a.s.tok[u.b + 1] - u.p;
+      }
+    } else if constexpr (ONE) {
+      j1 = first_blk + j0;
+      blk1 = __builtin_amdgcn_readfirstlane(a.bt[(int64_t)u.b * a.max_blocks + j1]);
+      if (blk1 < 0 || blk1 >= a.num_blocks) return;  // unmapped block: skipped
+    }
+
+    // Lanes whose unit lies outside the range (the first and last block of a
+    // sequence, unmapped blocks) move nothing.
+    int64_t po[kPagedUnroll], wo[kPagedUnroll];
+    bool ok[kPagedUnroll];
 #pragma unroll
     for (int i = 0; i < kPagedUnroll; ++i) {
-      if (base + i * kThreads + (int)threadIdx.x < total)
-        st_nt(v[i], (D == kPack) ? wire + hh[i] * w_h + ee[i] : pool + hh[i] * a.s_h + ee[i]);
+      // In pool order a wave's units follow each other (2 KB written in order:
+      // 1801 us against 1835 with the waves' units interleaved, LLaMA-2-70B
+      // pool); in table order they interleave (1 % faster).
+      const uint32_t idx = POOL ? (threadIdx.x & ~63u) * kPagedUnroll + i * 64 + lane
+                                : i * kThreads + threadIdx.x;
+      const uint32_t z = r0 + idx;
+      const uint32_t d = a.d_ub.div(z);
+      const uint32_t e = z - d * ub;
+      uint32_t h = h0 + d;
+      Seq s = u;
+      int j = j1;
+      ok[i] = true;
+      if constexpr (ONE) {
+        po[i] = (int64_t)blk1 * a.s_blk + (int64_t)h0 * ub + r0 + idx;
+      } else {
+        const uint32_t dj = a.d_heads.div(h);
+        h -= dj * heads;
+        if constexpr (POOL) {
+          const int blk = j0 + dj;
+          ok[i] = blk < a.num_blocks;
+          const int own = a.owner[min(blk, a.num_blocks - 1)];
+          s.b = a.d_max.div(max(own, 0));
+          ok[i] = ok[i] && own >= 0 && s.b < a.nseq;
+          j = own - s.b * a.max_blocks;
+          if (!ok[i]) s.b = 0;
+          if constexpr (N == 64) {
+            s.t0 = __shfl(t0_l, s.b, 64);
+            s.p = __shfl(p_l, s.b, 64);
+            s.n = __shfl(p1_l, s.b, 64) - s.p;
+          } else {
+            s.t0 = a.s.t0[s.b];
+            s.p = a.s.tok[s.b];
+            s.n = a.s.tok[s.b + 1] - s.p;
+          }
+          po[i] = (int64_t)(f + idx);
+        } else {
+          j = first_blk + j0 + dj;
+          // past the sequence's last block the range test below fails
+          const int blk = a.bt[(int64_t)s.b * a.max_blocks + min(j, a.max_blocks - 1)];
+          ok[i] = blk >= 0 && blk < a.num_blocks;  // unmapped block: skipped
+          po[i] = (int64_t)blk * a.s_blk + (int64_t)h * ub + e;
+        }
+      }
+      // The unit's place in the head's run.  The last logical block ends below
+      // 2^30 units and a tile reaches at most one tile past it, so nothing
+      // here wraps.
+      const int pu = j * (int)ub + (int)e - s.t0 * a.du;
+      const int run = s.n * a.du;
+      ok[i] = ok[i] && (uint32_t)pu < (uint32_t)run;
+      wo[i] = (int64_t)s.p * ((int64_t)heads * a.du) + (int64_t)h * run + pu;
+    }
+    if constexpr (ONE) {
+      // One access in flight per wave: load, store, and the store's end before
+      // the next load.  With the chip full of waves that is enough, and random
+      // blocks are served better: gather and pool-order scatter of the
+      // LLaMA-2-70B pool 1797 and 1801 us; without the last wait 1850 and 1803,
+      // with two loads in flight 1885 and 1870.
+#pragma unroll
+      for (int i = 0; i < kPagedUnroll; ++i) {
+        if (ok[i])
+          st_nt(ld_nt((D == kPack) ? pool + po[i] : wire + wo[i]),
+                (D == kPack) ? wire + wo[i] : pool + po[i]);
+        if (i + 1 < kPagedUnroll) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+    } else {
+      // Both loads in flight (up to 2 % faster than one here, where a wave has
+      // more to work out first), without guards: an idle lane reads the slab's
+      // first unit instead.
+      u32x4 v[kPagedUnroll];
+#pragma unroll
+      for (int i = 0; i < kPagedUnroll; ++i)
+        v[i] = (D == kPack) ? ld_nt(pool + (ok[i] ? po[i] : 0))
+                            : ld_nt(wire + (ok[i] ? wo[i] : 0));
+#pragma unroll
+      for (int i = 0; i < kPagedUnroll; ++i)
+        if (ok[i]) st_nt(v[i], (D == kPack) ? wire + wo[i] : pool + po[i]);
     }
   }
 }
 
-// Pool order for calls of more than 64 sequences (stream-in only): grid
-// (num_blocks * head pairs, nslabs); as paged_kernel's pool order, but one
-// launch covers every sequence of the call, a sequence's range and token
-// prefix coming from the arguments instead of a wavefront scan.  (For up to
-// 64 sequences paged_kernel is used: there the ranges load in parallel with
-// the owner entry, where here they depend on it; measured on MI355X this
-// kernel was 2.8 % slower on the LLaMA-2-70B pool's 32 sequences.)
-__global__ void __launch_bounds__(kThreads) paged_pool_kernel(PoolOrderArgs a) {
-  const int bs = a.block_size;
-  const int ngrp = (a.heads + kPagedHeads - 1) / kPagedHeads;
-  int tile;
-  int64_t y;
-  xcd_chunk_tile(&tile, &y);
-  const int blk = tile / ngrp;
-  const int grp = tile - blk * ngrp;
-  const int own = __builtin_amdgcn_readfirstlane(a.owner[blk]);
-  if (own < 0) return;  // block not written by this call
-  const int b = own / a.max_blocks;
-  const int j = own - b * a.max_blocks;
-  if (b >= a.nseq) return;
-  const int n_b = a.n[b];
-  const int t0_b = a.t0[b];
-  const int p_b = a.p[b];
-  const int s_lo = max(t0_b, j * bs);
-  const int s_hi = min(t0_b + n_b, (j + 1) * bs);
-  if (s_lo >= s_hi) return;
-
-  const int run = (s_hi - s_lo) * a.du;
-  const int64_t slab = a.m.slab0 + y * a.m.slab_step;
-  const int64_t wslab = a.m.wslab0 + y * a.m.slab_step;
-  const int h0 = grp * kPagedHeads;
-  u32x4* pool = (u32x4*)a.pool + slab * a.s_slab + (int64_t)blk * a.s_blk +
-                (int64_t)h0 * a.s_h + (int64_t)(s_lo - j * bs) * a.du;
-  const int64_t w_h = (int64_t)n_b * a.du;
-  u32x4* wire = (u32x4*)a.wire + wslab * a.m.w_slab + (int64_t)p_b * a.heads * a.du +
-                (int64_t)h0 * w_h + (int64_t)(s_lo - t0_b) * a.du;
-  const int total = min(kPagedHeads, a.heads - h0) * run;
-  for (int base = 0; base < total; base += kPagedUnroll * kThreads) {
+// Paged runs in wire order: grid (tiles_per_slab, nslabs).  Every lane holds a
+// unit of the range itself, however little of its blocks the range covers.
+template <int D, int N>
+__global__ void __launch_bounds__(kThreads) paged_runs_kernel(PagedRunArgs<N> a) {
+  const Seq q = find_seq(a.s, blockIdx.x);
+  const uint32_t run = q.n * a.du;  // units per head
+  const float rcp = 1.0f / (float)run;
+  const int64_t y = blockIdx.y;
+  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y * a.m.slab_step) * a.s_slab;
+  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y * a.m.slab_step) * a.m.w_slab +
+                (int64_t)q.p * ((int64_t)a.heads * a.du);
+  const int32_t* row = a.bt + (int64_t)q.b * a.max_blocks;
+  const int64_t units = (int64_t)a.heads * run;
+  for (int step = 0; step < a.steps; ++step) {
+    const int64_t f = ((int64_t)q.k * a.steps + step) * kPagedTile;
+    if (f >= units) return;
+    // The tile starts at unit r0 of head h0's run.
+    const uint32_t h0 = f >> 32 ? (uint32_t)(f / run) : (uint32_t)f / run;
+    const uint32_t r0 = (uint32_t)(f - (int64_t)h0 * run);
     u32x4 v[kPagedUnroll];
-    int hh[kPagedUnroll], ee[kPagedUnroll];
+    int64_t po[kPagedUnroll];
+    bool ok[kPagedUnroll];
 #pragma unroll
     for (int i = 0; i < kPagedUnroll; ++i) {
-      const int idx = min(base + i * kThreads + (int)threadIdx.x, total - 1);
-      hh[i] = idx >= run ? 1 : 0;
-      ee[i] = idx - hh[i] * run;
-      v[i] = ld_nt(wire + hh[i] * w_h + ee[i]);
+      const uint32_t idx = i * kThreads + threadIdx.x;
+      // Runs passed since r0: at most one where a run is longer than a tile;
+      // else z < 2^10, (z + 1/2) / run is at least 2^-10 away from an integer
+      // and its error in float below 2^-12.
+      const uint32_t z = r0 + idx;
+      const uint32_t d = run >= (uint32_t)kPagedTile ? (z >= run)
+                                                     : (uint32_t)(((float)z + 0.5f) * rcp);
+      const uint32_t h = h0 + d;
+      ok[i] = f + idx < units;
+      const uint32_t pu = ok[i] ? q.t0 * a.du + (z - d * run) : q.t0 * a.du;
+      const uint32_t j = a.d_ub.div(pu);
+      const int blk = row[j];
+      ok[i] = ok[i] && blk >= 0 && blk < a.num_blocks;  // unmapped block: skipped
+      po[i] = (int64_t)blk * a.s_blk + (int64_t)h * a.ub + (pu - j * a.ub);
+      v[i] = (D == kPack) ? ld_nt(pool + (ok[i] ? po[i] : 0))
+                          : ld_nt(wire + (ok[i] ? f + idx : 0));
     }
 #pragma unroll
-    for (int i = 0; i < kPagedUnroll; ++i) {
-      if (base + i * kThreads + (int)threadIdx.x < total) st_nt(v[i], pool + hh[i] * a.s_h + ee[i]);
-    }
+    for (int i = 0; i < kPagedUnroll; ++i)
+      if (ok[i])
+        st_nt(v[i], (D == kPack) ? wire + f + i * kThreads + threadIdx.x : pool + po[i]);
   }
 }
 
@@ -605,20 +722,44 @@ hipError_t launch_dense_runs(int dir, const DenseRunArgs& a, uint32_t tiles_per_
   return launch(fn, dim3(tiles_per_slab, nslabs), a, s);
 }
 
-hipError_t launch_paged(int dir, const PagedArgs& a, uint32_t tiles_per_slab, uint32_t nslabs,
+namespace {
+
+template <int N, bool ONE, bool WIDE>
+const void* paged_fn(int dir, bool pool) {
+  if (pool) return (const void*)&paged_kernel<kUnpack, true, ONE, WIDE, N>;
+  return dir == kPack ? (const void*)&paged_kernel<kPack, false, ONE, WIDE, N>
+                      : (const void*)&paged_kernel<kUnpack, false, ONE, WIDE, N>;
+}
+
+}  // namespace
+
+template <int N>
+hipError_t launch_paged(int dir, const PagedArgs<N>& a, bool wide, uint32_t nslabs,
                         hipStream_t s) {
-  const void* fn =
-      dir == kPack ? (const void*)&paged_kernel<kPack> : (const void*)&paged_kernel<kUnpack>;
+  const bool pool = a.owner != nullptr;
+  const void* fn = wide                          ? paged_fn<N, false, true>(dir, pool)
+                   : a.s_blk % kPagedTile == 0 ? paged_fn<N, true, false>(dir, pool)
+                                               : paged_fn<N, false, false>(dir, pool);
+  return launch(fn, dim3(a.tiles, nslabs), a, s);
+}
+template <int N>
+hipError_t launch_paged_runs(int dir, const PagedRunArgs<N>& a, uint32_t tiles_per_slab,
+                             uint32_t nslabs, hipStream_t s) {
+  const void* fn = dir == kPack ? (const void*)&paged_runs_kernel<kPack, N>
+                                : (const void*)&paged_runs_kernel<kUnpack, N>;
   return launch(fn, dim3(tiles_per_slab, nslabs), a, s);
 }
+template hipError_t launch_paged<kSeqPerLaunch>(int, const PagedArgs<kSeqPerLaunch>&, bool,
+                                                uint32_t, hipStream_t);
+template hipError_t launch_paged<kSeqMany>(int, const PagedArgs<kSeqMany>&, bool, uint32_t,
+                                           hipStream_t);
+template hipError_t launch_paged_runs<kSeqPerLaunch>(int, const PagedRunArgs<kSeqPerLaunch>&,
+                                                     uint32_t, uint32_t, hipStream_t);
+template hipError_t launch_paged_runs<kSeqMany>(int, const PagedRunArgs<kSeqMany>&, uint32_t,
+                                                uint32_t, hipStream_t);
 
 // Workgroups of kThreads lanes covering n items (n up to INT32_MAX).
 static uint32_t groups_of(int32_t n) { return (uint32_t)(((int64_t)n + kThreads - 1) / kThreads); }
-
-hipError_t launch_paged_pool_order(const PoolOrderArgs& a, uint32_t tiles_per_slab,
-                                   uint32_t nslabs, hipStream_t s) {
-  return launch((const void*)&paged_pool_kernel, dim3(tiles_per_slab, nslabs), a, s);
-}
 
 hipError_t launch_owner_clear(const OwnerArgs& a, hipStream_t s) {
   return launch((const void*)&owner_clear_kernel, dim3(groups_of(a.num_blocks)), a, s);
