@@ -351,6 +351,74 @@ int run_paged(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
   return DV_OK;
 }
 
+// A stream of short runs (or any whose slabs hold fewer than 2^31 units), in
+// launches of at most N sequences that have tokens and fewer than 2^31 units.
+template <int N>
+int run_rows(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<int32_t>& t0,
+             const std::vector<int32_t>& n, int64_t w_slab, void* wire, hipStream_t st) {
+  dv::RowArgs<N> a;
+  memset(&a, 0, sizeof a);
+  a.cache = v.base;
+  a.bt = v.bt;
+  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.du = (int32_t)v.du;
+  a.heads = (int32_t)v.H;
+  a.d_du = dv::fast_div((uint32_t)v.du);
+  a.d_heads = dv::fast_div((uint32_t)v.H);
+  a.d_bs = dv::fast_div(1);
+  for (int half = 0; half < 2; ++half) {
+    a.s_tok[half] = v.du;
+    a.s_e[half] = 1;
+  }
+  if (v.kind == DV_PAGED) {
+    a.paged = 1;
+    a.block_size = (int32_t)v.bs;
+    a.num_blocks = (int32_t)v.NB;
+    a.max_blocks = (int32_t)v.max_blocks;
+    a.s_slab = v.NB * v.H * v.bs * v.du;
+    a.s_b = v.H * v.bs * v.du;
+    a.s_h = v.bs * v.du;
+    a.d_bs = dv::fast_div((uint32_t)v.bs);
+  } else {
+    a.s_slab = v.B * v.H * v.S * v.du;
+    a.s_b = v.H * v.S * v.du;
+    a.s_h = v.S * v.du;
+    if (v.kind == DV_DENSE_KSPLIT) {  // key slabs: groups S units apart, tokens 1
+      a.s_tok[0] = 1;
+      a.s_e[0] = v.S;
+    }
+  }
+  const int64_t row = v.H * v.du;  // units of one token
+  int64_t p = 0;                   // tokens of all earlier launches
+  for (int64_t b = 0; b < v.B;) {
+    int nseq = 0;
+    int64_t tok = 0;
+    bool even = true;
+    for (; b < v.B && nseq < N; ++b) {
+      if (n[b] == 0) continue;
+      if ((tok + n[b]) * row >= (1ll << 31)) break;
+      a.tok[nseq] = (int32_t)tok;
+      a.t0[nseq] = t0[b];
+      a.seq[nseq] = (int32_t)b;
+      if (nseq == 0) a.n = n[b];
+      even = even && n[b] == a.n;
+      ++nseq;
+      tok += n[b];
+    }
+    if (nseq == 0) continue;  // only sequences without tokens were left
+    a.tok[nseq] = (int32_t)tok;
+    for (int i = nseq + 1; i <= N; ++i) a.tok[i] = INT32_MAX;
+    a.wire = static_cast<char*>(wire) + (uint64_t)p * row * 16;
+    a.total = (int32_t)(tok * row);
+    a.d_seq = dv::fast_div((uint32_t)(v.H * a.n));
+    a.d_n = dv::fast_div((uint32_t)a.n);
+    const hipError_t e = dv::launch_rows<N>(dir, even, a, 2 * nl, st);
+    if (e != hipSuccess) return hip_fail(e, "short-run kernel launch");
+    p += tok;
+  }
+  return DV_OK;
+}
+
 // Enqueue the pack (dir = kPack) or unpack of the validated ranges.  The wire
 // is at `wire`; per (layer, K|V) slab it holds N*H*du units.
 int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector<int32_t>& t0,
@@ -389,7 +457,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     }
   }
 
-  bool flat = small;  // the short-run kernel
+  bool flat = single || small;  // the short-run kernel
   if (v.kind == DV_PAGED && !single && !small) {
     // Tiles over whole blocks leave the lanes of tokens outside the range
     // idle: where the range covers less than three quarters of its blocks,
@@ -415,6 +483,10 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
                  : run_paged<kSeqPerLaunch>(dir, how, v, l0, nl, t0, n, w_slab, wire, st);
   }
 
+  if (flat)
+    return v.B > kSeqPerLaunch ? run_rows<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
+                               : run_rows<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
+
   int64_t p_group = 0;  // tokens of all earlier launch groups
   for (int64_t g0 = 0; g0 < v.B; g0 += kSeqPerLaunch) {
     const int nseq = (int)std::min<int64_t>(kSeqPerLaunch, v.B - g0);
@@ -429,110 +501,6 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     for (int i = 0; i < nseq; ++i) {
       r.t0[i] = t0[g0 + i];
       r.n[i] = n[g0 + i];
-    }
-
-    if (single) {
-      dv::TokenArgs a;
-      memset(&a, 0, sizeof a);
-      a.cache = v.base;
-      a.wire = wire_g;
-      a.bt = v.bt;
-      a.du = (int32_t)v.du;
-      a.heads = (int32_t)v.H;
-      a.nseq = nseq;
-      a.b0 = (int32_t)g0;
-      for (int i = 0; i < kSeqPerLaunch; ++i) a.pos[i] = (i < nseq && r.n[i] == 1) ? r.t0[i] : -1;
-      const uint32_t units = (uint32_t)(ntok * v.H * v.du);
-      hipError_t e;
-      if (v.kind == DV_PAGED) {
-        a.paged = 1;
-        a.block_size = (int32_t)v.bs;
-        a.num_blocks = (int32_t)v.NB;
-        a.max_blocks = (int32_t)v.max_blocks;
-        a.s_slab = v.NB * v.H * v.bs * v.du;
-        a.s_blk = v.H * v.bs * v.du;
-        a.s_h = v.bs * v.du;
-        a.s_tok = v.du;
-        a.s_e = 1;
-        a.m = {2 * l0, 1, 0, 0, w_slab};
-        e = dv::launch_token(dir, a, units, 2 * nl, st);
-      } else {
-        a.s_slab = v.B * v.H * v.S * v.du;
-        a.s_b = v.H * v.S * v.du;
-        a.s_h = v.S * v.du;
-        if (v.kind == DV_DENSE) {
-          a.s_tok = v.du;
-          a.s_e = 1;
-          a.m = {2 * l0, 1, 0, 0, w_slab};
-          e = dv::launch_token(dir, a, units, 2 * nl, st);
-        } else {
-          // split key slabs: groups S units apart, tokens 1 unit apart
-          a.s_tok = 1;
-          a.s_e = v.S;
-          a.m = {2 * l0, 2, 0, 0, w_slab};
-          e = dv::launch_token(dir, a, units, nl, st);
-          if (e == hipSuccess) {
-            a.s_tok = v.du;
-            a.s_e = 1;
-            a.m = {2 * l0 + 1, 2, 1, 0, w_slab};
-            e = dv::launch_token(dir, a, units, nl, st);
-          }
-        }
-      }
-      if (e != hipSuccess) return hip_fail(e, "token kernel launch");
-      continue;
-    }
-
-    if (flat) {
-      dv::SmallRunArgs a;
-      memset(&a, 0, sizeof a);
-      a.cache = v.base;
-      a.wire = wire_g;
-      a.bt = v.bt;
-      a.du = (int32_t)v.du;
-      a.heads = (int32_t)v.H;
-      a.nseq = nseq;
-      a.b0 = (int32_t)g0;
-      a.r = r;
-      const int64_t units = ntok * v.H * v.du;  // below 2^31: checked above (paged: w_slab is)
-      hipError_t e;
-      if (v.kind == DV_PAGED) {
-        a.paged = 1;
-        a.block_size = (int32_t)v.bs;
-        a.num_blocks = (int32_t)v.NB;
-        a.max_blocks = (int32_t)v.max_blocks;
-        a.s_slab = v.NB * v.H * v.bs * v.du;
-        a.s_blk = v.H * v.bs * v.du;
-        a.s_h = v.bs * v.du;
-        a.s_tok = v.du;
-        a.s_e = 1;
-        a.m = {2 * l0, 1, 0, 0, w_slab};
-        e = dv::launch_small_runs(dir, a, (uint32_t)units, 2 * nl, st);
-      } else {
-        a.s_slab = v.B * v.H * v.S * v.du;
-        a.s_b = v.H * v.S * v.du;
-        a.s_h = v.S * v.du;
-        if (v.kind == DV_DENSE) {
-          a.s_tok = v.du;
-          a.s_e = 1;
-          a.m = {2 * l0, 1, 0, 0, w_slab};
-          e = dv::launch_small_runs(dir, a, (uint32_t)units, 2 * nl, st);
-        } else {
-          // split key slabs: groups S units apart, tokens 1 unit apart
-          a.s_tok = 1;
-          a.s_e = v.S;
-          a.m = {2 * l0, 2, 0, 0, w_slab};
-          e = dv::launch_small_runs(dir, a, (uint32_t)units, nl, st);
-          if (e == hipSuccess) {
-            a.s_tok = v.du;
-            a.s_e = 1;
-            a.m = {2 * l0 + 1, 2, 1, 0, w_slab};
-            e = dv::launch_small_runs(dir, a, (uint32_t)units, nl, st);
-          }
-        }
-      }
-      if (e != hipSuccess) return hip_fail(e, "short-run kernel launch");
-      continue;
     }
 
     dv::DenseRunArgs a;

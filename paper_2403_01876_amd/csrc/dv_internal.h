@@ -135,47 +135,34 @@ struct OwnerArgs {
   SeqRanges r;
 };
 
-// Single-token ranges (decode-step increments): one unit per lane over the
-// flattened (active sequence, head, unit) space of each slab.
-struct TokenArgs {
+// Short runs (decode-step increments of one or a few tokens per sequence):
+// the 16-byte units of a slab in wire order, (sequence, head, token, group),
+// spread evenly over the lanes, so that none idles the way it would in a tile
+// sized for long runs.  A row is one token of one head: du units.  Only the
+// sequences with a token in the range are listed; unit g of a row sits at
+// cache offset sequence or block + head * s_h + token * s_tok[half] + g *
+// s_e[half], half 0 for key slabs and 1 for value slabs (a split-key cache's
+// differ), and both halves go in one launch.
+template <int N>
+struct RowArgs {
   void* cache;
-  void* wire;
-  const int32_t* bt;  // paged only
+  void* wire;          // contiguous buffer advanced to this launch's first sequence
+  const int32_t* bt;   // paged only
   int64_t s_slab;
-  int64_t s_b;        // dense: units per sequence
-  int64_t s_blk;      // paged: units per block
-  int64_t s_h;        // units per head (dense: S*du; paged: bs*du; split key: S*du)
-  int64_t s_tok;      // units per token (du, or 1 in a split key slab)
-  int64_t s_e;        // units between consecutive 16-byte groups of one token
-                      // (1, or S in a split key slab)
+  int64_t s_b;         // dense: units per sequence; paged: units per block
+  int64_t s_h;         // units per head
+  int64_t s_tok[2], s_e[2];
   SlabMap m;
-  int32_t du, heads, nseq, b0;
+  int32_t total;       // units per slab of this launch (below 2^31)
+  int32_t du, heads;
   int32_t paged, block_size, num_blocks, max_blocks;
-  int32_t pos[kSeqPerLaunch];  // token of each sequence, < 0 = inactive
+  int32_t n;           // tokens of every sequence, where they are equal
+  FastDiv d_du, d_heads, d_seq, d_n, d_bs;  // d_seq: heads * n
+  int32_t tok[N + 1];  // ragged: tokens of all earlier sequences; INT32_MAX past the last
+  int32_t t0[N];       // first token of each sequence's range
+  int32_t seq[N];      // its index in the cache
 };
-
-// Short runs (a few tokens per sequence, e.g. a decode step that accepts
-// several tokens): one 16-byte unit per lane over the flattened wire order
-// of each slab, (sequence, head, token, unit), so no lane idles the way it
-// would in a tile sized for long runs.  Unit e of sequence b's run for head
-// h holds token t0 + e / du, group e % du, at cache offset
-// (t0 + e / du) * s_tok + (e % du) * s_e from the (sequence, head) base;
-// paged caches find the token's block through the table.
-struct SmallRunArgs {
-  void* cache;
-  void* wire;
-  const int32_t* bt;  // paged only
-  int64_t s_slab;
-  int64_t s_b;        // dense: units per sequence
-  int64_t s_blk;      // paged: units per block
-  int64_t s_h;        // units per head
-  int64_t s_tok;      // units per token (du, or 1 in a split key slab)
-  int64_t s_e;        // units between consecutive 16-byte groups of a token (1, or S)
-  SlabMap m;
-  int32_t du, heads, nseq, b0;
-  int32_t paged, block_size, num_blocks, max_blocks;
-  SeqRanges r;
-};
+static_assert(sizeof(RowArgs<kSeqMany>) <= 3584, "arguments stay well under 4 KB");
 
 // Split-key slab: 64-token tiles transposed through LDS.
 struct KsplitArgs {
@@ -226,10 +213,9 @@ hipError_t launch_owner_build(const OwnerArgs& a, hipStream_t s);
 // [b0, b0 + nseq) that map to it, into `a.owner` (int32 counts), clearing
 // the counts first when `clear` is set.
 hipError_t launch_block_claims(const OwnerArgs& a, bool clear, hipStream_t s);
-hipError_t launch_token(int dir, const TokenArgs& a, uint32_t units_per_slab, uint32_t nslabs,
-                        hipStream_t s);
-hipError_t launch_small_runs(int dir, const SmallRunArgs& a, uint32_t units_per_slab,
-                             uint32_t nslabs, hipStream_t s);
+// `even`: every sequence has a.n tokens.
+template <int N>
+hipError_t launch_rows(int dir, bool even, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s);
 hipError_t launch_ksplit(int dir, const KsplitArgs& a, uint32_t tiles_per_slab, uint32_t nslabs,
                          hipStream_t s);
 hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs, hipStream_t s);

@@ -435,122 +435,112 @@ __global__ void __launch_bounds__(kThreads) owner_build_kernel(OwnerArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Single tokens: grid (ceil(units_per_slab / 256), nslabs).  Lane u of a
-// slab moves wire unit u; the active sequences are ranked once per
-// workgroup into LDS together with the cache offset of their token.
+// Short runs: grid (ceil(total / (256 * U)), nslabs); see RowArgs.  Each lane
+// moves U units of its slab, 256 apart.
+//
+// Small calls are bound by the launch and by one chain of dependent loads
+// (arguments, the sequence's place, a table entry, the data), larger ones by
+// instructions: what a unit costs to find.  Where every sequence has the same
+// number of tokens (a decode step), three multiplications find it.  Ragged
+// rows are found once per row, by as many lanes as the workgroup has rows, and
+// left in LDS for the units.  Before, every unit searched for its sequence and
+// divided three times, 64 sequences to a launch and a split-key cache's halves
+// apart (graph replays, one way in and one out): 32 sequences of 1-8 tokens, 8
+// heads x 128 x 2 bytes, 20 layers, paged, 16.3 -> 11.2 us; one token of 256
+// such sequences 36.6 -> 20.0; of 8 sequences of 72 heads, 16 layers, split
+// key, 19.7 -> 15.0; of 8 sequences of 40 heads, 10 layers, dense, 4.9 -> 4.3.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kThreads) token_kernel(TokenArgs a) {
-  __shared__ int64_t s_base[kSeqPerLaunch];
+template <int D, int U, bool EVEN, int N>
+__global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
   const int lane = lane_id();
-  const int p = lane < a.nseq ? a.pos[lane] : -1;
-  const uint64_t act = __ballot(p >= 0);
-  const int nact = __popcll(act);
-  if (threadIdx.x < 64 && p >= 0) {
-    const int rank = __popcll(act & ((1ull << lane) - 1ull));
-    const int b = a.b0 + lane;
-    int64_t base;
-    if (!a.paged) {
-      base = (int64_t)b * a.s_b + (int64_t)p * a.s_tok;
-    } else {
-      const int blk = a.bt[(int64_t)b * a.max_blocks + p / a.block_size];
-      base = (blk >= 0 && blk < a.num_blocks)
-                 ? (int64_t)blk * a.s_blk + (int64_t)(p % a.block_size) * a.s_tok
-                 : -1;
-    }
-    s_base[rank] = base;
-  }
-  __syncthreads();
-
-  const int hd = a.heads * a.du;
-  const int u = blockIdx.x * kThreads + threadIdx.x;
-  if (u >= nact * hd) return;
-  const int rank = u / hd;
-  const int rem = u - rank * hd;
-  const int h = rem / a.du;
-  const int e = rem - h * a.du;
-  const int64_t base = s_base[rank];
-  if (base < 0) return;  // unmapped block: skipped
-
   const int64_t y = blockIdx.y;
-  const int64_t slab = a.m.slab0 + y * a.m.slab_step;
-  const int64_t wslab = a.m.wslab0 + y * a.m.slab_step;
-  u32x4* cache = (u32x4*)a.cache + slab * a.s_slab + base + (int64_t)h * a.s_h +
-                 (int64_t)e * a.s_e;
-  u32x4* wire = (u32x4*)a.wire + wslab * a.m.w_slab + u;
-  if (D == kPack)
-    st_nt(ld_nt(cache), wire);
-  else
-    st_nt(ld_nt(wire), cache);
-}
+  const int half = (int)(y & 1);  // the launch starts at a layer's key slab
+  u32x4* cache = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab;
+  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y) * a.m.w_slab;
+  const int64_t s_tok = a.s_tok[half], s_e = a.s_e[half];
+  const uint32_t first = blockIdx.x * (kThreads * U);
+  const uint32_t last = min(first + kThreads * U, (uint32_t)a.total) - 1;
 
-// ---------------------------------------------------------------------------
-// Short runs: grid (ceil(units_per_slab / (256 * U)), nslabs).  Each lane
-// moves U wire units of the flattened (sequence, head, token, unit) order
-// of its slab, 256 units apart; the per-sequence prefix of run sizes sits in
-// LDS and a 6-step binary search names each unit's sequence (the
-// single-token kernel above skips the search, since there every run is one
-// token).  Loads are clamped to the last unit and issue before any store.
-// ---------------------------------------------------------------------------
-template <int D, int U>
-__global__ void __launch_bounds__(kThreads) small_runs_kernel(SmallRunArgs a) {
-  __shared__ int s_incl[kSeqPerLaunch];  // inclusive prefix of n_b * heads * du
-  __shared__ int s_run[kSeqPerLaunch];   // n_b * du: units per head of sequence b
-  __shared__ int s_t0[kSeqPerLaunch];
-  const int lane = lane_id();
-  if (threadIdx.x < 64) {
-    int n = 0, t0 = 0;
-    if (lane < a.nseq) {
-      n = a.r.n[lane];
-      t0 = a.r.t0[lane];
+  // Cache offset of token s of head h of the sequence; negative where its block
+  // is unmapped (skipped).
+  auto row_offset = [&](int seq, uint32_t h, uint32_t s) -> int64_t {
+    int64_t o = (int64_t)h * a.s_h;
+    if (!a.paged) return o + (int64_t)seq * a.s_b + (int64_t)s * s_tok;
+    const uint32_t j = a.d_bs.div(s);
+    const int blk = a.bt[(int64_t)seq * a.max_blocks + j];
+    if (blk < 0 || blk >= a.num_blocks) return -1;
+    return o + (int64_t)blk * a.s_b + (int64_t)(s - j * a.block_size) * s_tok;
+  };
+
+  __shared__ int64_t s_off[EVEN ? 1 : kThreads * U + 1];
+  const uint32_t row0 = EVEN ? 0 : a.d_du.div(first);
+  if constexpr (!EVEN) {
+    const uint32_t rows = a.d_du.div(last) - row0 + 1;
+    // Every lane of a wave that has rows takes one (the last one again past
+    // the end), so that lanes can read each other's sequences.
+    for (uint32_t k = threadIdx.x & ~63u; k < rows; k += kThreads) {
+      const uint32_t r = row0 + min(k + lane, rows - 1);
+      const uint32_t q = a.d_heads.div(r);  // tok[b] <= q < tok[b + 1]
+      const int qlo = a.d_heads.div(row0 + k);
+      const int qhi = a.d_heads.div(row0 + min(k + 63, rows - 1));
+      int b, b1 = -1, p, p1, t0, seq;
+      if constexpr (N == 64) {
+        const int tok = a.tok[lane];
+        b = __popcll(__ballot(tok <= qlo)) - 1;
+        b1 = __popcll(__ballot(tok <= qhi)) - 1;
+        const int b0 = b;
+        for (int i = b0 + 1; i <= b1; ++i) b += __builtin_amdgcn_readlane(tok, i) <= (int)q;
+        p = __shfl(tok, b, 64);
+        p1 = a.tok[b + 1];
+        t0 = __shfl(a.t0[lane], b, 64);
+        seq = __shfl(a.seq[lane], b, 64);
+      } else {
+        b = -1;
+#pragma unroll
+        for (int i = 0; i < N / 64; ++i) {
+          const int tok = a.tok[i * 64 + lane];
+          b += __popcll(__ballot(tok <= qlo));
+          b1 += __popcll(__ballot(tok <= qhi));
+        }
+        const int b0 = b;
+        for (int i = b0 + 1; i <= b1; ++i) b += a.tok[i] <= (int)q;
+        p = a.tok[b];
+        p1 = a.tok[b + 1];
+        t0 = a.t0[b];
+        seq = a.seq[b];
+      }
+      const uint32_t n = p1 - p, rr = r - (uint32_t)p * a.heads;
+      const uint32_t h = rr / n;
+      const int64_t o = row_offset(seq, h, t0 + (rr - h * n));
+      if (k + lane < rows) s_off[k + lane] = o;
     }
-    s_incl[lane] = wave_incl_scan(n * a.heads * a.du);
-    s_run[lane] = n * a.du;
-    s_t0[lane] = t0;
+    __syncthreads();
   }
-  __syncthreads();
-  const int total = s_incl[kSeqPerLaunch - 1];
-  const int64_t y = blockIdx.y;
-  const int64_t slab = a.m.slab0 + y * a.m.slab_step;
-  const int64_t wslab = a.m.wslab0 + y * a.m.slab_step;
-  u32x4* cache_slab = (u32x4*)a.cache + slab * a.s_slab;
-  u32x4* wire_slab = (u32x4*)a.wire + wslab * a.m.w_slab;
+
+  // Loads carry no guard (a lane past the end reads the last unit again, one
+  // of an unmapped block the slab's first), so they issue back to back.
   int64_t co[U];
-  bool ok[U];
   u32x4 v[U];
 #pragma unroll
   for (int i = 0; i < U; ++i) {
-    const int u0 = (blockIdx.x * U + i) * kThreads + threadIdx.x;
-    const int u = min(u0, total - 1);
-    // The first sequence whose inclusive prefix exceeds u (it has n_b > 0).
-    int lo = 0, hi = kSeqPerLaunch - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (s_incl[mid] > u) hi = mid; else lo = mid + 1;
-    }
-    const int b = lo;
-    const int run = s_run[b];
-    const int rem = u - (s_incl[b] - run * a.heads);
-    const int h = rem / run;
-    const int e = rem - h * run;  // unit within the (sequence, head) run
-    const int t = e / a.du;
-    const int g = e - t * a.du;   // 16-byte group within the token
-    const int s = s_t0[b] + t;    // token position in the cache
-    ok[i] = u0 < total;
-    if (!a.paged) {
-      co[i] = (int64_t)(a.b0 + b) * a.s_b + (int64_t)s * a.s_tok;
+    const uint32_t u = min(first + i * kThreads + threadIdx.x, last);
+    const uint32_t row = a.d_du.div(u);
+    const uint32_t g = u - row * a.du;
+    if constexpr (EVEN) {
+      const uint32_t b = a.d_seq.div(row);
+      const uint32_t rr = row - b * (uint32_t)(a.heads * a.n);
+      const uint32_t h = a.d_n.div(rr);
+      co[i] = row_offset(a.seq[b], h, a.t0[b] + (rr - h * a.n));
     } else {
-      const int blk = a.bt[(int64_t)(a.b0 + b) * a.max_blocks + s / a.block_size];
-      ok[i] = ok[i] && blk >= 0 && blk < a.num_blocks;  // unmapped block: skipped
-      co[i] = (int64_t)(ok[i] ? blk : 0) * a.s_blk + (int64_t)(s % a.block_size) * a.s_tok;
+      co[i] = s_off[row - row0];
     }
-    co[i] += (int64_t)h * a.s_h + (int64_t)g * a.s_e;
-    v[i] = ld_nt((D == kPack) ? cache_slab + co[i] : wire_slab + u);
+    if (co[i] >= 0) co[i] += (int64_t)g * s_e;
+    v[i] = (D == kPack) ? ld_nt(cache + (co[i] >= 0 ? co[i] : 0)) : ld_nt(wire + u);
   }
 #pragma unroll
   for (int i = 0; i < U; ++i) {
-    const int u = (blockIdx.x * U + i) * kThreads + threadIdx.x;
-    if (ok[i]) st_nt(v[i], (D == kPack) ? wire_slab + u : cache_slab + co[i]);
+    const uint32_t u = first + i * kThreads + threadIdx.x;
+    if (u <= last && co[i] >= 0) st_nt(v[i], (D == kPack) ? wire + u : cache + co[i]);
   }
 }
 
@@ -778,28 +768,29 @@ hipError_t launch_block_claims(const OwnerArgs& a, bool clear, hipStream_t s) {
   return launch((const void*)&claims_count_kernel, dim3(groups_of(a.max_blocks), a.nseq), a, s);
 }
 
-hipError_t launch_token(int dir, const TokenArgs& a, uint32_t units_per_slab, uint32_t nslabs,
-                        hipStream_t s) {
-  const void* fn =
-      dir == kPack ? (const void*)&token_kernel<kPack> : (const void*)&token_kernel<kUnpack>;
-  return launch(fn, dim3((units_per_slab + kThreads - 1) / kThreads, nslabs), a, s);
-}
-
-hipError_t launch_small_runs(int dir, const SmallRunArgs& a, uint32_t units_per_slab,
-                             uint32_t nslabs, hipStream_t s) {
-  // Two units per lane once a launch moves 8 MB or more; measured on MI355X
-  // for 2-16 tokens per sequence, one unit per lane is faster below that
-  // (fewer dependent steps per lane) and two above (fewer workgroups).
-  const bool two = (uint64_t)units_per_slab * nslabs >= (1ull << 19);
+template <int N>
+hipError_t launch_rows(int dir, bool even, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s) {
+  // Even launches take one unit per lane at every size (paged step of 256
+  // sequences, 10.5 MB: 9.8 us one way against 10.4 with two; 82 MB: 31.0
+  // against 32.0); ragged ones two from 4 MB on, where a workgroup's rows and
+  // barrier count (5.9 MB: 5.6 against 6.6 us; 144 MB: 50 against 55).
+  const bool two = !even && (uint64_t)a.total * nslabs >= (1ull << 18);
+  const uint32_t per = kThreads * (two ? 2 : 1);
   const void* fn;
   if (dir == kPack)
-    fn = two ? (const void*)&small_runs_kernel<kPack, 2> : (const void*)&small_runs_kernel<kPack, 1>;
+    fn = even  ? (const void*)&rows_kernel<kPack, 1, true, N>
+         : two ? (const void*)&rows_kernel<kPack, 2, false, N>
+               : (const void*)&rows_kernel<kPack, 1, false, N>;
   else
-    fn = two ? (const void*)&small_runs_kernel<kUnpack, 2>
-             : (const void*)&small_runs_kernel<kUnpack, 1>;
-  const uint32_t per = kThreads * (two ? 2 : 1);
-  return launch(fn, dim3((units_per_slab + per - 1) / per, nslabs), a, s);
+    fn = even  ? (const void*)&rows_kernel<kUnpack, 1, true, N>
+         : two ? (const void*)&rows_kernel<kUnpack, 2, false, N>
+               : (const void*)&rows_kernel<kUnpack, 1, false, N>;
+  return launch(fn, dim3((uint32_t)(((uint64_t)a.total + per - 1) / per), nslabs), a, s);
 }
+template hipError_t launch_rows<kSeqPerLaunch>(int, bool, const RowArgs<kSeqPerLaunch>&, uint32_t,
+                                               hipStream_t);
+template hipError_t launch_rows<kSeqMany>(int, bool, const RowArgs<kSeqMany>&, uint32_t,
+                                          hipStream_t);
 
 hipError_t launch_ksplit(int dir, const KsplitArgs& a, uint32_t tiles_per_slab, uint32_t nslabs,
                          hipStream_t s) {
