@@ -388,6 +388,9 @@ int run_rows(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<
       a.s_e[0] = v.S;
     }
   }
+  const int32_t max_n = *std::max_element(n.begin(), n.end());
+  a.tile = (int32_t)std::max<int64_t>(1, dv::kThreads * dv::kRowsUnroll / v.du);
+  a.d_tile = dv::fast_div((uint32_t)a.tile);
   const int64_t row = v.H * v.du;  // units of one token
   int64_t p = 0;                   // tokens of all earlier launches
   for (int64_t b = 0; b < v.B;) {
@@ -412,9 +415,48 @@ int run_rows(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<
     a.total = (int32_t)(tok * row);
     a.d_seq = dv::fast_div((uint32_t)(v.H * a.n));
     a.d_n = dv::fast_div((uint32_t)a.n);
-    const hipError_t e = dv::launch_rows<N>(dir, even, a, 2 * nl, st);
+    // Key slabs through LDS from 4 MB on; smaller launches are bound by
+    // latency (1.9 MB: 3.1 us out against 2.7 without, 4.2 in against 4.3).
+    const bool split = v.kind == DV_DENSE_KSPLIT && max_n > 1 &&
+                       (int64_t)a.total * 2 * nl >= (1 << 18);
+    const hipError_t e = split ? dv::launch_split_rows<N>(dir, a, 2 * nl, st)
+                               : dv::launch_rows<N>(dir, even, a, 2 * nl, st);
     if (e != hipSuccess) return hip_fail(e, "short-run kernel launch");
     p += tok;
+  }
+  return DV_OK;
+}
+
+// A split-key stream of runs longer than the short-run kernel's, in launches
+// of at most N sequences.
+template <int N>
+int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<int32_t>& t0,
+              const std::vector<int32_t>& n, int64_t w_slab, void* wire, hipStream_t st) {
+  dv::SplitArgs<N> a;
+  memset(&a, 0, sizeof a);
+  a.cache = v.base;
+  a.s_slab = v.B * v.H * v.S * v.du;
+  a.s_b = v.H * v.S * v.du;
+  a.s_h = v.S * v.du;
+  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.du = (int32_t)v.du;
+  a.heads = (int32_t)v.H;
+  a.seq_cap = (int32_t)v.S;
+  a.tile = dv::split_tile(v.du);
+  a.d_du = dv::fast_div((uint32_t)v.du);
+  a.d_tile = dv::fast_div((uint32_t)a.tile);
+  int64_t p = 0;  // tokens of all earlier launches
+  for (int64_t g0 = 0; g0 < v.B; g0 += N) {
+    const int nseq = (int)std::min<int64_t>(N, v.B - g0);
+    const int64_t tiles = fill_seqs(&a.s, t0, n, g0, nseq, [&](int i) {
+      return v.H * ((n[g0 + i] + a.tile - 1) / a.tile);
+    });
+    if (tiles == 0) continue;
+    a.wire = static_cast<char*>(wire) + (uint64_t)p * v.H * v.du * 16;
+    a.b0 = (int32_t)g0;
+    const hipError_t e = dv::launch_split<N>(dir, a, (uint32_t)tiles, 2 * nl, st);
+    if (e != hipSuccess) return hip_fail(e, "split-key kernel launch");
+    p += a.s.tok[N];
   }
   return DV_OK;
 }
@@ -483,6 +525,19 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
                  : run_paged<kSeqPerLaunch>(dir, how, v, l0, nl, t0, n, w_slab, wire, st);
   }
 
+  if (v.kind == DV_DENSE_KSPLIT && !flat) {
+    // Where tiles of one head each would be less than three quarters full,
+    // rows across heads and sequences (up to 22 tokens of 16 groups: 58 and 62
+    // us by 64-token tiles, 44 and 47 by the tiles below, 32 and 45 by rows).
+    const int64_t tile = dv::split_tile(v.du);
+    int64_t tiles = 0;
+    for (int64_t b = 0; b < v.B; ++b) tiles += (n[b] + tile - 1) / tile;
+    flat = 4 * N < 3 * tiles * tile && w_slab < (1ll << 31);
+    if (!flat)
+      return v.B > kSeqPerLaunch && N < (1ll << 31) && tiles * v.H < (1ll << 32) / dv::kThreads
+                 ? run_split<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
+                 : run_split<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
+  }
   if (flat)
     return v.B > kSeqPerLaunch ? run_rows<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
                                : run_rows<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
@@ -518,35 +573,9 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     int64_t tiles = 0;
     for (int i = 0; i < nseq; ++i)
       tiles += v.H * (((int64_t)r.n[i] * v.du + dv::kDenseTile - 1) / dv::kDenseTile);
-    if (v.kind == DV_DENSE) {
-      a.m = {2 * l0, 1, 0, 0, w_slab};
-      const hipError_t e = dv::launch_dense_runs(dir, a, (uint32_t)tiles, 2 * nl, st);
-      if (e != hipSuccess) return hip_fail(e, "dense kernel launch");
-      continue;
-    }
-    // split key: value slabs are dense runs, key slabs go through LDS
-    a.m = {2 * l0 + 1, 2, 1, 0, w_slab};
-    hipError_t e = dv::launch_dense_runs(dir, a, (uint32_t)tiles, nl, st);
+    a.m = {2 * l0, 1, 0, 0, w_slab};
+    const hipError_t e = dv::launch_dense_runs(dir, a, (uint32_t)tiles, 2 * nl, st);
     if (e != hipSuccess) return hip_fail(e, "dense kernel launch");
-    dv::KsplitArgs k;
-    memset(&k, 0, sizeof k);
-    k.cache = v.base;
-    k.wire = wire_g;
-    k.s_slab = a.s_slab;
-    k.s_b = a.s_b;
-    k.s_h = a.s_h;
-    k.m = {2 * l0, 2, 0, 0, w_slab};
-    k.du = (int32_t)v.du;
-    k.heads = (int32_t)v.H;
-    k.nseq = nseq;
-    k.b0 = (int32_t)g0;
-    k.seq_cap = (int32_t)v.S;
-    k.r = r;
-    int64_t ktiles = 0;
-    for (int i = 0; i < nseq; ++i)
-      ktiles += v.H * (((int64_t)r.n[i] + dv::kKsplitTile - 1) / dv::kKsplitTile);
-    e = dv::launch_ksplit(dir, k, (uint32_t)ktiles, nl, st);
-    if (e != hipSuccess) return hip_fail(e, "split-key kernel launch");
   }
   return DV_OK;
 }

@@ -42,6 +42,9 @@ inline FastDiv fast_div(uint32_t d) {
 // workgroup finds its sequence with one ballot per 64 entries instead of
 // scanning the counts.
 constexpr int kSeqMany = 256;
+
+// 16-byte units per lane of the kernel for several tokens in split-key caches.
+constexpr int kRowsUnroll = 2;
 template <int N>
 struct SeqTable {
   int32_t item[N];     // work items of all earlier sequences; INT32_MAX past the last
@@ -157,25 +160,42 @@ struct RowArgs {
   int32_t du, heads;
   int32_t paged, block_size, num_blocks, max_blocks;
   int32_t n;           // tokens of every sequence, where they are equal
-  FastDiv d_du, d_heads, d_seq, d_n, d_bs;  // d_seq: heads * n
+  int32_t tile;        // rows per workgroup (split_rows_kernel)
+  FastDiv d_du, d_heads, d_seq, d_n, d_bs, d_tile;  // d_seq: heads * n
   int32_t tok[N + 1];  // ragged: tokens of all earlier sequences; INT32_MAX past the last
   int32_t t0[N];       // first token of each sequence's range
   int32_t seq[N];      // its index in the cache
 };
 static_assert(sizeof(RowArgs<kSeqMany>) <= 3584, "arguments stay well under 4 KB");
 
-// Split-key slab: 64-token tiles transposed through LDS.
-struct KsplitArgs {
+// Split-key caches, long runs: a tile is a.tile tokens of one (sequence, head);
+// key slabs go through LDS, value slabs straight across, in one launch.
+template <int N>
+struct SplitArgs {
   void* cache;
-  void* wire;
+  void* wire;            // contiguous buffer advanced to this launch's first sequence
   int64_t s_slab, s_b, s_h;  // as dense
   SlabMap m;
-  int32_t du;  // 16-byte groups per token (head_dim * elem_bytes / 16), <= kKsplitMaxDu
-  int32_t heads, nseq, b0;
-  int32_t seq_cap;  // S: units between consecutive groups of one head
+  int32_t du;            // 16-byte groups per token, <= kKsplitMaxDu
+  int32_t heads, b0;
+  int32_t seq_cap;       // S: units between consecutive groups of one head
+  int32_t tile;          // tokens per tile (a multiple of 8)
   int32_t pad;
-  SeqRanges r;
+  FastDiv d_du, d_tile;
+  SeqTable<N> s;
 };
+
+// Tokens per tile: whole 128-byte lines of a key slab (8 tokens of a group) in
+// two units per lane, or in six where two would leave more than a fifth of the
+// lanes idle (22-25 groups per token: 16 tokens fill 70 to 78 %).  37 layers of
+// 12 heads x 96 x 4 bytes, 0.76 GB: 259 and 269 us out and in with six, 261 and
+// 283 with two, 263 and 281 with four.
+inline int32_t split_tile(int64_t du) {
+  const int32_t two = (int32_t)(2 * kThreads / du & ~7), six = (int32_t)(6 * kThreads / du & ~7);
+  return 5 * two * du >= 4 * 2 * kThreads ? two : six;
+}
+constexpr size_t kSplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do not
+
 // Cache-to-cache copy of the same logical positions between two dense
 // caches (device slot <-> pinned host mirror) for narrow rows.
 struct CopyArgs {
@@ -190,9 +210,8 @@ struct CopyArgs {
 };
 constexpr int kCopyUnroll = 2;
 
-constexpr int kKsplitTile = 64;
-constexpr int kKsplitMaxDu = 32;  // LDS tile at most 64 x 33 units (33.8 KB)
-constexpr size_t kKsplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do not
+constexpr int kKsplitTile = 64;   // the grid-size rule of the host counts 64-token tiles
+constexpr int kKsplitMaxDu = 32;
 
 // Launchers (dv_kernels.hip).  Each returns the hipError_t of its launch.
 hipError_t launch_dense_runs(int dir, const DenseRunArgs& a, uint32_t tiles_per_slab,
@@ -216,8 +235,11 @@ hipError_t launch_block_claims(const OwnerArgs& a, bool clear, hipStream_t s);
 // `even`: every sequence has a.n tokens.
 template <int N>
 hipError_t launch_rows(int dir, bool even, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s);
-hipError_t launch_ksplit(int dir, const KsplitArgs& a, uint32_t tiles_per_slab, uint32_t nslabs,
-                         hipStream_t s);
+template <int N>
+hipError_t launch_split_rows(int dir, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s);
+template <int N>
+hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t tiles_per_slab, uint32_t nslabs,
+                        hipStream_t s);
 hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs, hipStream_t s);
 
 // Units each dense-run workgroup moves (tiles are counted on the host with

@@ -434,6 +434,51 @@ __global__ void __launch_bounds__(kThreads) owner_build_kernel(OwnerArgs a) {
   a.owner[blk] = gb * a.max_blocks + j;
 }
 
+// Cache offsets of rows [row0, row0 + rows) of a launch's slab, by
+// offset(sequence, head, token), into LDS: one row per lane, shared out by
+// waves.  The caller synchronises.
+template <int N, typename F>
+__device__ __forceinline__ void rows_to_lds(const RowArgs<N>& a, uint32_t row0, uint32_t rows,
+                                            int64_t* s_off, F offset) {
+  const int lane = lane_id();
+  // Every lane of a wave that has rows takes one (the last one again past the
+  // end), so that lanes can read each other's sequences.
+  for (uint32_t k = threadIdx.x & ~63u; k < rows; k += kThreads) {
+    const uint32_t r = row0 + min(k + lane, rows - 1);
+    const uint32_t q = a.d_heads.div(r);  // tok[b] <= q < tok[b + 1]
+    const int qlo = a.d_heads.div(row0 + k);
+    const int qhi = a.d_heads.div(row0 + min(k + 63, rows - 1));
+    int b, b1, p, t0, seq;
+    if constexpr (N == 64) {
+      const int tok = a.tok[lane];
+      b = __popcll(__ballot(tok <= qlo)) - 1;
+      b1 = __popcll(__ballot(tok <= qhi)) - 1;
+      const int b0 = b;
+      for (int i = b0 + 1; i <= b1; ++i) b += __builtin_amdgcn_readlane(tok, i) <= (int)q;
+      p = __shfl(tok, b, 64);
+      t0 = __shfl(a.t0[lane], b, 64);
+      seq = __shfl(a.seq[lane], b, 64);
+    } else {
+      b = b1 = -1;
+#pragma unroll
+      for (int i = 0; i < N / 64; ++i) {
+        const int tok = a.tok[i * 64 + lane];
+        b += __popcll(__ballot(tok <= qlo));
+        b1 += __popcll(__ballot(tok <= qhi));
+      }
+      const int b0 = b;
+      for (int i = b0 + 1; i <= b1; ++i) b += a.tok[i] <= (int)q;
+      p = a.tok[b];
+      t0 = a.t0[b];
+      seq = a.seq[b];
+    }
+    const uint32_t n = a.tok[b + 1] - p, rr = r - (uint32_t)p * a.heads;
+    const uint32_t h = rr / n;
+    const int64_t o = offset(seq, h, t0 + (rr - h * n));
+    if (k + lane < rows) s_off[k + lane] = o;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Short runs: grid (ceil(total / (256 * U)), nslabs); see RowArgs.  Each lane
 // moves U units of its slab, 256 apart.
@@ -452,7 +497,6 @@ __global__ void __launch_bounds__(kThreads) owner_build_kernel(OwnerArgs a) {
 // ---------------------------------------------------------------------------
 template <int D, int U, bool EVEN, int N>
 __global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
-  const int lane = lane_id();
   const int64_t y = blockIdx.y;
   const int half = (int)(y & 1);  // the launch starts at a layer's key slab
   u32x4* cache = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab;
@@ -476,44 +520,7 @@ __global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
   const uint32_t row0 = EVEN ? 0 : a.d_du.div(first);
   if constexpr (!EVEN) {
     const uint32_t rows = a.d_du.div(last) - row0 + 1;
-    // Every lane of a wave that has rows takes one (the last one again past
-    // the end), so that lanes can read each other's sequences.
-    for (uint32_t k = threadIdx.x & ~63u; k < rows; k += kThreads) {
-      const uint32_t r = row0 + min(k + lane, rows - 1);
-      const uint32_t q = a.d_heads.div(r);  // tok[b] <= q < tok[b + 1]
-      const int qlo = a.d_heads.div(row0 + k);
-      const int qhi = a.d_heads.div(row0 + min(k + 63, rows - 1));
-      int b, b1 = -1, p, p1, t0, seq;
-      if constexpr (N == 64) {
-        const int tok = a.tok[lane];
-        b = __popcll(__ballot(tok <= qlo)) - 1;
-        b1 = __popcll(__ballot(tok <= qhi)) - 1;
-        const int b0 = b;
-        for (int i = b0 + 1; i <= b1; ++i) b += __builtin_amdgcn_readlane(tok, i) <= (int)q;
-        p = __shfl(tok, b, 64);
-        p1 = a.tok[b + 1];
-        t0 = __shfl(a.t0[lane], b, 64);
-        seq = __shfl(a.seq[lane], b, 64);
-      } else {
-        b = -1;
-#pragma unroll
-        for (int i = 0; i < N / 64; ++i) {
-          const int tok = a.tok[i * 64 + lane];
-          b += __popcll(__ballot(tok <= qlo));
-          b1 += __popcll(__ballot(tok <= qhi));
-        }
-        const int b0 = b;
-        for (int i = b0 + 1; i <= b1; ++i) b += a.tok[i] <= (int)q;
-        p = a.tok[b];
-        p1 = a.tok[b + 1];
-        t0 = a.t0[b];
-        seq = a.seq[b];
-      }
-      const uint32_t n = p1 - p, rr = r - (uint32_t)p * a.heads;
-      const uint32_t h = rr / n;
-      const int64_t o = row_offset(seq, h, t0 + (rr - h * n));
-      if (k + lane < rows) s_off[k + lane] = o;
-    }
+    rows_to_lds(a, row0, rows, s_off, row_offset);
     __syncthreads();
   }
 
@@ -545,98 +552,156 @@ __global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Split-key slab: grid (tiles_per_slab, nslabs); a tile is 64 tokens of one
-// (sequence, head).  The cache holds the head as [group][token] (each group
-// 16 bytes), the wire as [token][group]: the tile is read with lanes along
-// the contiguous axis of the source, transposed through LDS (dynamic, 64
-// rows of du + 1 units: the padding unit keeps column accesses on distinct
-// banks), and written with lanes along the contiguous axis of the
-// destination.  Both passes take 4 units per lane at a time with clamped,
-// unguarded loads, so the loads of a pass issue back to back (a guarded load
-// per group left most of the load latency exposed: 70 % -> 77 % of HBM peak
-// on the OPT-13B shape).
+// Short runs of two tokens and more in a split-key cache: grid (ceil(rows /
+// a.tile), nslabs); a workgroup takes a.tile rows of its slab.  The tokens of a
+// run stand side by side in each group of the key half, so a key slab's tile
+// is moved with lanes along the rows on the cache side and through LDS: a
+// lane per wire unit would touch each 128-byte line once per token (43 layers,
+// 29 heads x 256 x 2 bytes, 3 sequences of 1-3 tokens: 7.1 and 13.5 us out and
+// in that way, 6.3 and 10.2 this way).
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kThreads) ksplit_kernel(KsplitArgs a) {
-  static_assert(kKsplitTile == 64, "cache-side units split as (group, token) = (j >> 6, j & 63)");
-  extern __shared__ u32x4 lds[];
-  const int lane = lane_id();
-  int n = 0, t0 = 0;
-  if (lane < a.nseq) {
-    n = a.r.n[lane];
-    t0 = a.r.t0[lane];
+template <int D, int N>
+__global__ void __launch_bounds__(kThreads) split_rows_kernel(RowArgs<N> a) {
+  extern __shared__ u32x4 lds[];  // a.tile rows of du + 1 units, then their offsets
+  const int64_t y = blockIdx.y;
+  const int half = (int)(y & 1);
+  u32x4* cache = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab;
+  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y) * a.m.w_slab;
+  const uint32_t du = a.du, pitch = du + 1;
+  const int64_t s_tok = a.s_tok[half], s_e = a.s_e[half];
+  int64_t* s_off = (int64_t*)(lds + a.tile * pitch);
+  const uint32_t row0 = blockIdx.x * a.tile;
+  const uint32_t rows = min((uint32_t)a.tile, a.d_du.div(a.total) - row0);
+  rows_to_lds(a, row0, rows, s_off, [&](int seq, uint32_t h, uint32_t s) {
+    return (int64_t)seq * a.s_b + (int64_t)h * a.s_h + (int64_t)s * s_tok;
+  });
+  __syncthreads();
+  wire += (int64_t)row0 * du;
+  const uint32_t units = rows * du;
+  u32x4 v[kRowsUnroll];
+  int64_t co[kRowsUnroll];
+  u32x4* at[kRowsUnroll];  // the unit's place in LDS, cache side
+#pragma unroll
+  for (int i = 0; i < kRowsUnroll; ++i) {
+    const uint32_t j = min(i * kThreads + threadIdx.x, units - 1);
+    uint32_t r, g;
+    if (half) {  // value slab: units in wire order on both sides
+      r = a.d_du.div(j);
+      g = j - r * du;
+    } else {     // key slab: rows fastest
+      g = rows == (uint32_t)a.tile ? a.d_tile.div(j) : j / rows;
+      r = j - g * rows;
+    }
+    co[i] = s_off[r] + (int64_t)g * s_e;
+    at[i] = lds + r * pitch + g;
+    v[i] = (D == kPack) ? ld_nt(cache + co[i]) : ld_nt(wire + j);
   }
-  const int tpr = (n + kKsplitTile - 1) / kKsplitTile;
-  const int tiles = tpr * a.heads;
-  const int incl = wave_incl_scan(tiles);
-  const int tok_incl = wave_incl_scan(n);
+  if (half) {
+#pragma unroll
+    for (int i = 0; i < kRowsUnroll; ++i) {
+      const uint32_t j = i * kThreads + threadIdx.x;
+      if (j < units) st_nt(v[i], (D == kPack) ? wire + j : cache + co[i]);
+    }
+    return;
+  }
+  // Place of wire unit j (group j % du of row j / du) in LDS.
+  auto wire_at = [&](uint32_t j) { return lds + j + a.d_du.div(j); };
+#pragma unroll
+  for (int i = 0; i < kRowsUnroll; ++i) {
+    const uint32_t j = i * kThreads + threadIdx.x;
+    if (j < units) *((D == kPack) ? at[i] : wire_at(j)) = v[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kRowsUnroll; ++i) {
+    const uint32_t j = i * kThreads + threadIdx.x;
+    if (j < units) st_nt((D == kPack) ? *wire_at(j) : *at[i], (D == kPack) ? wire + j : cache + co[i]);
+  }
+}
 
+// ---------------------------------------------------------------------------
+// Split-key caches: grid (tiles_per_slab, nslabs); a tile is a.tile tokens of
+// one (sequence, head).  A key slab holds the head as [group][token] (each
+// group 16 bytes), the wire as [token][group]: the tile is read with lanes
+// along the contiguous axis of the source, transposed through LDS (rows of du
+// + 1 units: the padding unit keeps column accesses on distinct banks), and
+// written with lanes along the contiguous axis of the destination.  A value
+// slab's tile is contiguous on both sides.
+//
+// Bound by HBM for whole prompts: the OPT-13B stage's split-key shape (1.28 GB)
+// takes 397 and 396 us one way, 6.3 TB/s, against 402 and 399 in two launches
+// with key tiles of 16 KB (4 workgroups to a CU); small prompts gain the launch
+// (10 layers, one head, 254 tokens: 5.7 -> 2.5 us).
+// ---------------------------------------------------------------------------
+template <int D, int U, int N>
+__global__ void __launch_bounds__(kThreads) split_kernel(SplitArgs<N> a) {
+  extern __shared__ u32x4 lds[];
   int tile;
   int64_t y;
   xcd_tile(&tile, &y);
-  const int b = owner_lane(incl, tile);
-  const int excl_b = __shfl(incl - tiles, b, 64);
-  const int tpr_b = __shfl(tpr, b, 64);
-  const int n_b = __shfl(n, b, 64);
-  const int t0_b = __shfl(t0, b, 64);
-  const int p_b = __shfl(tok_incl - n, b, 64);
-  const int r = tile - excl_b;
-  const int h = r / tpr_b;
-  const int k = r - h * tpr_b;
-  const int tok0 = k * kKsplitTile;              // first token of the tile, range-relative
-  const int ntk = min(kKsplitTile, n_b - tok0);  // tokens in the tile
-  const int du = a.du;
-  const int pitch = du + 1;
-
-  const int64_t slab = a.m.slab0 + y * a.m.slab_step;
-  const int64_t wslab = a.m.wslab0 + y * a.m.slab_step;
-  u32x4* head = (u32x4*)a.cache + slab * a.s_slab + (int64_t)(a.b0 + b) * a.s_b +
-                (int64_t)h * a.s_h + t0_b + tok0;  // group 0 of the tile's first token
-  u32x4* wire = (u32x4*)a.wire + wslab * a.m.w_slab + (int64_t)p_b * a.heads * du +
-                (int64_t)h * n_b * du + (int64_t)tok0 * du;
+  const Seq q = find_seq(a.s, tile);
+  const uint32_t tpr = a.d_tile.div(q.n + a.tile - 1);  // tiles per run
+  const uint32_t h = (uint32_t)q.k / tpr, k = (uint32_t)q.k - h * tpr;
+  const uint32_t du = a.du, tok0 = k * a.tile;
+  const uint32_t ntk = min((uint32_t)a.tile, q.n - tok0);
+  const uint32_t units = ntk * du;
+  u32x4* head = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab + (int64_t)(a.b0 + q.b) * a.s_b +
+                (int64_t)h * a.s_h;
+  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y) * a.m.w_slab +
+                (int64_t)q.p * ((int64_t)a.heads * du) + ((int64_t)h * q.n + tok0) * du;
+  u32x4 v[U];
+  if (y & 1) {  // value slab
+    u32x4* run = head + (int64_t)(q.t0 + tok0) * du;
+    const u32x4* src = (D == kPack) ? run : wire;
+    u32x4* dst = (D == kPack) ? wire : run;
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      v[i] = ld_nt(src + min(i * kThreads + threadIdx.x, units - 1));
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const uint32_t idx = i * kThreads + threadIdx.x;
+      if (idx < units) st_nt(v[i], dst + idx);
+    }
+    return;
+  }
+  // Key slab: unit j of the cache side is token j % a.tile of group j / a.tile,
+  // unit j of the wire side group j % du of token j / du.
+  u32x4* key = head + q.t0 + tok0;
   const int64_t S = a.seq_cap;
-  // Cache side: unit j = group * 64 + token (tokens fastest); wire side:
-  // unit idx = token * du + group.
-  const int cache_units = du * kKsplitTile;
-  const int wire_units = ntk * du;
-  constexpr int kChunk = 4;
-  if (D == kPack) {
-    for (int base = 0; base < cache_units; base += kChunk * kThreads) {
-      u32x4 v[kChunk];
+  const uint32_t pitch = du + 1;
+  uint32_t g[U], t[U];
 #pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        const int j = min(base + i * kThreads + (int)threadIdx.x, cache_units - 1);
-        v[i] = ld_nt(head + (j >> 6) * S + min(j & 63, ntk - 1));
-      }
+  for (int i = 0; i < U; ++i) {
+    const uint32_t j = i * kThreads + threadIdx.x;
+    g[i] = a.d_tile.div(j);
+    t[i] = j - g[i] * a.tile;
+  }
 #pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        const int j = base + i * kThreads + (int)threadIdx.x;
-        if (j < cache_units && (j & 63) < ntk) lds[(j & 63) * pitch + (j >> 6)] = v[i];
-      }
-    }
+  for (int i = 0; i < U; ++i) {
+    const uint32_t j = min(i * kThreads + threadIdx.x, units - 1);
+    v[i] = (D == kPack) ? ld_nt(key + min(g[i], du - 1) * S + min(t[i], ntk - 1)) : ld_nt(wire + j);
+  }
+  if constexpr (D == kPack) {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (g[i] < du && t[i] < ntk) lds[t[i] * pitch + g[i]] = v[i];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < wire_units; idx += kThreads) {
-      const int t = idx / du;
-      st_nt(lds[t * pitch + (idx - t * du)], wire + idx);
-    }
-  } else {
-    for (int base = 0; base < wire_units; base += kChunk * kThreads) {
-      u32x4 v[kChunk];
+  }
 #pragma unroll
-      for (int i = 0; i < kChunk; ++i)
-        v[i] = ld_nt(wire + min(base + i * kThreads + (int)threadIdx.x, wire_units - 1));
-#pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        const int idx = base + i * kThreads + (int)threadIdx.x;
-        if (idx < wire_units) {
-          const int t = idx / du;
-          lds[t * pitch + (idx - t * du)] = v[i];
-        }
-      }
+  for (int i = 0; i < U; ++i) {
+    const uint32_t j = i * kThreads + threadIdx.x;
+    if (j < units) {
+      const uint32_t wt = a.d_du.div(j);
+      u32x4* at = lds + wt * pitch + (j - wt * du);
+      if (D == kPack) st_nt(*at, wire + j);
+      else *at = v[i];
     }
+  }
+  if constexpr (D == kUnpack) {
     __syncthreads();
-    for (int j = threadIdx.x; j < cache_units; j += kThreads)
-      if ((j & 63) < ntk) st_nt(lds[(j & 63) * pitch + (j >> 6)], head + (j >> 6) * S + (j & 63));
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (g[i] < du && t[i] < ntk) st_nt(lds[t[i] * pitch + g[i]], key + g[i] * S + t[i]);
   }
 }
 
@@ -787,22 +852,42 @@ hipError_t launch_rows(int dir, bool even, const RowArgs<N>& a, uint32_t nslabs,
                : (const void*)&rows_kernel<kUnpack, 1, false, N>;
   return launch(fn, dim3((uint32_t)(((uint64_t)a.total + per - 1) / per), nslabs), a, s);
 }
+template <int N>
+hipError_t launch_split_rows(int dir, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s) {
+  const void* fn = dir == kPack ? (const void*)&split_rows_kernel<kPack, N>
+                                : (const void*)&split_rows_kernel<kUnpack, N>;
+  const uint32_t rows = (uint32_t)(a.total / a.du);
+  const size_t lds = (size_t)a.tile * ((a.du + 1) * 16 + 8);
+  return launch(fn, dim3((rows + a.tile - 1) / a.tile, nslabs), a, s, lds);
+}
+template hipError_t launch_split_rows<kSeqPerLaunch>(int, const RowArgs<kSeqPerLaunch>&, uint32_t,
+                                                     hipStream_t);
+template hipError_t launch_split_rows<kSeqMany>(int, const RowArgs<kSeqMany>&, uint32_t,
+                                                hipStream_t);
 template hipError_t launch_rows<kSeqPerLaunch>(int, bool, const RowArgs<kSeqPerLaunch>&, uint32_t,
                                                hipStream_t);
 template hipError_t launch_rows<kSeqMany>(int, bool, const RowArgs<kSeqMany>&, uint32_t,
                                           hipStream_t);
 
-hipError_t launch_ksplit(int dir, const KsplitArgs& a, uint32_t tiles_per_slab, uint32_t nslabs,
-                         hipStream_t s) {
-  const void* fn =
-      dir == kPack ? (const void*)&ksplit_kernel<kPack> : (const void*)&ksplit_kernel<kUnpack>;
-  // The tile's LDS, rounded up for tiles of 16 KB or more so that at most 4
-  // workgroups share a CU's 160 KB: on MI355X 8 workgroups of 16 KB tiles
-  // ran 2-3 % slower than 4, while 8 KB tiles ran 13 % faster with 8.
-  size_t lds = (size_t)kKsplitTile * (a.du + 1) * sizeof(uint32_t) * 4;
-  if (a.du >= 16 && lds < kKsplitLdsFor4) lds = kKsplitLdsFor4;
+template <int N>
+hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t tiles_per_slab, uint32_t nslabs,
+                        hipStream_t s) {
+  const bool six = a.tile * a.du > kThreads * 2;
+  const void* fn;
+  if (dir == kPack)
+    fn = six ? (const void*)&split_kernel<kPack, 6, N> : (const void*)&split_kernel<kPack, 2, N>;
+  else
+    fn = six ? (const void*)&split_kernel<kUnpack, 6, N>
+             : (const void*)&split_kernel<kUnpack, 2, N>;
+  // Six units per lane: at most 4 workgroups to a CU (259 and 269 us as above;
+  // as many as fit 264 and 277).
+  const size_t lds = six ? kSplitLdsFor4 : (size_t)a.tile * (a.du + 1) * 16;
   return launch(fn, dim3(tiles_per_slab, nslabs), a, s, lds);
 }
+template hipError_t launch_split<kSeqPerLaunch>(int, const SplitArgs<kSeqPerLaunch>&, uint32_t,
+                                                uint32_t, hipStream_t);
+template hipError_t launch_split<kSeqMany>(int, const SplitArgs<kSeqMany>&, uint32_t, uint32_t,
+                                           hipStream_t);
 
 hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs,
                        hipStream_t s) {
