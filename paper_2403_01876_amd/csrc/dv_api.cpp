@@ -185,10 +185,58 @@ bool pool_order_applies(const View& v, const std::vector<int32_t>& t0,
   return 9 * tiles >= 5 * v.NB * ngrp;
 }
 
-// The owner map of a whole call: one clearing launch, one building launch per
-// group of 64 sequences.
+// Fills a launch's sequence table for sequences [g0, g0 + nseq) of the call;
+// items(i) is the number of work items of sequence g0 + i.  Returns the sum
+// of the items (which the caller has checked to be below 2^31).
+template <int N, typename Items>
+int64_t fill_seqs(dv::SeqTable<N>* s, const std::vector<int32_t>& t0,
+                  const std::vector<int32_t>& n, int64_t g0, int nseq, Items items) {
+  int64_t total = 0, tok = 0;
+  for (int i = 0; i < N; ++i) {
+    s->item[i] = i < nseq ? (int32_t)total : INT32_MAX;
+    s->tok[i] = (int32_t)tok;
+    s->t0[i] = i < nseq ? t0[g0 + i] : 0;
+    if (i < nseq) {
+      total += items(i);
+      tok += n[g0 + i];
+    }
+  }
+  s->tok[N] = (int32_t)tok;
+  return total;
+}
+
+// Blocks of the table that hold tokens [t0, t0 + n).
+int64_t blocks_of(const View& v, int64_t t0, int64_t n) {
+  return n > 0 ? (t0 + n + v.bs - 1) / v.bs - t0 / v.bs : 0;
+}
+
+// The owner map of a whole call of at most N sequences in one launch.
+template <int N>
+hipError_t launch_owner_map(const View& v, const std::vector<int32_t>& t0,
+                            const std::vector<int32_t>& n, hipStream_t st) {
+  dv::OwnerMapArgs<N> a;
+  memset(&a, 0, sizeof a);
+  a.owner = v.owner;
+  a.bt = v.bt;
+  a.num_blocks = (int32_t)v.NB;
+  a.max_blocks = (int32_t)v.max_blocks;
+  a.d_bs = dv::fast_div((uint32_t)v.bs);
+  a.chunks = (int32_t)fill_seqs(&a.s, t0, n, 0, (int)v.B, [&](int i) {
+    return (blocks_of(v, t0[i], n[i]) + 63) / 64;
+  });
+  return dv::launch_owner_map<N>(a, st);
+}
+
+// The owner map of a whole call: one launch for a small table, else one
+// clearing launch and one building launch per group of 64 sequences.
 int build_owner_map(const View& v, const std::vector<int32_t>& t0, const std::vector<int32_t>& n,
                     hipStream_t st) {
+  int64_t chunks = 0;
+  for (int64_t b = 0; b < v.B; ++b) chunks += (blocks_of(v, t0[b], n[b]) + 63) / 64;
+  if (v.B <= kSeqPerLaunch && chunks <= dv::kOwnerChunks)
+    return hip_fail(launch_owner_map<kSeqPerLaunch>(v, t0, n, st), "owner map launch");
+  if (v.B > kSeqPerLaunch && v.B <= dv::kSeqMany && chunks <= dv::kOwnerChunksMany)
+    return hip_fail(launch_owner_map<dv::kSeqMany>(v, t0, n, st), "owner map launch");
   dv::OwnerArgs o;
   memset(&o, 0, sizeof o);
   o.owner = v.owner;
@@ -213,31 +261,6 @@ int build_owner_map(const View& v, const std::vector<int32_t>& t0, const std::ve
     if (e != hipSuccess) return hip_fail(e, "owner map launch");
   }
   return DV_OK;
-}
-
-// Fills a launch's sequence table for sequences [g0, g0 + nseq) of the call;
-// items(i) is the number of work items of sequence g0 + i.  Returns the sum
-// of the items (which the caller has checked to be below 2^31).
-template <int N, typename Items>
-int64_t fill_seqs(dv::SeqTable<N>* s, const std::vector<int32_t>& t0,
-                  const std::vector<int32_t>& n, int64_t g0, int nseq, Items items) {
-  int64_t total = 0, tok = 0;
-  for (int i = 0; i < N; ++i) {
-    s->item[i] = i < nseq ? (int32_t)total : INT32_MAX;
-    s->tok[i] = (int32_t)tok;
-    s->t0[i] = i < nseq ? t0[g0 + i] : 0;
-    if (i < nseq) {
-      total += items(i);
-      tok += n[g0 + i];
-    }
-  }
-  s->tok[N] = (int32_t)tok;
-  return total;
-}
-
-// Blocks of the table that hold tokens [t0, t0 + n).
-int64_t blocks_of(const View& v, int64_t t0, int64_t n) {
-  return n > 0 ? (t0 + n + v.bs - 1) / v.bs - t0 / v.bs : 0;
 }
 
 // The smallest power of two of tiles per workgroup for which the launch's

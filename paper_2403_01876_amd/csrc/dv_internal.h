@@ -128,8 +128,9 @@ constexpr int kPoolSeqMax = kSeqMany;
 // Owner map of a paged table over the streamed ranges: owner[blk] =
 // b * max_blocks + j for each entry (b, j) whose logical block j holds a
 // streamed token of sequence b and whose block blk is in [0, num_blocks);
-// -1 for every other block.  Built by one clearing launch and one launch
-// per group of up to 64 sequences, b0 being the group's first sequence.
+// -1 for every other block.  Small tables: one launch (OwnerMapArgs).  Large
+// ones: one clearing launch and one launch per group of up to 64 sequences, b0
+// being the group's first sequence.
 struct OwnerArgs {
   int32_t* owner;
   const int32_t* bt;
@@ -137,6 +138,27 @@ struct OwnerArgs {
   int32_t b0, pad;  // index of the launch's first sequence
   SeqRanges r;
 };
+
+// The whole map in one launch: a workgroup owns kOwnerSpan blocks of the pool
+// and looks through every table entry of the ranges for them, 64 entries (a
+// chunk, s.item counts them) to a wave.
+template <int N>
+struct OwnerMapArgs {
+  int32_t* owner;
+  const int32_t* bt;
+  int32_t chunks, num_blocks, max_blocks, pad;
+  FastDiv d_bs;
+  SeqTable<N> s;
+};
+constexpr int kOwnerSpan = 512;
+constexpr int kOwnerThreads = 1024;
+// Chunks up to which one launch is used.  Every workgroup reads every entry, so
+// the launches it saves are paid for in large pools.  A pool-order stream-in of
+// one layer, one head, graph-replayed, with a launch to clear and one per 64
+// sequences against one for all: 544 blocks (32 chunks) 6.7 and 5.7 us, 4600
+// blocks (72) 17.6 and 16.5, 19200 blocks (320) 55.2 and 57.3; 200 sequences,
+// 4000 blocks (200) 21.3 and 17.1, 20000 blocks (400) 63.7 and 62.5.
+constexpr int kOwnerChunks = 192, kOwnerChunksMany = 512;
 
 // Short runs (decode-step increments of one or a few tokens per sequence):
 // the 16-byte units of a slab in wire order, (sequence, head, token, group),
@@ -228,6 +250,8 @@ hipError_t launch_paged_runs(int dir, const PagedRunArgs<N>& a, uint32_t tiles_p
 hipError_t launch_owner_clear(const OwnerArgs& a, hipStream_t s);
 // Fills the owner map from the table for sequences [b0, b0 + nseq).
 hipError_t launch_owner_build(const OwnerArgs& a, hipStream_t s);
+template <int N>
+hipError_t launch_owner_map(const OwnerMapArgs<N>& a, hipStream_t s);
 // Counts, per pool block, the table entries over the ranges of sequences
 // [b0, b0 + nseq) that map to it, into `a.owner` (int32 counts), clearing
 // the counts first when `clear` is set.

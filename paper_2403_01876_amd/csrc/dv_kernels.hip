@@ -399,6 +399,35 @@ __global__ void __launch_bounds__(kThreads) paged_runs_kernel(PagedRunArgs<N> a)
   }
 }
 
+// Owner map in one launch (see OwnerMapArgs).  Four chunks of a wave are in
+// flight at a time: the launch is bound by their latency.
+template <int N>
+__global__ void __launch_bounds__(kOwnerThreads) owner_map_kernel(OwnerMapArgs<N> a) {
+  __shared__ int s_own[kOwnerSpan];
+  const int lane = lane_id();
+  const int lo = blockIdx.x * kOwnerSpan;
+  const int span = min(kOwnerSpan, a.num_blocks - lo);
+  for (int i = threadIdx.x; i < span; i += kOwnerThreads) s_own[i] = -1;
+  __syncthreads();
+  constexpr int kWaves = kOwnerThreads / 64, kDeep = 4;
+  for (int c0 = threadIdx.x >> 6; c0 < a.chunks; c0 += kWaves * kDeep) {
+    int entry[kDeep], blk[kDeep];
+#pragma unroll
+    for (int i = 0; i < kDeep; ++i) {
+      const int c = min(c0 + i * kWaves, a.chunks - 1);  // past the end: the last one again
+      const Seq q = find_seq(a.s, c);
+      const int last = a.d_bs.div(q.t0 + q.n - 1);
+      entry[i] = q.b * a.max_blocks + min((int)a.d_bs.div(q.t0) + q.k * 64 + lane, last);
+      blk[i] = a.bt[entry[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < kDeep; ++i)
+      if (blk[i] >= lo && blk[i] < lo + span) s_own[blk[i] - lo] = entry[i];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < span; i += kOwnerThreads) a.owner[lo + i] = s_own[i];
+}
+
 // Owner map (see OwnerArgs): a clearing pass, then one lane per table entry.
 __global__ void __launch_bounds__(kThreads) owner_clear_kernel(OwnerArgs a) {
   const int i = blockIdx.x * kThreads + threadIdx.x;
@@ -823,6 +852,17 @@ hipError_t launch_owner_clear(const OwnerArgs& a, hipStream_t s) {
 hipError_t launch_owner_build(const OwnerArgs& a, hipStream_t s) {
   return launch((const void*)&owner_build_kernel, dim3(groups_of(a.max_blocks), a.nseq), a, s);
 }
+
+template <int N>
+hipError_t launch_owner_map(const OwnerMapArgs<N>& a, hipStream_t s) {
+  void* args[] = {const_cast<OwnerMapArgs<N>*>(&a)};
+  const uint32_t groups = (uint32_t)(((int64_t)a.num_blocks + kOwnerSpan - 1) / kOwnerSpan);
+  return hipLaunchKernel((const void*)&owner_map_kernel<N>, dim3(groups), dim3(kOwnerThreads),
+                         args, 0, s);
+}
+template hipError_t launch_owner_map<kSeqPerLaunch>(const OwnerMapArgs<kSeqPerLaunch>&,
+                                                    hipStream_t);
+template hipError_t launch_owner_map<kSeqMany>(const OwnerMapArgs<kSeqMany>&, hipStream_t);
 
 hipError_t launch_block_claims(const OwnerArgs& a, bool clear, hipStream_t s) {
   if (clear) {

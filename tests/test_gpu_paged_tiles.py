@@ -91,6 +91,33 @@ def test_paged_tiles(oracle_lib, shape, unmapped):
         assert G.host(recv)[: 2 * L * nb * blk].tobytes() == want, "pool order" if owners else "table"
 
 
+@pytest.mark.parametrize("B, blocks", [(1, 1), (3, 64), (5, 65), (1, 192 * 64), (1, 192 * 64 + 1),
+                                       (64, 193), (65, 30), (256, 128), (256, 129)])
+def test_owner_map_one_launch_or_several(B, blocks):
+    """The owner map of pools whose tables have chunks of 64 entries on either
+    side of the counts up to which one launch builds it (192 for at most 64
+    sequences, 512 for more), with unmapped entries, ranges that start in
+    later blocks and blocks that no entry names."""
+    bs, H, D = 4, 1, 8
+    r = np.random.default_rng(B * 1000 + blocks)
+    nb = B * blocks + min(5, B * blocks // 2)  # most of the pool written: pool order
+    bt = r.permutation(nb)[: B * blocks].reshape(B, blocks).astype(np.int32)
+    bt[r.random(bt.shape) < 0.05] = -1
+    t0 = r.integers(0, min(blocks, 3) * bs - bs + 1, size=B).astype(np.int32)
+    t1 = np.full(B, blocks * bs, np.int32)
+    t0[0] = 0
+    E = 2 if blocks * bs > 256 else 512  # runs past the short-run kernel's 256 units
+    pool = G.dev_const(2 * nb * H * bs * D * E, 0xA5)
+    owner = torch.full((nb + 1,), 77, dtype=torch.int32, device=G.DEV)
+    c = dv.Cache(dv.DV_PAGED, 1, H, D, B, [pool], elem_bytes=E, block_size=bs, num_blocks=nb,
+                 max_blocks=blocks, block_tables=[G.to_dev(bt)], block_owners=[owner])
+    size = dv.dv_packed_bytes(c, 0, 1, t0, t1)
+    dv.dv_stream_in(c, 0, 0, 1, t0, t1, G.dev_const(size, 1), size, stream())
+    torch.cuda.synchronize()
+    got = G.host(owner)
+    assert (got[:nb] == G.owner_map_expected(bt, nb, bs, t0, t1)).all() and got[nb] == 77
+
+
 def test_unit_numbers_past_2_31():
     """One sequence whose blocks hold 2^31 units of a slab, all but three of
     them unmapped: gather, scatter in table order, and scatter in pool order
