@@ -450,6 +450,37 @@ int run_rows(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<
   return DV_OK;
 }
 
+// A dense stream of runs longer than the short-run kernel's, in launches of at
+// most N sequences.
+template <int N>
+int run_dense(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<int32_t>& t0,
+              const std::vector<int32_t>& n, bool eighths, int64_t w_slab, void* wire,
+              hipStream_t st) {
+  dv::DenseRunArgs<N> a;
+  memset(&a, 0, sizeof a);
+  a.s_slab = v.B * v.H * v.S * v.du;
+  a.s_b = v.H * v.S * v.du;
+  a.s_h = v.S * v.du;
+  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.du = (int32_t)v.du;
+  a.heads = (int32_t)v.H;
+  int64_t p = 0;  // tokens of all earlier launches
+  for (int64_t g0 = 0; g0 < v.B; g0 += N) {
+    const int nseq = (int)std::min<int64_t>(N, v.B - g0);
+    const int64_t tiles = fill_seqs(&a.s, t0, n, g0, nseq, [&](int i) {
+      return v.H * ((n[g0 + i] * v.du + dv::kDenseTile - 1) / dv::kDenseTile);
+    });
+    if (tiles == 0) continue;
+    a.cache = v.base + (uint64_t)(g0 * a.s_b) * 16;
+    a.wire = static_cast<char*>(wire) + (uint64_t)p * v.H * v.du * 16;
+    a.deal = dv::deal_of(tiles, 2 * nl, eighths);
+    const hipError_t e = dv::launch_dense_runs<N>(dir, a, 2 * nl, st);
+    if (e != hipSuccess) return hip_fail(e, "dense kernel launch");
+    p += a.s.tok[N];
+  }
+  return DV_OK;
+}
+
 // A split-key stream of runs longer than the short-run kernel's, in launches
 // of at most N sequences.
 template <int N>
@@ -477,7 +508,8 @@ int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
     if (tiles == 0) continue;
     a.wire = static_cast<char*>(wire) + (uint64_t)p * v.H * v.du * 16;
     a.b0 = (int32_t)g0;
-    const hipError_t e = dv::launch_split<N>(dir, a, (uint32_t)tiles, 2 * nl, st);
+    a.deal = dv::deal_of(tiles, 2 * nl, true);
+    const hipError_t e = dv::launch_split<N>(dir, a, 2 * nl, st);
     if (e != hipSuccess) return hip_fail(e, "split-key kernel launch");
     p += a.s.tok[N];
   }
@@ -561,46 +593,30 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
                  ? run_split<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
                  : run_split<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
   }
+  bool eighths = true;
+  int64_t dense_tiles = 0;
+  if (v.kind == DV_DENSE && !flat) {
+    // Runs of a few hundred units fill their last tile badly.  A pack goes by
+    // rows then (its writes stay contiguous), an unpack only where most of
+    // the lanes would idle, and its tiles are not dealt in eighths.  Tiles in
+    // eighths, tiles in the hardware's order, rows: 11 sequences of 1-47
+    // tokens, 45 heads x 128 x 2 bytes, 33 layers (55 % full) 77.5, 71, 68.5 us
+    // out, 77.8, 73.5, 77.4 in; 13 of 1-18 tokens, 3 heads (30 %) 6.5, -, 5.3
+    // out, 7.6, -, 4.9 in; 60 of 24-472 tokens, 8 heads x 80 (91 %) 729, 799,
+    // 716 out, 728, 814, 792 in; prompts of 64-2048 tokens (98 %) 389, 416, 398
+    // out, 390, 423, 434 in.
+    for (int64_t b = 0; b < v.B; ++b)
+      dense_tiles += v.H * ((n[b] * v.du + dv::kDenseTile - 1) / dv::kDenseTile);
+    const int64_t full = dense_tiles * dv::kDenseTile;
+    flat = w_slab < (1ll << 31) && 100 * w_slab < (dir == dv::kPack ? 92 : 45) * full;
+    eighths = 100 * w_slab >= 80 * full;
+  }
   if (flat)
     return v.B > kSeqPerLaunch ? run_rows<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
                                : run_rows<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
-
-  int64_t p_group = 0;  // tokens of all earlier launch groups
-  for (int64_t g0 = 0; g0 < v.B; g0 += kSeqPerLaunch) {
-    const int nseq = (int)std::min<int64_t>(kSeqPerLaunch, v.B - g0);
-    int64_t ntok = 0;
-    for (int i = 0; i < nseq; ++i) ntok += n[g0 + i];
-    if (ntok == 0) continue;
-    char* wire_g = static_cast<char*>(wire) + (uint64_t)p_group * v.H * v.du * 16;
-    p_group += ntok;
-
-    dv::SeqRanges r;
-    memset(&r, 0, sizeof r);
-    for (int i = 0; i < nseq; ++i) {
-      r.t0[i] = t0[g0 + i];
-      r.n[i] = n[g0 + i];
-    }
-
-    dv::DenseRunArgs a;
-    memset(&a, 0, sizeof a);
-    a.cache = v.base;
-    a.wire = wire_g;
-    a.s_slab = v.B * v.H * v.S * v.du;
-    a.s_b = v.H * v.S * v.du;
-    a.s_h = v.S * v.du;
-    a.du = (int32_t)v.du;
-    a.heads = (int32_t)v.H;
-    a.nseq = nseq;
-    a.b0 = (int32_t)g0;
-    a.r = r;
-    int64_t tiles = 0;
-    for (int i = 0; i < nseq; ++i)
-      tiles += v.H * (((int64_t)r.n[i] * v.du + dv::kDenseTile - 1) / dv::kDenseTile);
-    a.m = {2 * l0, 1, 0, 0, w_slab};
-    const hipError_t e = dv::launch_dense_runs(dir, a, (uint32_t)tiles, 2 * nl, st);
-    if (e != hipSuccess) return hip_fail(e, "dense kernel launch");
-  }
-  return DV_OK;
+  return v.B > kSeqPerLaunch && N < (1ll << 31) && dense_tiles < (1ll << 32) / dv::kThreads
+             ? run_dense<dv::kSeqMany>(dir, v, l0, nl, t0, n, eighths, w_slab, wire, st)
+             : run_dense<kSeqPerLaunch>(dir, v, l0, nl, t0, n, eighths, w_slab, wire, st);
 }
 
 int check_kind_supported(const View& v) {

@@ -64,10 +64,26 @@ struct SlabMap {
   int64_t w_slab;  // wire units per slab: N * heads * du
 };
 
+// A launch's (tile, slab) grid, dealt so that each of the chip's 8 XCDs takes
+// one contiguous eighth of it, or (on = 0) left in the hardware's order.
+struct Deal {
+  uint32_t tiles;    // per slab (the grid's width)
+  uint32_t q, r;     // eighths of the grid: r of q + 1 items, the others of q
+  uint32_t on;
+  FastDiv d_tiles;
+};
+inline Deal deal_of(int64_t tiles, int64_t slabs, bool eighths) {
+  const int64_t total = tiles * slabs;
+  const bool on = eighths && total < (1ll << 31);
+  return Deal{(uint32_t)tiles, on ? (uint32_t)(total / 8) : 0, (uint32_t)(total % 8), on,
+              fast_div((uint32_t)tiles)};
+}
+
 // Dense runs: for each (sequence, head) the range is one contiguous run of
 // n*du units in the cache and in the wire.
+template <int N>
 struct DenseRunArgs {
-  void* cache;     // microbatch base
+  void* cache;     // microbatch base, advanced to this launch's first sequence
   void* wire;      // wire base advanced to this launch's first sequence
   int64_t s_slab;  // cache units per slab
   int64_t s_b;     // cache units per sequence
@@ -75,9 +91,8 @@ struct DenseRunArgs {
   SlabMap m;
   int32_t du;      // units per token (head_dim * elem_bytes / 16)
   int32_t heads;
-  int32_t nseq;    // sequences in this launch (<= 64)
-  int32_t b0;      // index of the launch's first sequence
-  SeqRanges r;
+  Deal deal;
+  SeqTable<N> s;
 };
 
 // Paged blocks.  A slab of the pool is one array of units in (block, head,
@@ -203,6 +218,7 @@ struct SplitArgs {
   int32_t seq_cap;       // S: units between consecutive groups of one head
   int32_t tile;          // tokens per tile (a multiple of 8)
   int32_t pad;
+  Deal deal;
   FastDiv d_du, d_tile;
   SeqTable<N> s;
 };
@@ -236,8 +252,8 @@ constexpr int kKsplitTile = 64;   // the grid-size rule of the host counts 64-to
 constexpr int kKsplitMaxDu = 32;
 
 // Launchers (dv_kernels.hip).  Each returns the hipError_t of its launch.
-hipError_t launch_dense_runs(int dir, const DenseRunArgs& a, uint32_t tiles_per_slab,
-                             uint32_t nslabs, hipStream_t s);
+template <int N>
+hipError_t launch_dense_runs(int dir, const DenseRunArgs<N>& a, uint32_t nslabs, hipStream_t s);
 // `wide`: some tile's first unit, or the number of the grid's workgroups, may
 // pass 2^31 (steps is 1 otherwise).
 template <int N>
@@ -262,8 +278,7 @@ hipError_t launch_rows(int dir, bool even, const RowArgs<N>& a, uint32_t nslabs,
 template <int N>
 hipError_t launch_split_rows(int dir, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s);
 template <int N>
-hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t tiles_per_slab, uint32_t nslabs,
-                        hipStream_t s);
+hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t nslabs, hipStream_t s);
 hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs, hipStream_t s);
 
 // Units each dense-run workgroup moves (tiles are counted on the host with

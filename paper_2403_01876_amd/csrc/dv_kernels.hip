@@ -32,13 +32,6 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return v;
 }
 
-// Index of the first lane whose inclusive prefix exceeds `item` (prefixes
-// are non-decreasing across lanes, so the lanes at or below `item` form a
-// prefix of the wavefront).
-__device__ __forceinline__ int owner_lane(int incl, int item) {
-  return __popcll(__ballot(incl <= item));
-}
-
 // The sequence that holds work item `item` of a launch, uniform over the
 // wavefront: every lane compares the prefixes of its share of the sequences,
 // and the count of prefixes at or below the item names the sequence (empty
@@ -74,18 +67,19 @@ __device__ __forceinline__ Seq find_seq(const SeqTable<N>& s, int item) {
 // Workgroup IDs are dealt round-robin to the chip's 8 XCDs (each with its
 // own L2).  The bulk kernels re-deal the linearised (tile, slab) grid so each
 // XCD streams a contiguous range of it: workgroup `lin` runs on XCD lin % 8
-// and takes item lin / 8 of that XCD's range; XCD x owns total / 8 items
-// (one more if x < total % 8) starting at x * (total / 8) + min(x, total % 8).
-// The map is a bijection on [0, total) whatever order the hardware actually
-// deals workgroups in; on MI355X it lifts the dense copy from 74 % to 77-79 %
-// of HBM peak.  (The paged kernels do not use it; see xcd_chunk_tile.)
-__device__ __forceinline__ void xcd_tile(int* tile, int64_t* slab_row) {
-  const uint64_t total = (uint64_t)gridDim.x * gridDim.y;
-  const uint64_t lin = blockIdx.x + (uint64_t)blockIdx.y * gridDim.x;
-  const uint64_t q = total / 8, r = total % 8, x = lin % 8;
-  const uint64_t t = x * q + (x < r ? x : r) + lin / 8;
-  *tile = (int)(t % gridDim.x);
-  *slab_row = (int64_t)(t / gridDim.x);
+// and takes item lin / 8 of that XCD's range; XCD x owns q items (one more if x
+// < r) starting at x * q + min(x, r).  The map is a bijection on the grid
+// whatever order the hardware actually deals workgroups in; on MI355X it lifts
+// the dense copy from 74 % to 77-79 % of HBM peak.  (The paged kernels do not
+// use it; see xcd_chunk.)
+__device__ __forceinline__ void xcd_tile(const Deal& d, uint32_t* tile, uint32_t* slab) {
+  *tile = blockIdx.x;
+  *slab = blockIdx.y;
+  if (!d.on) return;
+  const uint32_t lin = blockIdx.x + blockIdx.y * d.tiles, x = lin % 8;
+  const uint32_t t = x * d.q + min(x, d.r) + lin / 8;
+  *slab = d.d_tiles.div(t);
+  *tile = t - *slab * d.tiles;
 }
 
 // Pool-order scatters: the linearised (tile, slab) grid dealt to the XCDs in
@@ -107,45 +101,30 @@ __device__ __forceinline__ U xcd_chunk(U lin, U total) {
 
 // ---------------------------------------------------------------------------
 // Dense runs: grid (tiles_per_slab, nslabs); a tile is kDenseTile units of
-// one (sequence, head) run.
+// one (sequence, head) run.  Bound by HBM for whole prompts (6.2 TB/s, a plain
+// copy 6.5); launches of tens of microseconds also by how soon the first loads
+// leave: with the sequence found by two wavefront scans and the grid dealt by
+// 64-bit divisions, 402 instructions before them instead of about 150, one
+// layer of the OPT-13B stage's prompts (126 MB) took 44.2 us instead of 42.6,
+// 410 KB 2.5 us instead of 2.0.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kThreads) dense_runs_kernel(DenseRunArgs a) {
-  const int lane = lane_id();
-  int n = 0, t0 = 0;
-  if (lane < a.nseq) {
-    n = a.r.n[lane];
-    t0 = a.r.t0[lane];
-  }
-  const int run = n * a.du;
-  const int tpr = (run + kDenseTile - 1) / kDenseTile;
-  const int tiles = tpr * a.heads;
-  const int incl = wave_incl_scan(tiles);
-  const int tok_incl = wave_incl_scan(n);
+template <int D, int N>
+__global__ void __launch_bounds__(kThreads) dense_runs_kernel(DenseRunArgs<N> a) {
+  uint32_t tile, y;
+  xcd_tile(a.deal, &tile, &y);
+  const Seq q = find_seq(a.s, tile);
+  const int run = q.n * a.du;
+  const uint32_t tpr = (run + kDenseTile - 1) / kDenseTile;
+  const uint32_t h = (uint32_t)q.k / tpr, k = (uint32_t)q.k - h * tpr;
 
-  int tile;
-  int64_t y;
-  xcd_tile(&tile, &y);
-  const int b = owner_lane(incl, tile);
-  const int excl_b = __shfl(incl - tiles, b, 64);
-  const int tpr_b = __shfl(tpr, b, 64);
-  const int run_b = __shfl(run, b, 64);
-  const int t0_b = __shfl(t0, b, 64);
-  const int p_b = __shfl(tok_incl - n, b, 64);
-
-  const int r = tile - excl_b;
-  const int h = r / tpr_b;
-  const int k = r - h * tpr_b;
-
-  const int64_t slab = a.m.slab0 + y * a.m.slab_step;
-  const int64_t wslab = a.m.wslab0 + y * a.m.slab_step;
-  u32x4* cache = (u32x4*)a.cache + slab * a.s_slab + (int64_t)(a.b0 + b) * a.s_b +
-                 (int64_t)h * a.s_h + (int64_t)t0_b * a.du + (int64_t)k * kDenseTile;
-  u32x4* wire = (u32x4*)a.wire + wslab * a.m.w_slab + (int64_t)p_b * a.heads * a.du +
-                (int64_t)h * run_b + (int64_t)k * kDenseTile;
+  u32x4* cache = (u32x4*)a.cache + (int64_t)(a.m.slab0 + y) * a.s_slab + (int64_t)q.b * a.s_b +
+                 (int64_t)h * a.s_h + (int64_t)q.t0 * a.du + (int64_t)k * kDenseTile;
+  u32x4* wire = (u32x4*)a.wire + (int64_t)(a.m.wslab0 + y) * a.m.w_slab +
+                (int64_t)q.p * ((int64_t)a.heads * a.du) + (int64_t)h * run +
+                (int64_t)k * kDenseTile;
   const u32x4* src = (D == kPack) ? cache : wire;
   u32x4* dst = (D == kPack) ? wire : cache;
-  const int count = min(kDenseTile, run_b - k * kDenseTile);
+  const int count = min(kDenseTile, run - (int)k * kDenseTile);
 
   // Loads carry no per-lane guard (a lane past the tile's end re-reads the
   // tile's last unit), so they issue back to back with a single wait; a
@@ -665,18 +644,17 @@ __global__ void __launch_bounds__(kThreads) split_rows_kernel(RowArgs<N> a) {
 template <int D, int U, int N>
 __global__ void __launch_bounds__(kThreads) split_kernel(SplitArgs<N> a) {
   extern __shared__ u32x4 lds[];
-  int tile;
-  int64_t y;
-  xcd_tile(&tile, &y);
+  uint32_t tile, y;
+  xcd_tile(a.deal, &tile, &y);
   const Seq q = find_seq(a.s, tile);
   const uint32_t tpr = a.d_tile.div(q.n + a.tile - 1);  // tiles per run
   const uint32_t h = (uint32_t)q.k / tpr, k = (uint32_t)q.k - h * tpr;
   const uint32_t du = a.du, tok0 = k * a.tile;
   const uint32_t ntk = min((uint32_t)a.tile, q.n - tok0);
   const uint32_t units = ntk * du;
-  u32x4* head = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab + (int64_t)(a.b0 + q.b) * a.s_b +
+  u32x4* head = (u32x4*)a.cache + (int64_t)(a.m.slab0 + y) * a.s_slab + (int64_t)(a.b0 + q.b) * a.s_b +
                 (int64_t)h * a.s_h;
-  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y) * a.m.w_slab +
+  u32x4* wire = (u32x4*)a.wire + (int64_t)(a.m.wslab0 + y) * a.m.w_slab +
                 (int64_t)q.p * ((int64_t)a.heads * du) + ((int64_t)h * q.n + tok0) * du;
   u32x4 v[U];
   if (y & 1) {  // value slab
@@ -799,12 +777,16 @@ hipError_t launch(const void* fn, dim3 grid, const Args& a, hipStream_t s, size_
 
 }  // namespace
 
-hipError_t launch_dense_runs(int dir, const DenseRunArgs& a, uint32_t tiles_per_slab,
-                             uint32_t nslabs, hipStream_t s) {
-  const void* fn = dir == kPack ? (const void*)&dense_runs_kernel<kPack>
-                                : (const void*)&dense_runs_kernel<kUnpack>;
-  return launch(fn, dim3(tiles_per_slab, nslabs), a, s);
+template <int N>
+hipError_t launch_dense_runs(int dir, const DenseRunArgs<N>& a, uint32_t nslabs, hipStream_t s) {
+  const void* fn = dir == kPack ? (const void*)&dense_runs_kernel<kPack, N>
+                                : (const void*)&dense_runs_kernel<kUnpack, N>;
+  return launch(fn, dim3(a.deal.tiles, nslabs), a, s);
 }
+template hipError_t launch_dense_runs<kSeqPerLaunch>(int, const DenseRunArgs<kSeqPerLaunch>&,
+                                                     uint32_t, hipStream_t);
+template hipError_t launch_dense_runs<kSeqMany>(int, const DenseRunArgs<kSeqMany>&, uint32_t,
+                                                hipStream_t);
 
 namespace {
 
@@ -910,8 +892,7 @@ template hipError_t launch_rows<kSeqMany>(int, bool, const RowArgs<kSeqMany>&, u
                                           hipStream_t);
 
 template <int N>
-hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t tiles_per_slab, uint32_t nslabs,
-                        hipStream_t s) {
+hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t nslabs, hipStream_t s) {
   const bool six = a.tile * a.du > kThreads * 2;
   const void* fn;
   if (dir == kPack)
@@ -922,11 +903,11 @@ hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t tiles_per_slab,
   // Six units per lane: at most 4 workgroups to a CU (259 and 269 us as above;
   // as many as fit 264 and 277).
   const size_t lds = six ? kSplitLdsFor4 : (size_t)a.tile * (a.du + 1) * 16;
-  return launch(fn, dim3(tiles_per_slab, nslabs), a, s, lds);
+  return launch(fn, dim3(a.deal.tiles, nslabs), a, s, lds);
 }
 template hipError_t launch_split<kSeqPerLaunch>(int, const SplitArgs<kSeqPerLaunch>&, uint32_t,
-                                                uint32_t, hipStream_t);
-template hipError_t launch_split<kSeqMany>(int, const SplitArgs<kSeqMany>&, uint32_t, uint32_t,
+                                                hipStream_t);
+template hipError_t launch_split<kSeqMany>(int, const SplitArgs<kSeqMany>&, uint32_t,
                                            hipStream_t);
 
 hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs,
