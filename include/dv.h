@@ -257,7 +257,7 @@ DV_API int dv_block_claims(const dv_cache* c, int32_t mb, const int32_t* t0, con
  * and elem_bytes (their max_seq may differ); `dev` must be DV_MEM_DEVICE and
  * `host` DV_MEM_HOST_PINNED (allocated with hipHostMalloc, which kernels can
  * address).  Rows of 64 KB or more (one sequence's tokens of one head) move
- * on the DMA engines (hipMemcpy2DAsync over the token rows) on `stream`, so
+ * on the DMA engines (pitched copies over the token rows) on `stream`, so
  * they overlap kernels on other streams; narrower rows -- a decode step's
  * update is one 256-byte row per (layer, K|V, sequence, head) -- are copied
  * by one kernel on `stream` that writes the pinned mirror directly.

@@ -246,7 +246,6 @@ struct CopyArgs {
   int32_t pad;
   SeqRanges r;
 };
-constexpr int kCopyUnroll = 2;
 
 constexpr int kKsplitTile = 64;   // the grid-size rule of the host counts 64-token tiles
 constexpr int kKsplitMaxDu = 32;

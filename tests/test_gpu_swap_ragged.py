@@ -1,0 +1,88 @@
+"""Swaps of ragged wide rows (one 3-D copy per sequence on the DMA engines),
+byte for byte against the oracle: capacities that differ, ranges that start
+anywhere, sequences without tokens, layer sub-ranges, odd head sizes, and the
+same calls replayed from a HIP graph; and slabs of 2 GB, which keep 2-D copies."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2403_01876_amd import dv  # noqa: E402
+from tests import gpu_util as G  # noqa: E402
+
+# layers, (first, last) layer, heads, head_dim, elem_bytes, batch, slot and mirror capacity
+SHAPES = {
+    "even": (2, (0, 2), 3, 128, 2, 4, 600, 600),
+    "odd-heads": (3, (1, 3), 5, 80, 2, 3, 700, 913),
+    "narrower-mirror": (2, (0, 2), 2, 96, 4, 3, 401, 333),
+    "one-sequence-ragged-start": (1, (0, 1), 1, 256, 2, 2, 300, 290),
+}
+
+
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_ragged_wide_rows(oracle_lib, shape, captured):
+    L, (l0, l1), H, D, E, B, S, M = SHAPES[shape]
+    r = np.random.default_rng(sorted(SHAPES).index(shape))
+    cap, tok = min(S, M), D * E
+    t0 = r.integers(0, 20, size=B).astype(np.int32)
+    t1 = np.array([r.integers(a, cap + 1) for a in t0], np.int32)
+    t0[0], t1[0] = 3, cap  # rows of 64 KB and more
+    t1[B - 1] = t0[B - 1] if B > 2 else t1[B - 1]  # a sequence without tokens
+    assert (t1[0] - t0[0]) * tok >= 64 * 1024
+    dl = oracle.Layout(oracle.DENSE, L, H, D, B, seq_cap=S, elem_bytes=E)
+    hl = oracle.Layout(oracle.DENSE, L, H, D, B, seq_cap=M, elem_bytes=E)
+    slot_h = synth.fill_bytes(dl.storage_bytes(), 71)
+    slots = [G.to_dev(slot_h), G.dev_const(dl.storage_bytes(), 0xA5)]
+    mirror = torch.full((hl.storage_bytes(),), 0x77, dtype=torch.uint8, pin_memory=True)
+    d = dv.Cache(dv.DV_DENSE, L, H, D, B, slots, max_seq=S, elem_bytes=E)
+    h = dv.Cache(dv.DV_DENSE, L, H, D, B, [mirror], max_seq=M, elem_bytes=E,
+                 mem=dv.DV_MEM_HOST_PINNED)
+
+    def swap():
+        dv.dv_swap_out(d, 0, h, 0, l0, l1, t0, t1)
+        dv.dv_swap_in(h, 0, d, 1, l0, l1, t0, t1)
+
+    exp_host = np.full(hl.storage_bytes(), 0x77, np.uint8)
+    oracle_lib.copy_ranges(dl, slot_h, hl, exp_host, l0, l1, t0, t1)
+    exp_slot = np.full(dl.storage_bytes(), 0xA5, np.uint8)
+    oracle_lib.copy_ranges(hl, exp_host, dl, exp_slot, l0, l1, t0, t1)
+    if captured:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            swap()
+    for _ in range(3 if captured else 1):
+        mirror.fill_(0x77)
+        slots[1].fill_(0xA5)
+        torch.cuda.synchronize()
+        graph.replay() if captured else swap()
+        torch.cuda.synchronize()
+        assert mirror.numpy().tobytes() == exp_host.tobytes()
+        assert G.host(slots[1]).tobytes() == exp_slot.tobytes()
+
+
+def test_slabs_of_two_gigabytes():
+    L, H, D, E, B, S = 1, 16, 128, 2, 2, 1 << 18
+    row = D * E
+    slot = torch.empty(2 * B * H * S * row // 8, dtype=torch.int64, device=G.DEV).random_()
+    mirror = torch.empty(slot.numel(), dtype=torch.int64, pin_memory=True)
+    back = torch.zeros_like(slot)
+    d = dv.Cache(dv.DV_DENSE, L, H, D, B, [slot, back], max_seq=S)
+    h = dv.Cache(dv.DV_DENSE, L, H, D, B, [mirror], max_seq=S, mem=dv.DV_MEM_HOST_PINNED)
+    t0 = np.array([S - 300, 5], np.int32)
+    t1 = np.array([S, 12], np.int32)
+    dv.dv_swap_out(d, 0, h, 0, 0, L, t0, t1)
+    dv.dv_swap_in(h, 0, d, 1, 0, L, t0, t1)
+    torch.cuda.synchronize()
+    a, b = (x.view(2, B, H, S, row // 8) for x in (slot, back))
+    for s in range(B):
+        assert torch.equal(a[:, s, :, t0[s]:t1[s]], b[:, s, :, t0[s]:t1[s]])
+        b[:, s, :, t0[s]:t1[s]] = 0
+    assert not bool(back.any()), "bytes outside the ranges changed"
