@@ -374,6 +374,32 @@ int run_paged(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
   return DV_OK;
 }
 
+// Lists, from sequence *b on, up to N sequences that have tokens and whose rows
+// of `row` units each count below 2^31 units, and moves *b past them.  Returns
+// their number; *tok is their tokens, *even whether they have equally many.
+template <int N, typename Args>
+int fill_rows(Args* a, const std::vector<int32_t>& t0, const std::vector<int32_t>& n, int64_t row,
+              int64_t* b, int64_t* tok, bool* even) {
+  int nseq = 0;
+  *tok = 0;
+  *even = true;
+  for (; *b < (int64_t)n.size() && nseq < N; ++*b) {
+    const int32_t k = n[*b];
+    if (k == 0) continue;
+    if ((*tok + k) * row >= (1ll << 31)) break;
+    a->tok[nseq] = (int32_t)*tok;
+    a->t0[nseq] = t0[*b];
+    a->seq[nseq] = (int32_t)*b;
+    *tok += k;
+    *even = *even && k * (int64_t)(nseq + 1) == *tok;
+    ++nseq;
+  }
+  a->tok[nseq] = (int32_t)*tok;
+  for (int i = nseq + 1; i <= N; ++i) a->tok[i] = INT32_MAX;
+  a->total = (int32_t)(*tok * row);
+  return nseq;
+}
+
 // A stream of short runs (or any whose slabs hold fewer than 2^31 units), in
 // launches of at most N sequences that have tokens and fewer than 2^31 units.
 template <int N>
@@ -417,25 +443,12 @@ int run_rows(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<
   const int64_t row = v.H * v.du;  // units of one token
   int64_t p = 0;                   // tokens of all earlier launches
   for (int64_t b = 0; b < v.B;) {
-    int nseq = 0;
-    int64_t tok = 0;
-    bool even = true;
-    for (; b < v.B && nseq < N; ++b) {
-      if (n[b] == 0) continue;
-      if ((tok + n[b]) * row >= (1ll << 31)) break;
-      a.tok[nseq] = (int32_t)tok;
-      a.t0[nseq] = t0[b];
-      a.seq[nseq] = (int32_t)b;
-      if (nseq == 0) a.n = n[b];
-      even = even && n[b] == a.n;
-      ++nseq;
-      tok += n[b];
-    }
+    int64_t tok;
+    bool even;
+    const int nseq = fill_rows<N>(&a, t0, n, row, &b, &tok, &even);
     if (nseq == 0) continue;  // only sequences without tokens were left
-    a.tok[nseq] = (int32_t)tok;
-    for (int i = nseq + 1; i <= N; ++i) a.tok[i] = INT32_MAX;
     a.wire = static_cast<char*>(wire) + (uint64_t)p * row * 16;
-    a.total = (int32_t)(tok * row);
+    a.n = (int32_t)(tok / nseq);  // read where the runs are even
     a.d_seq = dv::fast_div((uint32_t)(v.H * a.n));
     a.d_n = dv::fast_div((uint32_t)a.n);
     // Key slabs through LDS from 4 MB on; smaller launches are bound by
@@ -647,6 +660,36 @@ int stream_out(const dv_cache* src, int32_t mb, int32_t l0, int32_t l1, const in
   return run_stream(dv::kPack, v, l0, l1, r0, rn, N, dst, static_cast<hipStream_t>(stream));
 }
 
+// The validated ranges of narrow rows between two dense caches by kernel, in
+// launches of at most N sequences that have tokens and fewer than 2^31 units.
+template <int N>
+int run_copy(const View& from, const View& to, int32_t l0, uint32_t nl,
+             const std::vector<int32_t>& t0, const std::vector<int32_t>& n, hipStream_t st) {
+  dv::CopyArgs<N> a;
+  memset(&a, 0, sizeof a);
+  a.src = from.base;
+  a.dst = to.base;
+  a.s_slab = from.B * from.H * from.S * from.du;
+  a.s_b = from.H * from.S * from.du;
+  a.s_h = from.S * from.du;
+  a.d_slab = to.B * to.H * to.S * to.du;
+  a.d_b = to.H * to.S * to.du;
+  a.d_h = to.S * to.du;
+  a.slab0 = 2 * l0;
+  a.du = (int32_t)from.du;
+  a.heads = (int32_t)from.H;
+  a.d_du = dv::fast_div((uint32_t)from.du);
+  a.d_heads = dv::fast_div((uint32_t)from.H);
+  for (int64_t b = 0; b < from.B;) {
+    int64_t tok;
+    bool even;
+    if (fill_rows<N>(&a, t0, n, from.H * from.du, &b, &tok, &even) == 0) continue;
+    const hipError_t e = dv::launch_copy<N>(a, 2 * nl, st);
+    if (e != hipSuccess) return hip_fail(e, "copy kernel launch");
+  }
+  return DV_OK;
+}
+
 // Copy rows of the validated ranges between two dense caches with DMA.
 int swap_copy(const dv_cache* from, int32_t from_mb, const dv_cache* to, int32_t to_mb,
               int32_t l0, int32_t l1, const int32_t* t0, const int32_t* t1, void* stream,
@@ -683,34 +726,8 @@ int swap_copy(const dv_cache* from, int32_t from_mb, const dv_cache* to, int32_t
       if (units >= (1ll << 31)) return DV_ERR_UNSUPPORTED;
     }
     const uint32_t nl = (uint32_t)(l1 - l0);
-    for (int64_t g0 = 0; g0 < a.B; g0 += kSeqPerLaunch) {
-      const int nseq = (int)std::min<int64_t>(kSeqPerLaunch, a.B - g0);
-      dv::CopyArgs k;
-      memset(&k, 0, sizeof k);
-      int64_t units = 0;
-      for (int i = 0; i < nseq; ++i) {
-        k.r.t0[i] = r0[g0 + i];
-        k.r.n[i] = rn[g0 + i];
-        units += (int64_t)rn[g0 + i] * a.H * a.du;
-      }
-      if (units == 0) continue;
-      k.src = a.base;
-      k.dst = b.base;
-      k.s_slab = a.B * a.H * a.S * a.du;
-      k.s_b = a.H * a.S * a.du;
-      k.s_h = a.S * a.du;
-      k.d_slab = b.B * b.H * b.S * b.du;
-      k.d_b = b.H * b.S * b.du;
-      k.d_h = b.S * b.du;
-      k.slab0 = 2 * l0;
-      k.du = (int32_t)a.du;
-      k.heads = (int32_t)a.H;
-      k.nseq = nseq;
-      k.b0 = (int32_t)g0;
-      const hipError_t e = dv::launch_copy(k, (uint32_t)units, 2 * nl, st);
-      if (e != hipSuccess) return hip_fail(e, "copy kernel launch");
-    }
-    return DV_OK;
+    return a.B > kSeqPerLaunch ? run_copy<dv::kSeqMany>(a, b, l0, nl, r0, rn, st)
+                               : run_copy<kSeqPerLaunch>(a, b, l0, nl, r0, rn, st);
   }
 
   const hipMemcpyKind kind =

@@ -234,18 +234,24 @@ inline int32_t split_tile(int64_t du) {
 }
 constexpr size_t kSplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do not
 
-// Cache-to-cache copy of the same logical positions between two dense
-// caches (device slot <-> pinned host mirror) for narrow rows.
+// Cache-to-cache copy of the same logical positions between two dense caches
+// (device slot <-> pinned host mirror) for narrow rows: rows as in RowArgs,
+// with a place in each cache.
+template <int N>
 struct CopyArgs {
   void* src;
   void* dst;
   int64_t s_slab, s_b, s_h;  // source strides (units); token stride du
   int64_t d_slab, d_b, d_h;  // destination strides (units)
   int32_t slab0;             // grid row y copies slab slab0 + y
-  int32_t du, heads, nseq, b0;
-  int32_t pad;
-  SeqRanges r;
+  int32_t total;             // units per slab of this launch (below 2^31)
+  int32_t du, heads;
+  FastDiv d_du, d_heads;
+  int32_t tok[N + 1];        // as RowArgs
+  int32_t t0[N];
+  int32_t seq[N];
 };
+constexpr int kCopyUnroll = 1;
 
 constexpr int kKsplitTile = 64;   // the grid-size rule of the host counts 64-token tiles
 constexpr int kKsplitMaxDu = 32;
@@ -278,7 +284,8 @@ template <int N>
 hipError_t launch_split_rows(int dir, const RowArgs<N>& a, uint32_t nslabs, hipStream_t s);
 template <int N>
 hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t nslabs, hipStream_t s);
-hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs, hipStream_t s);
+template <int N>
+hipError_t launch_copy(const CopyArgs<N>& a, uint32_t nslabs, hipStream_t s);
 
 // Units each dense-run workgroup moves (tiles are counted on the host with
 // the same constant).  Two 16-byte units per lane (8 KB per workgroup) keeps

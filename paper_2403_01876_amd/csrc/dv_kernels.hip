@@ -21,17 +21,6 @@ __device__ __forceinline__ void st_nt(u32x4 v, u32x4* p) { __builtin_nontemporal
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
-// Inclusive prefix sum across the 64 lanes of a wavefront.
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
 // The sequence that holds work item `item` of a launch, uniform over the
 // wavefront: every lane compares the prefixes of its share of the sequences,
 // and the count of prefixes at or below the item names the sequence (empty
@@ -442,12 +431,11 @@ __global__ void __launch_bounds__(kThreads) owner_build_kernel(OwnerArgs a) {
   a.owner[blk] = gb * a.max_blocks + j;
 }
 
-// Cache offsets of rows [row0, row0 + rows) of a launch's slab, by
-// offset(sequence, head, token), into LDS: one row per lane, shared out by
-// waves.  The caller synchronises.
-template <int N, typename F>
-__device__ __forceinline__ void rows_to_lds(const RowArgs<N>& a, uint32_t row0, uint32_t rows,
-                                            int64_t* s_off, F offset) {
+// Finds rows [row0, row0 + rows) of a launch's slab, one per lane, shared out by
+// waves: store(row - row0, sequence, head, token) leaves them in LDS.  The
+// caller synchronises.
+template <int N, typename Args, typename F>
+__device__ __forceinline__ void find_rows(const Args& a, uint32_t row0, uint32_t rows, F store) {
   const int lane = lane_id();
   // Every lane of a wave that has rows takes one (the last one again past the
   // end), so that lanes can read each other's sequences.
@@ -482,8 +470,7 @@ __device__ __forceinline__ void rows_to_lds(const RowArgs<N>& a, uint32_t row0, 
     }
     const uint32_t n = a.tok[b + 1] - p, rr = r - (uint32_t)p * a.heads;
     const uint32_t h = rr / n;
-    const int64_t o = offset(seq, h, t0 + (rr - h * n));
-    if (k + lane < rows) s_off[k + lane] = o;
+    if (k + lane < rows) store(k + lane, seq, h, t0 + (rr - h * n));
   }
 }
 
@@ -528,7 +515,9 @@ __global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
   const uint32_t row0 = EVEN ? 0 : a.d_du.div(first);
   if constexpr (!EVEN) {
     const uint32_t rows = a.d_du.div(last) - row0 + 1;
-    rows_to_lds(a, row0, rows, s_off, row_offset);
+    find_rows<N>(a, row0, rows, [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
+      s_off[i] = row_offset(seq, h, s);
+    });
     __syncthreads();
   }
 
@@ -580,8 +569,8 @@ __global__ void __launch_bounds__(kThreads) split_rows_kernel(RowArgs<N> a) {
   int64_t* s_off = (int64_t*)(lds + a.tile * pitch);
   const uint32_t row0 = blockIdx.x * a.tile;
   const uint32_t rows = min((uint32_t)a.tile, a.d_du.div(a.total) - row0);
-  rows_to_lds(a, row0, rows, s_off, [&](int seq, uint32_t h, uint32_t s) {
-    return (int64_t)seq * a.s_b + (int64_t)h * a.s_h + (int64_t)s * s_tok;
+  find_rows<N>(a, row0, rows, [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
+    s_off[i] = (int64_t)seq * a.s_b + (int64_t)h * a.s_h + (int64_t)s * s_tok;
   });
   __syncthreads();
   wire += (int64_t)row0 * du;
@@ -713,43 +702,49 @@ __global__ void __launch_bounds__(kThreads) split_kernel(SplitArgs<N> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Cache-to-cache copy: grid (ceil(units_per_slab / 256), nslabs).  Unit u of
-// a slab is the u-th 16-byte unit of the ranges taken in (sequence, head,
-// token, unit) order, i.e. the wire order, but it moves straight from the
-// source cache to the same logical place in the destination cache.  Used for
-// swaps whose rows are too narrow for DMA to run efficiently (a decode step's
-// one-token update is 256-byte rows); on pinned host memory each lane's store
-// or load crosses the host link.
+// Cache-to-cache copy: grid (ceil(total / (256 * kCopyUnroll)), nslabs).  The
+// units of a slab's ranges in wire order, as in the short-run kernel, but
+// straight from the source cache to the same logical place in the destination
+// cache.  Used for swaps whose rows are too narrow for DMA to run efficiently (a
+// decode step's one-token update is 256-byte rows); on pinned host memory each
+// lane's store or load crosses the host link.
 //
 // Bound by the link's requests of narrow rows: 4.72 MB in 18432 rows of 256
-// bytes take 92 us out and 112 us in, where a contiguous copy takes 83.  The
-// stores are ordinary ones: nontemporal, they took 98 us out.
+// bytes take 90 us out and 113 us in, where a contiguous copy takes 83.  The
+// stores are ordinary ones: nontemporal, they took 98 us out.  One unit per
+// lane: with two, 132 MB of 7-31 KB rows came in in 2.44 ms instead of 2.41.
+// Up to 256 sequences go in a launch: 171 of one token, 0.44 MB, 12.8 us out
+// and 25 in, in three launches 20 and 34.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kThreads) copy_kernel(CopyArgs a) {
-  __shared__ int s_incl[kSeqPerLaunch];
-  const int lane = lane_id();
-  if (threadIdx.x < 64) {
-    const int n = lane < a.nseq ? a.r.n[lane] : 0;
-    s_incl[lane] = wave_incl_scan(n * a.heads * a.du);
-  }
+template <int N>
+__global__ void __launch_bounds__(kThreads) copy_kernel(CopyArgs<N> a) {
+  constexpr int U = kCopyUnroll;
+  __shared__ int64_t s_src[kThreads * U], s_dst[kThreads * U];
+  const uint32_t first = blockIdx.x * (kThreads * U);
+  const uint32_t last = min(first + kThreads * U, (uint32_t)a.total) - 1;
+  const uint32_t row0 = a.d_du.div(first);
+  find_rows<N>(a, row0, a.d_du.div(last) - row0 + 1,
+               [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
+                 const int64_t e = (int64_t)s * a.du;
+                 s_src[i] = (int64_t)seq * a.s_b + (int64_t)h * a.s_h + e;
+                 s_dst[i] = (int64_t)seq * a.d_b + (int64_t)h * a.d_h + e;
+               });
   __syncthreads();
-  const int u = blockIdx.x * kThreads + threadIdx.x;
-  if (u >= s_incl[kSeqPerLaunch - 1]) return;
-  // sequence: first lane whose inclusive prefix exceeds u
-  int lo = 0, hi = kSeqPerLaunch - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (s_incl[mid] > u) hi = mid; else lo = mid + 1;
-  }
-  const int b = lo;
-  const int run = a.r.n[b] * a.du;
-  const int rem = u - (s_incl[b] - run * a.heads);
-  const int h = rem / run;
-  const int e = rem - h * run + a.r.t0[b] * a.du;
   const int64_t slab = a.slab0 + (int64_t)blockIdx.y;
-  const u32x4* src = (const u32x4*)a.src + slab * a.s_slab + (int64_t)(a.b0 + b) * a.s_b;
-  u32x4* dst = (u32x4*)a.dst + slab * a.d_slab + (int64_t)(a.b0 + b) * a.d_b;
-  dst[(int64_t)h * a.d_h + e] = ld_nt(src + (int64_t)h * a.s_h + e);
+  const u32x4* src = (const u32x4*)a.src + slab * a.s_slab;
+  u32x4* dst = (u32x4*)a.dst + slab * a.d_slab;
+  u32x4 v[U];
+  int64_t to[U];
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    const uint32_t u = min(first + i * kThreads + threadIdx.x, last);
+    const uint32_t row = a.d_du.div(u), g = u - row * a.du;
+    to[i] = s_dst[row - row0] + g;
+    v[i] = ld_nt(src + s_src[row - row0] + g);
+  }
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+    if (first + i * kThreads + threadIdx.x <= last) dst[to[i]] = v[i];
 }
 
 }  // namespace
@@ -900,10 +895,14 @@ template hipError_t launch_split<kSeqPerLaunch>(int, const SplitArgs<kSeqPerLaun
 template hipError_t launch_split<kSeqMany>(int, const SplitArgs<kSeqMany>&, uint32_t,
                                            hipStream_t);
 
-hipError_t launch_copy(const CopyArgs& a, uint32_t units_per_slab, uint32_t nslabs,
-                       hipStream_t s) {
-  return launch((const void*)&copy_kernel,
-                dim3((units_per_slab + kThreads - 1) / kThreads, nslabs), a, s);
+template <int N>
+hipError_t launch_copy(const CopyArgs<N>& a, uint32_t nslabs, hipStream_t s) {
+  const uint32_t per = kThreads * kCopyUnroll;
+  return launch((const void*)&copy_kernel<N>,
+                dim3((uint32_t)(((uint64_t)a.total + per - 1) / per), nslabs), a, s);
 }
+template hipError_t launch_copy<kSeqPerLaunch>(const CopyArgs<kSeqPerLaunch>&, uint32_t,
+                                               hipStream_t);
+template hipError_t launch_copy<kSeqMany>(const CopyArgs<kSeqMany>&, uint32_t, hipStream_t);
 
 }  // namespace dv

@@ -86,3 +86,32 @@ def test_slabs_of_two_gigabytes():
         assert torch.equal(a[:, s, :, t0[s]:t1[s]], b[:, s, :, t0[s]:t1[s]])
         b[:, s, :, t0[s]:t1[s]] = 0
     assert not bool(back.any()), "bytes outside the ranges changed"
+
+
+@pytest.mark.parametrize("B, hi", [(3, 9), (64, 1), (65, 5), (200, 1), (256, 3), (300, 4)])
+def test_narrow_rows_of_many_sequences(oracle_lib, B, hi):
+    """The copy kernel's launches of up to 64, up to 256 and more sequences, idle
+    ones among them."""
+    L, H, D, E, S, M = 2, 3, 80, 1, 40, 37
+    r = np.random.default_rng(B)
+    t0 = r.integers(0, M - hi, size=B).astype(np.int32)
+    n = r.integers(0, hi + 1, size=B)
+    n[B // 2] = hi
+    t1 = (t0 + n).astype(np.int32)
+    dl = oracle.Layout(oracle.DENSE, L, H, D, B, seq_cap=S, elem_bytes=E)
+    hl = oracle.Layout(oracle.DENSE, L, H, D, B, seq_cap=M, elem_bytes=E)
+    slot_h = synth.fill_bytes(dl.storage_bytes(), 81)
+    slots = [G.to_dev(slot_h), G.dev_const(dl.storage_bytes(), 0xA5)]
+    mirror = torch.full((hl.storage_bytes(),), 0x77, dtype=torch.uint8, pin_memory=True)
+    d = dv.Cache(dv.DV_DENSE, L, H, D, B, slots, max_seq=S, elem_bytes=E)
+    h = dv.Cache(dv.DV_DENSE, L, H, D, B, [mirror], max_seq=M, elem_bytes=E,
+                 mem=dv.DV_MEM_HOST_PINNED)
+    dv.dv_swap_out(d, 0, h, 0, 1, L, t0, t1)
+    dv.dv_swap_in(h, 0, d, 1, 1, L, t0, t1)
+    torch.cuda.synchronize()
+    exp_host = np.full(hl.storage_bytes(), 0x77, np.uint8)
+    oracle_lib.copy_ranges(dl, slot_h, hl, exp_host, 1, L, t0, t1)
+    assert mirror.numpy().tobytes() == exp_host.tobytes()
+    exp_slot = np.full(dl.storage_bytes(), 0xA5, np.uint8)
+    oracle_lib.copy_ranges(hl, exp_host, dl, exp_slot, 1, L, t0, t1)
+    assert G.host(slots[1])[: exp_slot.size].tobytes() == exp_slot.tobytes()
