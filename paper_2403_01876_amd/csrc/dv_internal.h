@@ -302,12 +302,15 @@ constexpr int kPagedTile = kThreads * kPagedUnroll;
 // one block.
 constexpr int kPagedHeads = 2;
 
-// Pool-order scatters deal their (tile, slab) grid to the 8 XCDs in chunks
-// of this many consecutive tiles (8 pool blocks of one slab at 8 heads; 256
-// KB for the LLaMA-2-70B pool).  Measured on MI355X on that pool against the
-// hardware's round-robin dealing, contiguous eighths and chunks of 8, 16, 48
-// and 64 tiles; table-order kernels keep the round-robin order, which was
-// fastest for them.
+// Pool-order scatters deal their (tile, slab) grid to the 8 XCDs in chunks of
+// this many consecutive tiles (8 pool blocks of one slab at 8 heads; 256 KB for
+// the LLaMA-2-70B pool).  Measured on MI355X on that pool against the hardware's
+// round-robin dealing, contiguous eighths and chunks of 8, 16, 48 and 64 tiles.
 constexpr int kPoolChunk = 32;
+// The same for table-order launches whose tiles cross blocks.  80 layers of one
+// head, 1-byte cache, gather and scatter: round robin 903 and 990 us, chunks of
+// 4 907 and 996, of 16 890 and 969, of 64 887 and 968, of 256 898 and 972,
+// eighths 936 and 1013; launches of 400 MB do not tell them apart.
+constexpr int kTableChunk = 64;
 
 }  // namespace dv

@@ -71,17 +71,16 @@ __device__ __forceinline__ void xcd_tile(const Deal& d, uint32_t* tile, uint32_t
   *tile = t - *slab * d.tiles;
 }
 
-// Pool-order scatters: the linearised (tile, slab) grid dealt to the XCDs in
-// chunks of kPoolChunk consecutive items.  Workgroup `lin` runs on XCD lin %
-// 8 and takes item (lin / 8) % C of that XCD's (lin / 8) / C-th chunk; round
-// r gives chunk 8r + x to XCD x.  Items past the last whole round keep their
-// place.  A bijection on [0, total), whatever order the hardware actually
-// deals workgroups in.  On MI355X it lifts the LLaMA-2-70B pool-order
-// scatter from 75 % to 77 % of HBM peak, where contiguous eighths (as
-// xcd_tile) cost it 2 points and cost the table-order gather 6.
+// The linearised (tile, slab) grid dealt to the XCDs in chunks of C consecutive
+// items.  Workgroup `lin` runs on XCD lin % 8 and takes item (lin / 8) % C of
+// that XCD's (lin / 8) / C-th chunk; round r gives chunk 8r + x to XCD x.
+// Items past the last whole round keep their place.  A bijection on [0, total),
+// whatever order the hardware actually deals workgroups in.  On MI355X chunks
+// of 32 lift the LLaMA-2-70B pool-order scatter from 75 % to 77 % of HBM peak,
+// where contiguous eighths (as xcd_tile) cost it 2 points and cost the
+// table-order gather 6.
 template <typename U>
-__device__ __forceinline__ U xcd_chunk(U lin, U total) {
-  constexpr U C = kPoolChunk;
+__device__ __forceinline__ U xcd_chunk(U lin, U total, U C) {
   const U full = total / (8 * C) * (8 * C);
   if (lin >= full) return lin;
   const U x = lin % 8, k = lin / 8;
@@ -160,9 +159,10 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
   static_assert(!(ONE && WIDE), "wide launches look every unit up");
   const int lane = lane_id();
   const uint32_t ub = a.ub, heads = a.heads;
-  // Table order keeps the hardware's round-robin dealing: pool blocks are
-  // scattered by the block table anyway, and on MI355X every XCD-grouped
-  // order measured was slower (by 2-8 %).  Pool order deals chunks of tiles.
+  // Tiles within one block keep the hardware's round-robin dealing in table
+  // order: pool blocks are scattered by the block table anyway, and on MI355X
+  // every XCD-grouped order measured was slower (by 2-8 %).  Pool order, and
+  // table order with tiles across blocks, deal chunks of tiles.
   int64_t y = blockIdx.y;
   uint32_t tile = blockIdx.x;
   Seq q = {};
@@ -176,15 +176,22 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
     }
     if constexpr (WIDE) {
       const uint64_t t = xcd_chunk<uint64_t>(tile + (uint64_t)y * a.tiles,
-                                             (uint64_t)a.tiles * gridDim.y);
+                                             (uint64_t)a.tiles * gridDim.y, kPoolChunk);
       y = (int64_t)(t / (uint32_t)a.tiles);
       tile = (uint32_t)(t - (uint64_t)y * a.tiles);
     } else {
-      const uint32_t t = xcd_chunk<uint32_t>(tile + (uint32_t)y * a.tiles, a.tiles * gridDim.y);
+      const uint32_t t = xcd_chunk<uint32_t>(tile + (uint32_t)y * a.tiles, a.tiles * gridDim.y,
+                                             kPoolChunk);
       y = a.d_tiles.div(t);
       tile = t - (uint32_t)y * a.tiles;
     }
   } else {
+    if constexpr (!ONE && !WIDE) {
+      const uint32_t t = xcd_chunk<uint32_t>(tile + (uint32_t)y * a.tiles, a.tiles * gridDim.y,
+                                             kTableChunk);
+      y = a.d_tiles.div(t);
+      tile = t - (uint32_t)y * a.tiles;
+    }
     q = find_seq(a.s, tile);
     tile = q.k;
     first_blk = a.d_bs.div(q.t0);
