@@ -21,9 +21,8 @@
  *    on the host before anything is enqueued; on a validation error
  *    (DV_ERR_INVALID, _RANGE, _SPACE, _UNSUPPORTED) nothing is enqueued and no
  *    memory is touched.  DV_ERR_HIP means the runtime refused a launch or
- *    copy; a call that enqueues several (more than 64 sequences, split-key
- *    caches, ragged swaps, owner maps) may then have enqueued the ones
- *    before it, so the destination is unspecified until the call succeeds.
+ *    copy; a call that enqueues several (more than 64 sequences, ragged
+ *    swaps, owner maps) may then have enqueued the ones before it, so the destination is unspecified until the call succeeds.
  *  - Asynchrony: work is enqueued on `stream` (a hipStream_t; NULL is the
  *    null stream) and is complete only once that stream has been
  *    synchronised.  Host arrays passed in (ranges, mb_base, block_table) are
@@ -75,8 +74,8 @@ typedef enum {
                               whose stream of every layer and sequence at full capacity,
                               reaches 2^48 bytes,
                               or a launch whose grid would count 2^31 or more
-                              tiles or 16-byte units (each launch covers up to 64
-                              sequences; every launch of a call is checked first) */
+                              tiles or 16-byte units over 64 consecutive sequences
+                              (checked for the whole call before anything starts) */
   DV_ERR_HIP = -5          /* the HIP runtime refused to enqueue the work */
 } dv_status;
 
@@ -189,17 +188,17 @@ DV_API int dv_stream_out_token(const dv_cache* src, int32_t mb, int32_t l0, int3
  * t0 = pos, t1 = pos + 1.
  *
  * Paged receivers with a block_owner workspace for `mb`: when some
- * sequence's run per head is longer than 4 KB (shorter runs go through a
- * kernel that moves one 16-byte unit per lane in stream order), the call
- * has at most 256 sequences and fewer than 2^31 tokens, and it writes at
- * least five ninths of the pool's blocks, the library first rebuilds in the
- * workspace the inverse of the table over the streamed ranges (pool block
- * -> sequence * max_blocks + logical block, -1 for blocks not written) and
- * then writes the pool in physical block order in one launch, so the
- * writes are sequential instead of scattered
- * by the table (measured on MI355X: 69 % -> 75 % of HBM peak for the
- * LLaMA-2-70B stage's pool; below about five ninths of the blocks, the
- * workgroups that find no block to write cost more than that gains).  The bytes
+ * sequence's run per head is longer than 4 KB, the call has at most 256
+ * sequences and fewer than 2^31 tokens, and it writes at least five ninths of
+ * the pool's blocks, the library first rebuilds in the workspace the inverse
+ * of the table over the streamed ranges (pool block -> sequence * max_blocks +
+ * logical block, -1 for blocks not written).  If the ranges fill at least
+ * three quarters of those blocks it then writes the pool in physical block
+ * order, so the writes are sequential instead of scattered by the table
+ * (measured on MI355X: 69 % -> 76 % of HBM peak for the LLaMA-2-70B stage's
+ * pool; below about five ninths of the blocks, the workgroups that find no
+ * block to write cost more than that gains).  Otherwise, and for shorter runs,
+ * the units are written in stream order.  The bytes
  * written are the same either way.  The workspace must not overlap the
  * cache or `src` (DV_ERR_INVALID); its contents are scratch between calls,
  * and calls that scatter into the same microbatch must not overlap in time.

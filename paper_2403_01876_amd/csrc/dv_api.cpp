@@ -22,13 +22,13 @@ using dv::kSeqPerLaunch;
 // this go through the copy kernel instead of DMA.  Measured on MI355X for
 // the OPT-66B stage: a one-token update (256-byte rows) took 162 us by one
 // 2-D DMA and 2.5 ms by per-sequence DMA with ragged positions, against
-// about 100 us by kernel; rows of whole prompts move faster by DMA
-// (57 GB/s against 54 GB/s).
+// 90 to 113 us by kernel; rows of whole prompts move faster by DMA
+// (57 GB/s against 54 GB/s), which leaves the compute units to other streams.
 constexpr int64_t kNarrowRowBytes = 64 * 1024;
 
 // Streams whose longest (sequence, head) run has at most this many 16-byte
-// units use the flattened short-run kernel; longer runs use the tiled
-// kernels, whose 512-unit tiles would otherwise leave most lanes idle.
+// units use the short-run kernels; longer runs the tiled ones, except where
+// they would leave many of a tile's lanes idle (run_stream).
 constexpr int64_t kSmallRunUnits = 256;
 
 // A validated view of one microbatch of a cache, sizes in 16-byte units.
@@ -296,7 +296,7 @@ hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uin
     a.bt = v.bt + g0 * v.max_blocks;
     a.s_slab = s_slab;
     a.s_blk = s_blk;
-    a.m = {2 * l0, 1, 0, 0, w_slab};
+    a.m = {2 * l0, 0, w_slab};
     a.ub = (int32_t)(v.bs * v.du);
     a.du = (int32_t)v.du;
     a.heads = (int32_t)v.H;
@@ -320,7 +320,7 @@ hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uin
   a.owner = how == Paged::kPool ? v.owner : nullptr;
   a.s_slab = s_slab;
   a.s_blk = s_blk;
-  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.m = {2 * l0, 0, w_slab};
   a.ub = (int32_t)(v.bs * v.du);
   a.du = (int32_t)v.du;
   a.heads = (int32_t)v.H;
@@ -409,7 +409,7 @@ int run_rows(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector<
   memset(&a, 0, sizeof a);
   a.cache = v.base;
   a.bt = v.bt;
-  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.m = {2 * l0, 0, w_slab};
   a.du = (int32_t)v.du;
   a.heads = (int32_t)v.H;
   a.d_du = dv::fast_div((uint32_t)v.du);
@@ -474,7 +474,7 @@ int run_dense(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
   a.s_slab = v.B * v.H * v.S * v.du;
   a.s_b = v.H * v.S * v.du;
   a.s_h = v.S * v.du;
-  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.m = {2 * l0, 0, w_slab};
   a.du = (int32_t)v.du;
   a.heads = (int32_t)v.H;
   int64_t p = 0;  // tokens of all earlier launches
@@ -505,7 +505,7 @@ int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
   a.s_slab = v.B * v.H * v.S * v.du;
   a.s_b = v.H * v.S * v.du;
   a.s_h = v.S * v.du;
-  a.m = {2 * l0, 1, 0, 0, w_slab};
+  a.m = {2 * l0, 0, w_slab};
   a.du = (int32_t)v.du;
   a.heads = (int32_t)v.H;
   a.seq_cap = (int32_t)v.S;

@@ -9,8 +9,8 @@
 
 namespace dv {
 
-// Sequences handled by one launch: one per lane of a 64-wide wavefront, so
-// per-sequence prefix sums are a single wavefront scan.
+// Sequences of an ordinary launch: one per lane of a 64-wide wavefront.  (Larger
+// batches go kSeqMany to a launch.)
 constexpr int kSeqPerLaunch = 64;
 constexpr int kThreads = 256;
 
@@ -58,9 +58,9 @@ struct SeqRanges {
 };
 
 // Slab = one (layer, K|V) half of the cache; grid row y handles cache slab
-// slab0 + y*slab_step, whose data sits in wire slab wslab0 + y*slab_step.
+// slab0 + y, whose data sits in wire slab y.
 struct SlabMap {
-  int32_t slab0, slab_step, wslab0, pad;
+  int32_t slab0, pad;
   int64_t w_slab;  // wire units per slab: N * heads * du
 };
 

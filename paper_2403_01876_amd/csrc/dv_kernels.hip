@@ -4,11 +4,11 @@
 // touches the payload and no MFMA is involved.
 //
 // Work resolution: a launch covers at most 64 sequences, one per lane of a
-// wavefront.  Each workgroup recomputes, with one 64-lane inclusive scan, the
-// prefix of per-sequence tile counts and token counts; a ballot of
-// "prefix <= my tile" then gives the workgroup's sequence directly.  The
-// per-sequence ranges travel by value in the kernel arguments, so nothing is
-// copied to the device before a launch.
+// wavefront, or 256, four per lane.  Their ranges travel by value in the kernel
+// arguments with the prefixes of their tile and token counts, so nothing is
+// copied to the device before a launch; a ballot of "prefix <= my tile" gives
+// the workgroup's sequence.  Divisions by extents that a launch shares are
+// multiplications (FastDiv).
 #include "dv_internal.h"
 
 namespace dv {
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kThreads) dense_runs_kernel(DenseRunArgs<N> a)
 
   u32x4* cache = (u32x4*)a.cache + (int64_t)(a.m.slab0 + y) * a.s_slab + (int64_t)q.b * a.s_b +
                  (int64_t)h * a.s_h + (int64_t)q.t0 * a.du + (int64_t)k * kDenseTile;
-  u32x4* wire = (u32x4*)a.wire + (int64_t)(a.m.wslab0 + y) * a.m.w_slab +
+  u32x4* wire = (u32x4*)a.wire + (int64_t)y * a.m.w_slab +
                 (int64_t)q.p * ((int64_t)a.heads * a.du) + (int64_t)h * run +
                 (int64_t)k * kDenseTile;
   const u32x4* src = (D == kPack) ? cache : wire;
@@ -196,8 +196,8 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
     tile = q.k;
     first_blk = a.d_bs.div(q.t0);
   }
-  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y * a.m.slab_step) * a.s_slab;
-  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y * a.m.slab_step) * a.m.w_slab;
+  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y) * a.s_slab;
+  u32x4* wire = (u32x4*)a.wire + y * a.m.w_slab;
 
   for (int step = 0; step < (WIDE ? a.steps : 1); ++step) {
     // The tile's first unit: unit r0 of head h0 of block j0.
@@ -334,8 +334,8 @@ __global__ void __launch_bounds__(kThreads) paged_runs_kernel(PagedRunArgs<N> a)
   const uint32_t run = q.n * a.du;  // units per head
   const float rcp = 1.0f / (float)run;
   const int64_t y = blockIdx.y;
-  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y * a.m.slab_step) * a.s_slab;
-  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y * a.m.slab_step) * a.m.w_slab +
+  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y) * a.s_slab;
+  u32x4* wire = (u32x4*)a.wire + y * a.m.w_slab +
                 (int64_t)q.p * ((int64_t)a.heads * a.du);
   const int32_t* row = a.bt + (int64_t)q.b * a.max_blocks;
   const int64_t units = (int64_t)a.heads * run;
@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
   const int64_t y = blockIdx.y;
   const int half = (int)(y & 1);  // the launch starts at a layer's key slab
   u32x4* cache = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab;
-  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y) * a.m.w_slab;
+  u32x4* wire = (u32x4*)a.wire + y * a.m.w_slab;
   const int64_t s_tok = a.s_tok[half], s_e = a.s_e[half];
   const uint32_t first = blockIdx.x * (kThreads * U);
   const uint32_t last = min(first + kThreads * U, (uint32_t)a.total) - 1;
@@ -570,7 +570,7 @@ __global__ void __launch_bounds__(kThreads) split_rows_kernel(RowArgs<N> a) {
   const int64_t y = blockIdx.y;
   const int half = (int)(y & 1);
   u32x4* cache = (u32x4*)a.cache + (a.m.slab0 + y) * a.s_slab;
-  u32x4* wire = (u32x4*)a.wire + (a.m.wslab0 + y) * a.m.w_slab;
+  u32x4* wire = (u32x4*)a.wire + y * a.m.w_slab;
   const uint32_t du = a.du, pitch = du + 1;
   const int64_t s_tok = a.s_tok[half], s_e = a.s_e[half];
   int64_t* s_off = (int64_t*)(lds + a.tile * pitch);
@@ -650,7 +650,7 @@ __global__ void __launch_bounds__(kThreads) split_kernel(SplitArgs<N> a) {
   const uint32_t units = ntk * du;
   u32x4* head = (u32x4*)a.cache + (int64_t)(a.m.slab0 + y) * a.s_slab + (int64_t)(a.b0 + q.b) * a.s_b +
                 (int64_t)h * a.s_h;
-  u32x4* wire = (u32x4*)a.wire + (int64_t)(a.m.wslab0 + y) * a.m.w_slab +
+  u32x4* wire = (u32x4*)a.wire + (int64_t)y * a.m.w_slab +
                 (int64_t)q.p * ((int64_t)a.heads * du) + ((int64_t)h * q.n + tok0) * du;
   u32x4 v[U];
   if (y & 1) {  // value slab
