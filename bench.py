@@ -492,8 +492,8 @@ def multi_token_bench(torch, dv, synth, ks=(1, 2, 4, 8, 16, 32)):
     accepts several tokens, or replication batched over K steps): stream-out
     then stream-in of [len, len + K) for every sequence, captured 50 times
     into a graph and replayed, on the OPT-13B stage and the LLaMA-2-70B paged
-    pool.  K = 1 takes the single-token kernel, 2 <= K <= 16 the short-run
-    kernel, K = 32 the tiled kernels."""
+    pool.  K <= 16 takes the short-run kernel, K = 32 the tiled
+    kernels."""
     dev = torch.device("cuda:0")
     out = {}
     for idx in (1, 4):
@@ -1502,7 +1502,7 @@ def roofline_rows(out, paged):
     row("llama2-70b-paged", "paged gather (table order)", "paged_kernel<pack>",
         gbs2(P, k["gather"]))
     row("llama2-70b-paged", "paged scatter, pool order (owner map included)",
-        "owner_clear/build + paged_kernel<unpack>", gbs2(P, k["scatter_pool_order"]))
+        "owner_map_kernel + paged_kernel<unpack>", gbs2(P, k["scatter_pool_order"]))
     row("llama2-70b-paged", "paged scatter, table order", "paged_kernel<unpack>",
         gbs2(P, k["scatter_table_order"]))
     step = out.get("opt13b_step")
@@ -1516,7 +1516,7 @@ def roofline_rows(out, paged):
         for op in ("stream_out", "stream_in", "stream_in_table_order"):
             if op in res:
                 row(name, op, "paged_kernel" if "paged" in name else
-                    ("ksplit_kernel + dense_runs_kernel" if "split" in name
+                    ("split_kernel" if "split" in name
                      else "dense_runs_kernel"), res[op]["GBps_2x"], cache=cold)
     sw = out.get("swap")
     if sw:
