@@ -189,19 +189,19 @@ DV_API int dv_stream_out_token(const dv_cache* src, int32_t mb, int32_t l0, int3
  *
  * Paged receivers with a block_owner workspace for `mb`: when some
  * sequence's run per head is longer than 4 KB, the call has at most 256
- * sequences and fewer than 2^31 tokens, and it writes at least five ninths of
- * the pool's blocks, the library first rebuilds in the workspace the inverse
- * of the table over the streamed ranges (pool block -> sequence * max_blocks +
- * logical block, -1 for blocks not written).  If the ranges fill at least
- * three quarters of those blocks it then writes the pool in physical block
+ * sequences and fewer than 2^31 tokens, it writes at least five ninths of the
+ * pool's blocks, and its ranges fill at least three quarters of the blocks
+ * they touch, the library first rebuilds in the workspace the inverse of the
+ * table over the streamed ranges (pool block -> sequence * max_blocks + logical
+ * block, -1 for blocks not written) and then writes the pool in physical block
  * order, so the writes are sequential instead of scattered by the table
  * (measured on MI355X: 69 % -> 76 % of HBM peak for the LLaMA-2-70B stage's
  * pool; below about five ninths of the blocks, the workgroups that find no
- * block to write cost more than that gains).  Otherwise, and for shorter runs,
- * the units are written in stream order.  The bytes
- * written are the same either way.  The workspace must not overlap the
- * cache or `src` (DV_ERR_INVALID); its contents are scratch between calls,
- * and calls that scatter into the same microbatch must not overlap in time.
+ * block to write cost more than that gains).  Every other call leaves the
+ * workspace as it is.  The bytes written to the pool are the same either way.
+ * The workspace must not overlap the cache or `src` (DV_ERR_INVALID); its
+ * contents are scratch between calls, and calls that scatter into the same
+ * microbatch must not overlap in time.
  * DV_OK, DV_ERR_INVALID, DV_ERR_RANGE, DV_ERR_SPACE, DV_ERR_UNSUPPORTED,
  * DV_ERR_HIP. */
 DV_API int dv_stream_in(const dv_cache* dst, int32_t mb, int32_t l0, int32_t l1, const int32_t* t0,

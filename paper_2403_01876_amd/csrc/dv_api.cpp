@@ -579,10 +579,11 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
       tiles += (n[b] * v.H * v.du + dv::kPagedTile - 1) / dv::kPagedTile;
     }
     Paged how = 4 * N < 3 * blocks * v.bs ? Paged::kWire : Paged::kTable;
-    if (dir == dv::kUnpack && v.owner && pool_order_applies(v, t0, n, N)) {
+    if (how == Paged::kTable && dir == dv::kUnpack && v.owner &&
+        pool_order_applies(v, t0, n, N)) {
       const int rc = build_owner_map(v, t0, n, st);
       if (rc != DV_OK) return rc;
-      if (how == Paged::kTable) how = Paged::kPool;
+      how = Paged::kPool;
     }
     flat = how == Paged::kWire && 4 * w_slab < 3 * tiles * dv::kPagedTile && w_slab < (1ll << 31);
     // More than 64 sequences go 256 to a launch while their tokens count

@@ -1,0 +1,90 @@
+"""Which kernels a call launches, without a GPU: the library's host code is
+linked with launchers that write down what they are asked (tests/c/
+dispatch_record.cpp) and called with made-up addresses, which nothing reads."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2403_01876_amd import dv
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+CACHE, WIRE, TABLE, OWNER = 1 << 44, 1 << 47, 1 << 46, 1 << 42
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("dispatch") / "libdispatch.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wall", "-Werror",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    os.path.join(ROOT, "paper_2403_01876_amd", "csrc", "dv_api.cpp"),
+                    os.path.join(ROOT, "tests", "c", "dispatch_record.cpp"),
+                    "-L", os.path.join(ROCM, "lib"), "-lamdhip64",
+                    "-Wl,-rpath," + os.path.join(ROCM, "lib"), "-o", out], check=True, timeout=300)
+    lib = ctypes.CDLL(out)
+    for name in ("dv_packed_bytes", "dv_stream_out_prompt", "dv_stream_in",
+                 "dv_stream_in_noalloc", "dv_swap_out"):
+        getattr(lib, name).argtypes = getattr(dv.lib, name).argtypes
+    lib.dispatch_record_take.restype = ctypes.c_char_p
+    return lib
+
+
+def paged(L, H, D, E, B, bs, nb, maxb, owner=True):
+    return dv.Cache(dv.DV_PAGED, L, H, D, B, [CACHE], elem_bytes=E, block_size=bs, num_blocks=nb,
+                    max_blocks=maxb, block_tables=[TABLE], block_owners=[OWNER] if owner else None)
+
+
+def dense(L, H, D, E, B, S, kind=dv.DV_DENSE):
+    return dv.Cache(kind, L, H, D, B, [CACHE], max_seq=S, elem_bytes=E)
+
+
+def call(lib, name, cache, t0, t1, status=dv.DV_OK):
+    """The launches of one call over all layers: a list of (kernel, fields)."""
+    t0 = np.ascontiguousarray(t0, np.int32)
+    t1 = np.ascontiguousarray(t1, np.int32)
+    args = [cache.ref, 0, 0, cache.c.num_layers, t0.ctypes.data, t1.ctypes.data, WIRE, 1 << 62]
+    lib.dispatch_record_take()
+    if name == "out":
+        got = lib.dv_stream_out_prompt(*args, None, None)
+    else:
+        got = getattr(lib, "dv_stream_in_noalloc" if name == "in_noalloc" else "dv_stream_in")(
+            *args, None)
+    assert got == status, (name, got)
+    lines = lib.dispatch_record_take().decode().splitlines()
+    return [(ln.split()[0], {k: int(v) for k, v in (f.split("=") for f in ln.split() if "=" in f)})
+            for ln in lines]
+
+
+def kernels(launches):
+    return [name for name, _ in launches]
+
+
+@pytest.mark.parametrize("name", ["in", "in_noalloc"])
+def test_owner_map_is_built_where_pool_order_reads_it(lib, name):
+    """Over random paged shapes and ranges the owner map is launched exactly
+    when the pool-order kernel follows, and that is when the header says."""
+    r = np.random.default_rng(3)
+    seen = set()
+    for _ in range(3000):
+        H, D, E = int(r.integers(1, 9)), int(r.choice([16, 64, 128])), int(r.choice([1, 2, 4]))
+        B, bs = int(r.choice([1, 3, 40, 64, 65, 256, 257])), int(r.choice([1, 4, 16, 64, 256]))
+        n = r.integers(0, int(r.choice([2, 40, 300, 1500])) + 1, size=B)
+        t0 = r.integers(0, int(r.choice([1, bs + 1, 4 * bs])), size=B)
+        t1 = t0 + n
+        blocks = int(np.where(n > 0, -(-t1 // bs) - t0 // bs, 0).sum())
+        maxb = max(1, -(-int(t1.max()) // bs))
+        nb = max(1, int(blocks / r.choice([1.0, 0.8, 0.56, 0.5, 0.3])))
+        c = paged(2, H, D, E, B, bs, nb, maxb)
+        ran = kernels(call(lib, name, c, t0, t1))
+        want = (B <= 256 and n.max() * D * E // 16 > 256 and n.max() > 1 and
+                9 * blocks >= 5 * nb and 4 * n.sum() >= 3 * blocks * bs)
+        assert ("pool" in ran) == want, (ran, blocks, nb, bs, n.sum())
+        built = [k for k in ran if k.startswith("owner")]
+        assert bool(built) == want, ran
+        if want:
+            assert ran[-1] == "pool" and ran[:-1] == built
+        seen.add((want, ran[-1] if ran else None))
+    assert {(True, "pool"), (False, "rows"), (False, "table")} <= seen

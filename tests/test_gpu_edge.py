@@ -198,7 +198,7 @@ def test_graph_replay_paged_pool_order_and_split_key(oracle_lib):
     round trip.  Each replay starts from a sentinel receiver and a garbage
     owner workspace and must give the oracle's result."""
     L, H, D, B, bs = 2, 3, 128, 5, 16
-    lens = [40, 17, 64, 1, 33]
+    lens = [40, 17, 64, 1, 48]  # 170 tokens in 13 blocks: over three quarters, so pool order
     steps = 4
     maxb = max((n + steps + bs - 1) // bs for n in lens) + 1
     bt, nb = synth.make_paged_tables(77, [n + steps for n in lens], bs, maxb)

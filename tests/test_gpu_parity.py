@@ -179,9 +179,10 @@ def test_paged_scatter_pool_order(oracle_lib, seed):
     """Scatter with an owner-map workspace: the pool equals the oracle's
     unpack whichever order the library picks; when the header's conditions
     hold (some run longer than 256 16-byte units, at most 256 sequences, at
-    least five ninths of the pool's blocks written) the workspace holds the owner
-    map afterwards, otherwise it is untouched.  A second call with another
-    table reuses the stale workspace."""
+    least five ninths of the pool's blocks written, those blocks three quarters
+    full) pool order runs and the workspace holds the owner map afterwards,
+    otherwise it is untouched.  A second call with another table reuses the
+    stale workspace."""
     r = np.random.default_rng(900 + seed)
     L, H, D, B, E, bs, lens, maxb, bt, nb = paged_setup(r, seed, big_batch=(seed % 6 == 5))
     kind = seed % 3
@@ -223,7 +224,8 @@ def test_paged_scatter_pool_order(oracle_lib, seed):
         # runs of at most 256 units per (sequence, head) take the short-run
         # kernel, which scatters in stream order
         pool_order = (n > 0 and B <= 256 and (t1 - t0).max() > 1 and
-                      (t1 - t0).max() * du > 256 and 9 * blocks >= 5 * nb)
+                      (t1 - t0).max() * du > 256 and 9 * blocks >= 5 * nb and
+                      4 * int((t1 - t0).clip(0).sum()) >= 3 * blocks * bs)
         w = G.host(ws)
         assert (w[nb * 4:] == 0x7E).all(), "wrote past the workspace"
         if pool_order:
