@@ -272,52 +272,22 @@ int32_t steps_for(Fill fill, int64_t* tiles) {
   return steps;
 }
 
-// How a paged call moves: tiles over whole blocks in table order or in pool
-// order (paged_kernel), or over the range alone in wire order
-// (paged_runs_kernel).
-enum class Paged { kTable, kPool, kWire };
-
 // One launch over sequences [g0, g0 + nseq) of a call, their part of the
 // contiguous buffer at `wire`.  In pool order (the owner map built) it covers
 // the whole pool and all sequences of the call.
 template <int N>
-hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
+hipError_t launch_paged_group(int dir, bool pool, const View& v, int32_t l0, uint32_t nl,
                               const std::vector<int32_t>& t0, const std::vector<int32_t>& n,
                               int64_t g0, int nseq, int64_t w_slab, void* wire,
                               hipStream_t st) {
   const int64_t s_blk = v.H * v.bs * v.du, s_slab = v.NB * s_blk;
-  const dv::FastDiv d_ub = dv::fast_div((uint32_t)(v.bs * v.du));
   int64_t tiles = 0;
-  if (how == Paged::kWire) {
-    dv::PagedRunArgs<N> a;
-    memset(&a, 0, sizeof a);
-    a.pool = v.base;
-    a.wire = wire;
-    a.bt = v.bt + g0 * v.max_blocks;
-    a.s_slab = s_slab;
-    a.s_blk = s_blk;
-    a.m = {2 * l0, 0, w_slab};
-    a.ub = (int32_t)(v.bs * v.du);
-    a.du = (int32_t)v.du;
-    a.heads = (int32_t)v.H;
-    a.num_blocks = (int32_t)v.NB;
-    a.max_blocks = (int32_t)v.max_blocks;
-    a.d_ub = d_ub;
-    a.steps = steps_for(
-        [&](int64_t steps) {
-          const int64_t tile = dv::kPagedTile * steps;
-          return fill_seqs(&a.s, t0, n, g0, nseq,
-                           [&](int i) { return (n[g0 + i] * v.H * v.du + tile - 1) / tile; });
-        },
-        &tiles);
-    return dv::launch_paged_runs<N>(dir, a, (uint32_t)tiles, 2 * nl, st);
-  }
   dv::PagedArgs<N> a;
   memset(&a, 0, sizeof a);
   a.pool = v.base;
   a.wire = wire;
   a.bt = v.bt + g0 * v.max_blocks;
-  a.owner = how == Paged::kPool ? v.owner : nullptr;
+  a.owner = pool ? v.owner : nullptr;
   a.s_slab = s_slab;
   a.s_blk = s_blk;
   a.m = {2 * l0, 0, w_slab};
@@ -327,7 +297,7 @@ hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uin
   a.nseq = nseq;
   a.num_blocks = (int32_t)v.NB;
   a.max_blocks = (int32_t)v.max_blocks;
-  a.d_ub = d_ub;
+  a.d_ub = dv::fast_div((uint32_t)(v.bs * v.du));
   a.d_heads = dv::fast_div((uint32_t)v.H);
   a.d_bs = dv::fast_div((uint32_t)v.bs);
   a.d_max = dv::fast_div((uint32_t)v.max_blocks);
@@ -341,7 +311,7 @@ hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uin
           units = std::max(units, f);
           return (f + tile - 1) / tile;
         });
-        if (how != Paged::kPool) return table;
+        if (!pool) return table;
         units = s_slab;
         return (s_slab + tile - 1) / tile;
       },
@@ -356,7 +326,7 @@ hipError_t launch_paged_group(int dir, Paged how, const View& v, int32_t l0, uin
 // A paged stream of runs longer than the short-run kernel's, in launches of
 // at most N sequences.
 template <int N>
-int run_paged(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
+int run_paged(int dir, bool pool, const View& v, int32_t l0, uint32_t nl,
               const std::vector<int32_t>& t0, const std::vector<int32_t>& n, int64_t w_slab,
               void* wire, hipStream_t st) {
   int64_t p = 0;  // tokens of all earlier launches
@@ -366,7 +336,7 @@ int run_paged(int dir, Paged how, const View& v, int32_t l0, uint32_t nl,
     for (int i = 0; i < nseq; ++i) tok += n[g0 + i];
     if (tok == 0) continue;
     const hipError_t e =
-        launch_paged_group<N>(dir, how, v, l0, nl, t0, n, g0, nseq, w_slab,
+        launch_paged_group<N>(dir, pool, v, l0, nl, t0, n, g0, nseq, w_slab,
                               static_cast<char*>(wire) + (uint64_t)p * v.H * v.du * 16, st);
     if (e != hipSuccess) return hip_fail(e, "paged kernel launch");
     p += tok;
@@ -570,28 +540,29 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
   bool flat = single || small;  // the short-run kernel
   if (v.kind == DV_PAGED && !single && !small) {
     // Tiles over whole blocks leave the lanes of tokens outside the range
-    // idle: where the range covers less than three quarters of its blocks,
-    // tiles over the range alone, and where those would not be three quarters
-    // full either (a few hundred units per sequence), the short-run kernel.
-    int64_t blocks = 0, tiles = 0;
-    for (int64_t b = 0; b < v.B; ++b) {
-      blocks += blocks_of(v, t0[b], n[b]);
-      tiles += (n[b] * v.H * v.du + dv::kPagedTile - 1) / dv::kPagedTile;
-    }
-    Paged how = 4 * N < 3 * blocks * v.bs ? Paged::kWire : Paged::kTable;
-    if (how == Paged::kTable && dir == dv::kUnpack && v.owner &&
-        pool_order_applies(v, t0, n, N)) {
+    // idle: where the range fills less than three quarters of its blocks, rows.
+    // Tiles in table order, tiles in pool order, rows; 20 layers, 8 heads x 128
+    // x 2 bytes, 32 sequences, the pool written whole: blocks of 16 tokens 36 %
+    // full 17.9, -, 13.8 us out, 17.9, 18.8, 14.3 in; 73 % 55.2, -, 53.1 out,
+    // 55.5, 55.7, 54.2 in; 94 % 54.7, -, 54.1 out, 55.3, 55.4, 54.6 in; of 64
+    // tokens 71 % full 191, -, 182 out, 192, 187, 191 in, 90 % 278, -, 278 out,
+    // 282, 276, 292 in; of 256 tokens 34 % 205, -, 142 out, 209, 168, 151 in.
+    int64_t blocks = 0;
+    for (int64_t b = 0; b < v.B; ++b) blocks += blocks_of(v, t0[b], n[b]);
+    const bool partial = 4 * N < 3 * blocks * v.bs;
+    flat = partial && w_slab < (1ll << 31);
+    const bool pool =
+        !partial && dir == dv::kUnpack && v.owner && pool_order_applies(v, t0, n, N);
+    if (pool) {
       const int rc = build_owner_map(v, t0, n, st);
       if (rc != DV_OK) return rc;
-      how = Paged::kPool;
     }
-    flat = how == Paged::kWire && 4 * w_slab < 3 * tiles * dv::kPagedTile && w_slab < (1ll << 31);
     // More than 64 sequences go 256 to a launch while their tokens count
     // below 2^31 (those of 64 always do).
     if (!flat)
       return v.B > kSeqPerLaunch && N < (1ll << 31)
-                 ? run_paged<dv::kSeqMany>(dir, how, v, l0, nl, t0, n, w_slab, wire, st)
-                 : run_paged<kSeqPerLaunch>(dir, how, v, l0, nl, t0, n, w_slab, wire, st);
+                 ? run_paged<dv::kSeqMany>(dir, pool, v, l0, nl, t0, n, w_slab, wire, st)
+                 : run_paged<kSeqPerLaunch>(dir, pool, v, l0, nl, t0, n, w_slab, wire, st);
   }
 
   if (v.kind == DV_DENSE_KSPLIT && !flat) {

@@ -120,23 +120,6 @@ struct PagedArgs {
 };
 static_assert(sizeof(PagedArgs<kSeqMany>) <= 3584, "arguments stay well under 4 KB");
 
-// Paged runs in wire order: a tile is kPagedTile consecutive units of one
-// sequence's part of the contiguous buffer, (head, token, group) order.
-template <int N>
-struct PagedRunArgs {
-  void* pool;
-  void* wire;
-  const int32_t* bt;
-  int64_t s_slab, s_blk;
-  SlabMap m;
-  int32_t ub, du, heads;
-  int32_t num_blocks, max_blocks;
-  int32_t steps;         // tiles a workgroup takes one after another (1 unless the grid
-                         // would pass 2^32 lanes)
-  FastDiv d_ub;
-  SeqTable<N> s;
-};
-
 // Sequences a pool-order stream-in covers.
 constexpr int kPoolSeqMax = kSeqMany;
 
@@ -264,9 +247,6 @@ hipError_t launch_dense_runs(int dir, const DenseRunArgs<N>& a, uint32_t nslabs,
 template <int N>
 hipError_t launch_paged(int dir, const PagedArgs<N>& a, bool wide, uint32_t nslabs,
                         hipStream_t s);
-template <int N>
-hipError_t launch_paged_runs(int dir, const PagedRunArgs<N>& a, uint32_t tiles_per_slab,
-                             uint32_t nslabs, hipStream_t s);
 // Sets every entry of the owner map to -1.
 hipError_t launch_owner_clear(const OwnerArgs& a, hipStream_t s);
 // Fills the owner map from the table for sequences [b0, b0 + nseq).

@@ -326,54 +326,6 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
   }
 }
 
-// Paged runs in wire order: grid (tiles_per_slab, nslabs).  Every lane holds a
-// unit of the range itself, however little of its blocks the range covers.
-template <int D, int N>
-__global__ void __launch_bounds__(kThreads) paged_runs_kernel(PagedRunArgs<N> a) {
-  const Seq q = find_seq(a.s, blockIdx.x);
-  const uint32_t run = q.n * a.du;  // units per head
-  const float rcp = 1.0f / (float)run;
-  const int64_t y = blockIdx.y;
-  u32x4* pool = (u32x4*)a.pool + (a.m.slab0 + y) * a.s_slab;
-  u32x4* wire = (u32x4*)a.wire + y * a.m.w_slab +
-                (int64_t)q.p * ((int64_t)a.heads * a.du);
-  const int32_t* row = a.bt + (int64_t)q.b * a.max_blocks;
-  const int64_t units = (int64_t)a.heads * run;
-  for (int step = 0; step < a.steps; ++step) {
-    const int64_t f = ((int64_t)q.k * a.steps + step) * kPagedTile;
-    if (f >= units) return;
-    // The tile starts at unit r0 of head h0's run.
-    const uint32_t h0 = f >> 32 ? (uint32_t)(f / run) : (uint32_t)f / run;
-    const uint32_t r0 = (uint32_t)(f - (int64_t)h0 * run);
-    u32x4 v[kPagedUnroll];
-    int64_t po[kPagedUnroll];
-    bool ok[kPagedUnroll];
-#pragma unroll
-    for (int i = 0; i < kPagedUnroll; ++i) {
-      const uint32_t idx = i * kThreads + threadIdx.x;
-      // Runs passed since r0: at most one where a run is longer than a tile;
-      // else z < 2^10, (z + 1/2) / run is at least 2^-10 away from an integer
-      // and its error in float below 2^-12.
-      const uint32_t z = r0 + idx;
-      const uint32_t d = run >= (uint32_t)kPagedTile ? (z >= run)
-                                                     : (uint32_t)(((float)z + 0.5f) * rcp);
-      const uint32_t h = h0 + d;
-      ok[i] = f + idx < units;
-      const uint32_t pu = ok[i] ? q.t0 * a.du + (z - d * run) : q.t0 * a.du;
-      const uint32_t j = a.d_ub.div(pu);
-      const int blk = row[j];
-      ok[i] = ok[i] && blk >= 0 && blk < a.num_blocks;  // unmapped block: skipped
-      po[i] = (int64_t)blk * a.s_blk + (int64_t)h * a.ub + (pu - j * a.ub);
-      v[i] = (D == kPack) ? ld_nt(pool + (ok[i] ? po[i] : 0))
-                          : ld_nt(wire + (ok[i] ? f + idx : 0));
-    }
-#pragma unroll
-    for (int i = 0; i < kPagedUnroll; ++i)
-      if (ok[i])
-        st_nt(v[i], (D == kPack) ? wire + f + i * kThreads + threadIdx.x : pool + po[i]);
-  }
-}
-
 // Owner map in one launch (see OwnerMapArgs).  Four chunks of a wave are in
 // flight at a time: the launch is bound by their latency.
 template <int N>
@@ -800,22 +752,10 @@ hipError_t launch_paged(int dir, const PagedArgs<N>& a, bool wide, uint32_t nsla
                                                : paged_fn<N, false, false>(dir, pool);
   return launch(fn, dim3(a.tiles, nslabs), a, s);
 }
-template <int N>
-hipError_t launch_paged_runs(int dir, const PagedRunArgs<N>& a, uint32_t tiles_per_slab,
-                             uint32_t nslabs, hipStream_t s) {
-  const void* fn = dir == kPack ? (const void*)&paged_runs_kernel<kPack, N>
-                                : (const void*)&paged_runs_kernel<kUnpack, N>;
-  return launch(fn, dim3(tiles_per_slab, nslabs), a, s);
-}
 template hipError_t launch_paged<kSeqPerLaunch>(int, const PagedArgs<kSeqPerLaunch>&, bool,
                                                 uint32_t, hipStream_t);
 template hipError_t launch_paged<kSeqMany>(int, const PagedArgs<kSeqMany>&, bool, uint32_t,
                                            hipStream_t);
-template hipError_t launch_paged_runs<kSeqPerLaunch>(int, const PagedRunArgs<kSeqPerLaunch>&,
-                                                     uint32_t, uint32_t, hipStream_t);
-template hipError_t launch_paged_runs<kSeqMany>(int, const PagedRunArgs<kSeqMany>&, uint32_t,
-                                                uint32_t, hipStream_t);
-
 // Workgroups of kThreads lanes covering n items (n up to INT32_MAX).
 static uint32_t groups_of(int32_t n) { return (uint32_t)(((int64_t)n + kThreads - 1) / kThreads); }
 

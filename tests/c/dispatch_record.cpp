@@ -39,11 +39,6 @@ hipError_t launch_paged(int dir, const PagedArgs<N>& a, bool wide, uint32_t slab
   return record("%s %s n=%d tiles=%d slabs=%u steps=%d wide=%d\n", a.owner ? "pool" : "table",
                 way(dir), N, a.tiles, slabs, a.steps, (int)wide);
 }
-template <int N>
-hipError_t launch_paged_runs(int dir, const PagedRunArgs<N>& a, uint32_t tiles, uint32_t slabs,
-                             hipStream_t) {
-  return record("wire %s n=%d tiles=%u slabs=%u steps=%d\n", way(dir), N, tiles, slabs, a.steps);
-}
 hipError_t launch_owner_clear(const OwnerArgs&, hipStream_t) { return record("owner-clear\n"); }
 hipError_t launch_owner_build(const OwnerArgs& a, hipStream_t) {
   return record("owner-build b0=%d nseq=%d\n", a.b0, a.nseq);
@@ -85,10 +80,6 @@ template hipError_t launch_paged<kSeqPerLaunch>(int, const PagedArgs<kSeqPerLaun
                                                 hipStream_t);
 template hipError_t launch_paged<kSeqMany>(int, const PagedArgs<kSeqMany>&, bool, uint32_t,
                                            hipStream_t);
-template hipError_t launch_paged_runs<kSeqPerLaunch>(int, const PagedRunArgs<kSeqPerLaunch>&,
-                                                     uint32_t, uint32_t, hipStream_t);
-template hipError_t launch_paged_runs<kSeqMany>(int, const PagedRunArgs<kSeqMany>&, uint32_t,
-                                                uint32_t, hipStream_t);
 template hipError_t launch_owner_map<kSeqPerLaunch>(const OwnerMapArgs<kSeqPerLaunch>&,
                                                     hipStream_t);
 template hipError_t launch_owner_map<kSeqMany>(const OwnerMapArgs<kSeqMany>&, hipStream_t);

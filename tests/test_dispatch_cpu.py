@@ -88,3 +88,22 @@ def test_owner_map_is_built_where_pool_order_reads_it(lib, name):
             assert ran[-1] == "pool" and ran[:-1] == built
         seen.add((want, ran[-1] if ran else None))
     assert {(True, "pool"), (False, "rows"), (False, "table")} <= seen
+
+
+@pytest.mark.parametrize("name", ["out", "in"])
+@pytest.mark.parametrize("owner", [False, True])
+def test_ranges_under_three_quarters_of_their_blocks_go_by_rows(lib, name, owner):
+    """48 of 64 tokens stand for the table's (or the pool's) order, 47 for rows,
+    whether rows fill tiles of their own well (16 heads) or not (one head); slabs
+    of 2^31 units and more are past the row kernel and keep whole blocks."""
+    whole = "pool" if owner and name == "in" else "table"
+    for H in (1, 16):
+        c = paged(2, H, 128, 2, 5, 64, 5, 1, owner)
+        z = np.zeros(5, np.int32)
+        assert kernels(call(lib, name, c, z, z + 48))[-1] == whole
+        assert kernels(call(lib, name, c, z, z + 47)) == ["rows"]
+        t0, t1 = z + 8, z + 50  # 42 tokens
+        assert kernels(call(lib, name, c, t0, t1)) == ["rows"]
+    big = paged(1, 1 << 16, 128, 2, 1, 4096, 1, 1, owner)  # 2^20 units a token
+    assert kernels(call(lib, name, big, [0], [2047])) == ["rows"]
+    assert kernels(call(lib, name, big, [0], [2048])) == ["table"]

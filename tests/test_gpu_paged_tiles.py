@@ -1,9 +1,9 @@
 """Paged streams at the edges of the kernel's tiles, byte for byte against the
 oracle: blocks smaller than a tile (several to a tile), blocks that tiles
 straddle, blocks of whole tiles, ranges that cover just more and just less than
-three quarters of their blocks (where tiles over whole blocks give way to tiles
-over the range, or to the short-run kernel), unmapped table entries inside the ranges, and batches past 64
-and 256 sequences.  One case has tiles whose unit numbers pass 2^31."""
+three quarters of their blocks (where tiles over whole blocks give way to the
+rows of the range alone), unmapped table entries inside the ranges, and batches
+past 64 and 256 sequences.  One case has tiles whose unit numbers pass 2^31."""
 import numpy as np
 import pytest
 
