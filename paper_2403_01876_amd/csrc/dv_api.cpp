@@ -480,13 +480,18 @@ int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
   a.heads = (int32_t)v.H;
   a.seq_cap = (int32_t)v.S;
   a.tile = dv::split_tile(v.du);
+  if (v.S % 8 == 0) {  // then slabs, heads and groups are whole lines apart
+    a.line0 = (int32_t)((reinterpret_cast<uintptr_t>(v.base) >> 4) & 7);
+    a.line_mask = 7;
+  }
   a.d_du = dv::fast_div((uint32_t)v.du);
   a.d_tile = dv::fast_div((uint32_t)a.tile);
   int64_t p = 0;  // tokens of all earlier launches
   for (int64_t g0 = 0; g0 < v.B; g0 += N) {
     const int nseq = (int)std::min<int64_t>(N, v.B - g0);
     const int64_t tiles = fill_seqs(&a.s, t0, n, g0, nseq, [&](int i) {
-      return v.H * ((n[g0 + i] + a.tile - 1) / a.tile);
+      const int64_t lead = (a.line0 + t0[g0 + i]) & a.line_mask, k = n[g0 + i];
+      return k > 0 ? v.H * ((lead + k + a.tile - 1) / a.tile) : 0;
     });
     if (tiles == 0) continue;
     a.wire = static_cast<char*>(wire) + (uint64_t)p * v.H * v.du * 16;
@@ -574,7 +579,8 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     for (int64_t b = 0; b < v.B; ++b) tiles += (n[b] + tile - 1) / tile;
     flat = 4 * N < 3 * tiles * tile && w_slab < (1ll << 31);
     if (!flat)
-      return v.B > kSeqPerLaunch && N < (1ll << 31) && tiles * v.H < (1ll << 32) / dv::kThreads
+      return v.B > kSeqPerLaunch && N < (1ll << 31) &&
+                     (tiles + v.B) * v.H < (1ll << 32) / dv::kThreads
                  ? run_split<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
                  : run_split<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
   }

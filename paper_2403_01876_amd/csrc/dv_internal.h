@@ -189,7 +189,9 @@ struct RowArgs {
 static_assert(sizeof(RowArgs<kSeqMany>) <= 3584, "arguments stay well under 4 KB");
 
 // Split-key caches, long runs: a tile is a.tile tokens of one (sequence, head);
-// key slabs go through LDS, value slabs straight across, in one launch.
+// key slabs go through LDS, value slabs straight across, in one launch.  Where a
+// head's groups start on lines of 8 tokens (line_mask 7), tiles end on them too:
+// a run's first tile is shorter by the tokens its start lies past one.
 template <int N>
 struct SplitArgs {
   void* cache;
@@ -200,7 +202,7 @@ struct SplitArgs {
   int32_t heads, b0;
   int32_t seq_cap;       // S: units between consecutive groups of one head
   int32_t tile;          // tokens per tile (a multiple of 8)
-  int32_t pad;
+  int32_t line0, line_mask;  // token t lies (line0 + t) & line_mask past a line's start
   Deal deal;
   FastDiv d_du, d_tile;
   SeqTable<N> s;
@@ -208,7 +210,7 @@ struct SplitArgs {
 
 // Tokens per tile: whole 128-byte lines of a key slab (8 tokens of a group) in
 // two units per lane, or in six where two would leave more than a fifth of the
-// lanes idle (22-25 groups per token: 16 tokens fill 70 to 78 %).  37 layers of
+// lanes idle (17 and 22-25 groups per token: 24 and 16 tokens fill 69 to 80 %).  37 layers of
 // 12 heads x 96 x 4 bytes, 0.76 GB: 259 and 269 us out and in with six, 261 and
 // 283 with two, 263 and 281 with four.
 inline int32_t split_tile(int64_t du) {

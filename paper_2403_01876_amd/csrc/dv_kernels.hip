@@ -587,7 +587,11 @@ __global__ void __launch_bounds__(kThreads) split_rows_kernel(RowArgs<N> a) {
 // Bound by HBM for whole prompts: the OPT-13B stage's split-key shape (1.28 GB)
 // takes 397 and 396 us one way, 6.3 TB/s, against 402 and 399 in two launches
 // with key tiles of 16 KB (4 workgroups to a CU); small prompts gain the launch
-// (10 layers, one head, 254 tokens: 5.7 -> 2.5 us).
+// (10 layers, one head, 254 tokens: 5.7 -> 2.5 us).  Tiles that end inside lines
+// write those twice, each time in part: 16 sequences of 300-1100 tokens at
+// positions 0-200, 20 heads, 32 groups a token, 399 MB, 138.2 and 158.9 us out and
+// in, 132.1 and 132.3 with tiles that end on lines; 16 groups, 331 MB, 112.2 and
+// 118.7, 110.1 and 110.0.
 // ---------------------------------------------------------------------------
 template <int D, int U, int N>
 __global__ void __launch_bounds__(kThreads) split_kernel(SplitArgs<N> a) {
@@ -595,10 +599,11 @@ __global__ void __launch_bounds__(kThreads) split_kernel(SplitArgs<N> a) {
   uint32_t tile, y;
   xcd_tile(a.deal, &tile, &y);
   const Seq q = find_seq(a.s, tile);
-  const uint32_t tpr = a.d_tile.div(q.n + a.tile - 1);  // tiles per run
+  const uint32_t lead = (a.line0 + q.t0) & a.line_mask;
+  const uint32_t tpr = a.d_tile.div(lead + q.n + a.tile - 1);  // tiles per run
   const uint32_t h = (uint32_t)q.k / tpr, k = (uint32_t)q.k - h * tpr;
-  const uint32_t du = a.du, tok0 = k * a.tile;
-  const uint32_t ntk = min((uint32_t)a.tile, q.n - tok0);
+  const uint32_t du = a.du, tok0 = k ? k * a.tile - lead : 0;
+  const uint32_t ntk = min((k + 1) * a.tile - lead, (uint32_t)q.n) - tok0;
   const uint32_t units = ntk * du;
   u32x4* head = (u32x4*)a.cache + (int64_t)(a.m.slab0 + y) * a.s_slab + (int64_t)(a.b0 + q.b) * a.s_b +
                 (int64_t)h * a.s_h;

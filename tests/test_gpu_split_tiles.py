@@ -19,15 +19,21 @@ from paper_2403_01876_amd import dv  # noqa: E402
 from tests import gpu_util as G  # noqa: E402
 
 
-def check(oracle_lib, L, H, D, E, t0, n):
+def check(oracle_lib, L, H, D, E, t0, n, whole_lines=False, shift=0):
+    """``whole_lines``: a capacity of whole 128-byte lines (8 tokens of a group),
+    the caches starting ``shift`` tokens past a line."""
     B = len(n)
     t0 = np.asarray(t0, np.int32)
     t1 = (t0 + n).astype(np.int32)
     S = int(t1.max()) + 3
+    if whole_lines:
+        S += -S % 8
     lay = oracle.Layout(oracle.KSPLIT, L, H, D, B, seq_cap=S, elem_bytes=E)
     host = synth.fill_bytes(lay.storage_bytes(), 51)
-    src = dv.Cache(dv.DV_DENSE_KSPLIT, L, H, D, B, [G.to_dev(host)], max_seq=S, elem_bytes=E)
-    recv = G.dev_const(lay.storage_bytes(), 0xA5)
+    moved = G.dev_const(lay.storage_bytes() + 16 * shift, 0)[16 * shift:]
+    moved[:host.size] = G.to_dev(host)[:host.size]
+    src = dv.Cache(dv.DV_DENSE_KSPLIT, L, H, D, B, [moved], max_seq=S, elem_bytes=E)
+    recv = G.dev_const(lay.storage_bytes() + 16 * shift, 0xA5)[16 * shift:]
     dst = dv.Cache(dv.DV_DENSE_KSPLIT, L, H, D, B, [recv], max_seq=S, elem_bytes=E)
     size = dv.dv_packed_bytes(src, 0, L, t0, t1)
     wire = G.dev_const(size + 32, 0x5C)
@@ -48,6 +54,21 @@ def test_split_tiles(oracle_lib, groups):
     tile = two if two * groups * 5 >= 4 * 512 else six  # tokens
     n = np.array([3 * tile, 4 * tile + 1, 4 * tile - 1, 0, 4 * tile])
     check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 13], n)
+
+
+@pytest.mark.parametrize("groups", [1, 5, 16, 24, 32])
+@pytest.mark.parametrize("shift", [0, 3, 7])
+def test_split_tiles_that_end_on_lines(oracle_lib, groups, shift):
+    """Capacities of whole lines: starts at every place in a line, runs that end
+    on a tile's last token, one past it and inside the shortened first tile."""
+    two, six = 512 // groups & ~7, 1536 // groups & ~7
+    tile = two if two * groups * 5 >= 4 * 512 else six  # tokens
+    t0 = np.arange(12)
+    lead = (t0 + shift) % 8
+    ends = np.array([4, 4, 4, 3, 3, 3, 5, 5, 5, 4, 4, 4]) * tile + np.tile([-1, 0, 1], 4)
+    n = ends - lead
+    n[4], n[8] = 0, 2
+    check(oracle_lib, 2, 2, 8 * groups, 2, t0, n, True, shift)
 
 
 @pytest.mark.parametrize("B, lo, hi", [(7, 18, 40), (90, 20, 64), (300, 33, 64)])
