@@ -209,14 +209,19 @@ struct SplitArgs {
 };
 
 // Tokens per tile: whole 128-byte lines of a key slab (8 tokens of a group) in
-// two units per lane, or in six where two would leave more than a fifth of the
-// lanes idle (17 and 22-25 groups per token: 24 and 16 tokens fill 69 to 80 %).  37 layers of
-// 12 heads x 96 x 4 bytes, 0.76 GB: 259 and 269 us out and in with six, 261 and
-// 283 with two, 263 and 281 with four.
-inline int32_t split_tile(int64_t du) {
-  const int32_t two = (int32_t)(2 * kThreads / du & ~7), six = (int32_t)(6 * kThreads / du & ~7);
-  return 5 * two * du >= 4 * 2 * kThreads ? two : six;
-}
+// two units per lane, or in six.  Six where two would leave more than a fifth of
+// the lanes idle (17 and 22-25 groups per token: 24 and 16 tokens fill 69 to 80
+// %).  37 layers of 12 heads x 96 x 4 bytes, 0.76 GB: 259 and 269 us out and in
+// with six, 261 and 283 with two, 263 and 281 with four.
+inline int32_t split_tile(int64_t du, bool six) { return (int32_t)((six ? 6 : 2) * kThreads / du & ~7); }
+inline bool split_six(int64_t du) { return 5 * split_tile(du, false) * du < 4 * 2 * kThreads; }
+// Six also for a stream-in from this many groups per token on where max_seq is
+// not whole lines, so that every tile ends inside some, if it fills those tiles
+// three quarters: 16 sequences of 300-1100 tokens, 20 heads, 32 groups, 261 MB,
+// 102.2 us with two, 97.6 with six; 20 groups, 285 MB, 108.5 and 105.2; 16
+// groups, 382 MB, 136.6 and 136.8; 60 sequences of 45-62 tokens, 32 groups, 474
+// MB, 186.7 and 191.9.
+constexpr int64_t kSplitSixDu = 20;
 constexpr size_t kSplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do not
 
 // Cache-to-cache copy of the same logical positions between two dense caches

@@ -58,7 +58,8 @@ hipError_t launch_split_rows(int dir, const RowArgs<N>& a, uint32_t slabs, hipSt
 }
 template <int N>
 hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t slabs, hipStream_t) {
-  return record("split %s n=%d tiles=%u slabs=%u\n", way(dir), N, a.deal.tiles, slabs);
+  return record("split %s n=%d tiles=%u slabs=%u tile=%d\n", way(dir), N, a.deal.tiles, slabs,
+                a.tile);
 }
 template <int N>
 hipError_t launch_copy(const CopyArgs<N>& a, uint32_t slabs, hipStream_t) {

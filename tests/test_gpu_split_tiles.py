@@ -54,6 +54,9 @@ def test_split_tiles(oracle_lib, groups):
     tile = two if two * groups * 5 >= 4 * 512 else six  # tokens
     n = np.array([3 * tile, 4 * tile + 1, 4 * tile - 1, 0, 4 * tile])
     check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 13], n)
+    # six units per lane on the way in, for 20 groups and more
+    n = np.array([3 * six, six // 2, six + 1, 0, 2 * six - 1])
+    check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 12], n)
 
 
 @pytest.mark.parametrize("groups", [1, 5, 16, 24, 32])
