@@ -479,20 +479,20 @@ int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
   a.du = (int32_t)v.du;
   a.heads = (int32_t)v.H;
   a.seq_cap = (int32_t)v.S;
-  bool six = dv::split_six(v.du);
+  int units = dv::split_units(v.du);
   if (v.S % 8 == 0) {  // then slabs, heads and groups are whole lines apart
     a.line0 = (int32_t)((reinterpret_cast<uintptr_t>(v.base) >> 4) & 7);
     a.line_mask = 7;
-  } else if (dir == dv::kUnpack && v.du >= dv::kSplitSixDu) {
-    const int64_t tile = dv::split_tile(v.du, true);
+  } else if (dir == dv::kUnpack && v.du >= dv::kSplitEightDu) {
+    const int64_t tile = dv::split_tile(v.du, 8);
     int64_t tok = 0, tiles = 0;
     for (int32_t k : n) {
       tok += k;
       tiles += (k + tile - 1) / tile;
     }
-    six = six || 4 * tok >= 3 * tiles * tile;
+    if (3 * tok >= tiles * tile) units = 8;
   }
-  a.tile = dv::split_tile(v.du, six);
+  a.tile = dv::split_tile(v.du, units);
   a.d_du = dv::fast_div((uint32_t)v.du);
   a.d_tile = dv::fast_div((uint32_t)a.tile);
   int64_t p = 0;  // tokens of all earlier launches
@@ -583,7 +583,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     // Where tiles of one head each would be less than three quarters full,
     // rows across heads and sequences (up to 22 tokens of 16 groups: 58 and 62
     // us by 64-token tiles, 44 and 47 by the tiles below, 32 and 45 by rows).
-    const int64_t tile = dv::split_tile(v.du, dv::split_six(v.du));
+    const int64_t tile = dv::split_tile(v.du, dv::split_units(v.du));
     int64_t tiles = 0;
     for (int64_t b = 0; b < v.B; ++b) tiles += (n[b] + tile - 1) / tile;
     flat = 4 * N < 3 * tiles * tile && w_slab < (1ll << 31);

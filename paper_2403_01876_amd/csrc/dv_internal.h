@@ -209,19 +209,21 @@ struct SplitArgs {
 };
 
 // Tokens per tile: whole 128-byte lines of a key slab (8 tokens of a group) in
-// two units per lane, or in six.  Six where two would leave more than a fifth of
-// the lanes idle (17 and 22-25 groups per token: 24 and 16 tokens fill 69 to 80
+// two units per lane, six or eight.  Six where two would leave more than a fifth
+// of the lanes idle (17 and 22-25 groups per token: 24 and 16 tokens fill 69 to 80
 // %).  37 layers of 12 heads x 96 x 4 bytes, 0.76 GB: 259 and 269 us out and in
 // with six, 261 and 283 with two, 263 and 281 with four.
-inline int32_t split_tile(int64_t du, bool six) { return (int32_t)((six ? 6 : 2) * kThreads / du & ~7); }
-inline bool split_six(int64_t du) { return 5 * split_tile(du, false) * du < 4 * 2 * kThreads; }
-// Six also for a stream-in from this many groups per token on where max_seq is
-// not whole lines, so that every tile ends inside some, if it fills those tiles
-// three quarters: 16 sequences of 300-1100 tokens, 20 heads, 32 groups, 261 MB,
-// 102.2 us with two, 97.6 with six; 20 groups, 285 MB, 108.5 and 105.2; 16
-// groups, 382 MB, 136.6 and 136.8; 60 sequences of 45-62 tokens, 32 groups, 474
-// MB, 186.7 and 191.9.
-constexpr int64_t kSplitSixDu = 20;
+inline int32_t split_tile(int64_t du, int units) { return (int32_t)(units * kThreads / du & ~7); }
+inline int split_units(int64_t du) { return 5 * split_tile(du, 2) * du >= 4 * 2 * kThreads ? 2 : 6; }
+// Eight for a stream-in from this many groups per token on where max_seq is not
+// whole lines, so that every tile ends inside some, if its runs fill those tiles
+// a third.  Two (as with whole lines) and eight units per lane, 20 heads: 32
+// groups, 50-62 tokens 120 and 109 us, 28-36 tokens 150 and 133, 0-47 tokens 145
+// and 135 (as good as two when they fill less), 20 groups, 36-50 tokens 125 and
+// 119, 60-100 tokens 126 and 120; 24 groups, where two is six: 70-75 tokens 122
+// and 106, 28-36 tokens 136 and 138.  16 groups of 300-1100 tokens do not gain
+// (136.6 with two, 138.5 with four, 136.8 with six).
+constexpr int64_t kSplitEightDu = 20;
 constexpr size_t kSplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do not
 
 // Cache-to-cache copy of the same logical positions between two dense caches

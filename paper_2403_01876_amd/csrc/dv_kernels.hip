@@ -830,16 +830,18 @@ template hipError_t launch_rows<kSeqMany>(int, bool, const RowArgs<kSeqMany>&, u
 
 template <int N>
 hipError_t launch_split(int dir, const SplitArgs<N>& a, uint32_t nslabs, hipStream_t s) {
-  const bool six = a.tile * a.du > kThreads * 2;
+  const int units = a.tile * a.du <= kThreads * 2 ? 2 : a.tile * a.du <= kThreads * 6 ? 6 : 8;
   const void* fn;
-  if (dir == kPack)
-    fn = six ? (const void*)&split_kernel<kPack, 6, N> : (const void*)&split_kernel<kPack, 2, N>;
+  if (dir == kPack)  // eight is for stream-in only
+    fn = units == 2 ? (const void*)&split_kernel<kPack, 2, N>
+                    : (const void*)&split_kernel<kPack, 6, N>;
   else
-    fn = six ? (const void*)&split_kernel<kUnpack, 6, N>
-             : (const void*)&split_kernel<kUnpack, 2, N>;
+    fn = units == 2   ? (const void*)&split_kernel<kUnpack, 2, N>
+         : units == 6 ? (const void*)&split_kernel<kUnpack, 6, N>
+                      : (const void*)&split_kernel<kUnpack, 8, N>;
   // Six units per lane: at most 4 workgroups to a CU (259 and 269 us as above;
-  // as many as fit 264 and 277).
-  const size_t lds = six ? kSplitLdsFor4 : (size_t)a.tile * (a.du + 1) * 16;
+  // as many as fit 264 and 277); eight need nearly as much.
+  const size_t lds = units > 2 ? kSplitLdsFor4 : (size_t)a.tile * (a.du + 1) * 16;
   return launch(fn, dim3(a.deal.tiles, nslabs), a, s, lds);
 }
 template hipError_t launch_split<kSeqPerLaunch>(int, const SplitArgs<kSeqPerLaunch>&, uint32_t,

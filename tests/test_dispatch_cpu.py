@@ -109,18 +109,17 @@ def test_ranges_under_three_quarters_of_their_blocks_go_by_rows(lib, name, owner
     assert kernels(call(lib, name, big, [0], [2048])) == ["table"]
 
 
-@pytest.mark.parametrize("du, tile, odd_in", [(16, 32, 32), (20, 24, 72), (32, 16, 48), (24, 64, 64)])
+@pytest.mark.parametrize("du, tile, odd_in", [(16, 32, 32), (20, 24, 96), (24, 64, 80), (32, 16, 64)])
 def test_split_tiles_for_capacities_that_are_not_whole_lines(lib, du, tile, odd_in):
-    """Tokens per tile: six units per lane instead of two for a stream-in of
-    wide tokens into a capacity that is no multiple of 8, where its runs fill
-    such tiles three quarters."""
+    """Tokens per tile: eight units per lane instead of two or six for a
+    stream-in of wide tokens into a capacity that is no multiple of 8, where its
+    runs fill such tiles a third."""
     z = np.zeros(3, np.int32)
-    for S, name, n, want in ((2048, "out", 1000, tile), (2048, "in", 1000, tile),
-                             (2049, "out", 1000, tile), (2049, "in", 1000, odd_in)):
+    cases = [(2048, "out", 1000, tile), (2048, "in", 1000, tile), (2049, "out", 1000, tile),
+             (2049, "in", 1000, odd_in)]
+    if odd_in > 2 * tile:
+        cases += [(2049, "in", tile, tile), (2049, "in", 2 * tile, odd_in)]
+    for S, name, n, want in cases:
         c = dense(40, 64, 8 * du, 2, 3, S, dv.DV_DENSE_KSPLIT)
         ran = call(lib, name, c, z, z + n)
         assert kernels(ran) == ["split"] and ran[0][1]["tile"] == want, (S, name, n, ran)
-    if odd_in > tile:  # two thirds and three quarters of six units per lane
-        c = dense(40, 64, 8 * du, 2, 3, 2049, dv.DV_DENSE_KSPLIT)
-        assert call(lib, "in", c, z, z + 2 * tile)[0][1]["tile"] == tile
-        assert call(lib, "in", c, z, z + 3 * odd_in // 4)[0][1]["tile"] == odd_in

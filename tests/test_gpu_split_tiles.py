@@ -1,6 +1,6 @@
 """Split-key streams of long runs at the edges of the kernel's tiles, byte for
 byte against the oracle: every tile length (whole 128-byte lines of a key slab
-in two units per lane, or in six), runs of whole tiles, of one token more and
+in two units per lane, six or eight), runs of whole tiles, of one token more and
 of one less, starts inside a line, runs that fill tiles badly (which go row by
 row), and batches past 64 and 256 sequences."""
 import numpy as np
@@ -54,8 +54,9 @@ def test_split_tiles(oracle_lib, groups):
     tile = two if two * groups * 5 >= 4 * 512 else six  # tokens
     n = np.array([3 * tile, 4 * tile + 1, 4 * tile - 1, 0, 4 * tile])
     check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 13], n)
-    # six units per lane on the way in, for 20 groups and more
-    n = np.array([3 * six, six // 2, six + 1, 0, 2 * six - 1])
+    # eight units per lane on the way in, for 20 groups and more
+    eight = 2048 // groups & ~7
+    n = np.array([3 * eight, eight // 2, eight + 1, 0, 2 * eight - 1])
     check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 12], n)
 
 
