@@ -580,13 +580,20 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
   }
 
   if (v.kind == DV_DENSE_KSPLIT && !flat) {
-    // Where tiles of one head each would be less than three quarters full,
-    // rows across heads and sequences (up to 22 tokens of 16 groups: 58 and 62
-    // us by 64-token tiles, 44 and 47 by the tiles below, 32 and 45 by rows).
+    // Where tiles of one head each would be less than three quarters full, rows
+    // across heads and sequences: always on the way out (up to 22 tokens of 16
+    // groups 44 us by tiles, 32 by rows), but on the way in only up to 400 MB over
+    // the groups per token.  A workgroup's rows of a key slab are written in
+    // pieces of lines, the shorter the wider the tokens.  Tiles and rows, 64
+    // sequences: 32 groups, 10-20 tokens, 10 MB 7.4 and 6.6 us, 20 MB 12.2 and
+    // 12.8, 101 MB 48 and 59, 391 MB 184 and 230; 16 groups, 10-60 tokens, 10 MB
+    // 6.1 and 5.6, 24 MB 11.7 and 12.4, 379 MB 147 and 181; 8 groups, 23-47
+    // tokens, 35 MB 16.3 and 15.6, 106 MB 43.8 and 45.2, 393 MB 156 and 177.
     const int64_t tile = dv::split_tile(v.du, dv::split_units(v.du));
     int64_t tiles = 0;
     for (int64_t b = 0; b < v.B; ++b) tiles += (n[b] + tile - 1) / tile;
-    flat = 4 * N < 3 * tiles * tile && w_slab < (1ll << 31);
+    flat = 4 * N < 3 * tiles * tile && w_slab < (1ll << 31) &&
+           (dir == dv::kPack || w_slab * 2 * nl * v.du <= 25'000'000);
     if (!flat)
       return v.B > kSeqPerLaunch && N < (1ll << 31) &&
                      (tiles + v.B) * v.H < (1ll << 32) / dv::kThreads

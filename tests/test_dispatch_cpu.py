@@ -117,9 +117,22 @@ def test_split_tiles_for_capacities_that_are_not_whole_lines(lib, du, tile, odd_
     z = np.zeros(3, np.int32)
     cases = [(2048, "out", 1000, tile), (2048, "in", 1000, tile), (2049, "out", 1000, tile),
              (2049, "in", 1000, odd_in)]
-    if odd_in > 2 * tile:
-        cases += [(2049, "in", tile, tile), (2049, "in", 2 * tile, odd_in)]
+    if odd_in > tile:
+        cases += [(2049, "in", (odd_in - 1) // 3, tile), (2049, "in", -(-odd_in // 3), odd_in)]
     for S, name, n, want in cases:
         c = dense(40, 64, 8 * du, 2, 3, S, dv.DV_DENSE_KSPLIT)
         ran = call(lib, name, c, z, z + n)
         assert kernels(ran) == ["split"] and ran[0][1]["tile"] == want, (S, name, n, ran)
+
+
+@pytest.mark.parametrize("du", [8, 16, 32])
+def test_large_split_key_stream_ins_of_short_runs_go_by_tiles(lib, du):
+    """Runs that fill a tile three fifths: rows on the way out at every size, on
+    the way in up to 25 million units times groups per token."""
+    n = 512 // du * 3 // 5
+    z = np.zeros(10, np.int32)
+    most = 25_000_000 // (2 * 5 * 10 * n * du * du)  # layers
+    for L in (most, most + 1):
+        c = dense(L, 5, 8 * du, 2, 10, 64, dv.DV_DENSE_KSPLIT)
+        assert kernels(call(lib, "out", c, z, z + n)) == ["split-rows"]
+        assert kernels(call(lib, "in", c, z, z + n)) == ["split-rows" if L == most else "split"]
