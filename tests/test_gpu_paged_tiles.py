@@ -118,6 +118,43 @@ def test_owner_map_one_launch_or_several(B, blocks):
     assert (got[:nb] == G.owner_map_expected(bt, nb, bs, t0, t1)).all() and got[nb] == 77
 
 
+@pytest.mark.parametrize("H, D, E, bs", [(1, 8, 2, 64), (1, 8, 2, 127), (1, 8, 2, 128), (1, 8, 2, 129),
+                                         (3, 64, 2, 16), (5, 80, 2, 8), (2, 72, 4, 30)])
+@pytest.mark.parametrize("B", [64, 65, 200])
+def test_pool_order_blocks_around_a_wave(oracle_lib, H, D, E, bs, B):
+    """Pool order, blocks of a wave's 128 units, one less and one more, and larger
+    ones that tiles straddle: a pool half again as large as what is written,
+    ranges that start and end inside blocks, one sequence without tokens."""
+    L, du = 2, D * E // 16
+    r = np.random.default_rng(H * bs + B)
+    t0 = r.integers(0, bs // 8 + 1, size=B).astype(np.int32)
+    n = bs * r.integers(3, 8, size=B) - r.integers(0, bs // 8 + 1, size=B)
+    n[1], n[B - 1] = 0, max(5 * bs, 256 // du + 1)
+    t1 = (t0 + n).astype(np.int32)
+    blocks = np.where(n > 0, -(-t1 // bs) - t0 // bs, 0)
+    maxb, nb = int(-(-t1.max() // bs)), int(blocks.sum() * 3 // 2)
+    assert 4 * n.sum() >= 3 * blocks.sum() * bs and 9 * blocks.sum() >= 5 * nb
+    bt = np.full((B, maxb), -1, np.int32)
+    free = iter(r.permutation(nb))
+    for b in range(B):
+        for j in range(t0[b] // bs, t0[b] // bs + blocks[b]):
+            bt[b, j] = next(free)
+    lay = oracle.Layout(oracle.PAGED, L, H, D, B, elem_bytes=E, block_size=bs, num_blocks=nb,
+                        block_table=bt)
+    recv = G.dev_const(lay.storage_bytes(), 0xA5)
+    owner = G.dev_const(nb * 4, 0x7E)
+    c = dv.Cache(dv.DV_PAGED, L, H, D, B, [recv], elem_bytes=E, block_size=bs, num_blocks=nb,
+                 max_blocks=maxb, block_tables=[G.to_dev(bt)], block_owners=[owner])
+    size = dv.dv_packed_bytes(c, 0, L, t0, t1)
+    wire_h = synth.fill_bytes(size, 33)
+    dv.dv_stream_in(c, 0, 0, L, t0, t1, G.to_dev(wire_h), size, stream())
+    torch.cuda.synchronize()
+    want = np.full(lay.storage_bytes(), 0xA5, np.uint8)
+    oracle_lib.unpack(lay, want, 0, L, t0, t1, wire_h)
+    assert G.host(recv)[: want.size].tobytes() == want.tobytes()
+    assert (G.host(owner).view(np.int32) == G.owner_map_expected(bt, nb, bs, t0, t1)).all()
+
+
 def test_unit_numbers_past_2_31():
     """One sequence whose blocks hold 2^31 units of a slab, all but three of
     them unmapped: gather, scatter in table order, and scatter in pool order
