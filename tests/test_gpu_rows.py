@@ -1,8 +1,9 @@
 """The short-run kernel where it can go wrong, byte for byte against the oracle:
 even and ragged runs, one and two units per lane (on either side of 2^18 units
 a launch), up to 64, up to 256 and more sequences with idle ones among them,
-tokens of one unit and of many, one head, and every layout; both halves of a
-split-key cache in one launch, from a layer other than the first."""
+tokens of one unit and of many, one head, few and many sequences to a wave, and
+every layout; both halves of a split-key cache in one launch, from a layer other
+than the first."""
 import numpy as np
 import pytest
 
@@ -33,6 +34,9 @@ SHAPES = {
     "longest-runs": (2, 2, 256, 5, (7, 8), 1.0),
     "two-units-per-lane": (3, 24, 128, 30, (1, 16), 1.0),
     "two-units-past-64": (2, 16, 128, 130, (1, 16), 1.0),
+    # sequences that a wave's 64 rows lie in: 40 to 45, four to six
+    "wave-of-forty": (2, 1, 8, 64, (1, 2), 1.0),
+    "wave-of-five": (2, 1, 8, 60, (11, 20), 1.0),
 }
 
 
