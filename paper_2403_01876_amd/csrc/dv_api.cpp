@@ -611,11 +611,17 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
     // out, 77.8, 73.5, 77.4 in; 13 of 1-18 tokens, 3 heads (30 %) 6.5, -, 5.3
     // out, 7.6, -, 4.9 in; 60 of 24-472 tokens, 8 heads x 80 (91 %) 729, 799,
     // 716 out, 728, 814, 792 in; prompts of 64-2048 tokens (98 %) 389, 416, 398
-    // out, 390, 423, 434 in.
+    // out, 390, 423, 434 in.  Tokens of one unit are a look-up each: below 16 MB
+    // their packs keep tiles that are 70 % full (8 MB, 79 %: 4.5 us by tiles, 5.3
+    // by rows; 11 MB, 74 % 5.6 and 6.1, 66 % 6.0 and 6.1, 52 % 7.5 and 6.4; 33 MB,
+    // 78 % 13.3 and 13.6, 82 % 14.6 and 14.1; four units a token, 11 MB, 78 % 5.7
+    // and 5.2).
     for (int64_t b = 0; b < v.B; ++b)
       dense_tiles += v.H * ((n[b] * v.du + dv::kDenseTile - 1) / dv::kDenseTile);
     const int64_t full = dense_tiles * dv::kDenseTile;
-    flat = w_slab < (1ll << 31) && 100 * w_slab < (dir == dv::kPack ? 92 : 45) * full;
+    const bool look_ups = v.du == 1 && w_slab * 2 * nl < (1 << 20);
+    const int line = dir == dv::kUnpack ? 45 : look_ups ? 70 : 92;
+    flat = w_slab < (1ll << 31) && 100 * w_slab < line * full;
     eighths = 100 * w_slab >= 80 * full;
   }
   if (flat)

@@ -136,3 +136,25 @@ def test_large_split_key_stream_ins_of_short_runs_go_by_tiles(lib, du):
         c = dense(L, 5, 8 * du, 2, 10, 64, dv.DV_DENSE_KSPLIT)
         assert kernels(call(lib, "out", c, z, z + n)) == ["split-rows"]
         assert kernels(call(lib, "in", c, z, z + n)) == ["split-rows" if L == most else "split"]
+
+
+@pytest.mark.parametrize("du, L, line", [(1, 1, 70), (1, 40, 92), (4, 1, 92)])
+def test_dense_runs_that_fill_tiles_badly_go_by_rows(lib, du, L, line):
+    """Out: below 92 % of the tiles' units, for small streams of one-unit tokens
+    below 70 %; in: below 45 %."""
+    B = 100
+    c = dense(L, 5, 16 * du, 1, B, 2048)
+    tile = 512 // du
+    z = np.zeros(B, np.int32)
+    for percent in (46, 60, 69, 71, 91, 93):  # runs of two tiles, of one below the half
+        tiles = 1 if percent < 52 else 2
+        n = z + -(-tiles * tile * percent // 100)
+        if percent == 46:  # below the short-run bound but for one run of two tiles
+            n[0] = tile + 1
+        full = int((-(-n * du // 512)).sum()) * 512
+        assert call(lib, "out", c, z, z + n)[0][0] == (
+            "rows" if 100 * n.sum() * du < line * full else "dense"), percent
+        assert call(lib, "in", c, z, z + n)[0][0] == (
+            "rows" if 100 * n.sum() * du < 45 * full else "dense"), percent
+    n = np.where(np.arange(B) % 10, 1, tile)  # mostly empty tiles
+    assert kernels(call(lib, "in", c, z, z + n)) == ["rows"]

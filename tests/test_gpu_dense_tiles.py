@@ -1,7 +1,7 @@
 """Dense streams on every side of the rules that pick their kernel, byte for byte
 against the oracle: runs that fill tiles of 512 units well (tiles dealt in
-eighths), fairly (tiles in the hardware's order on unpack, rows on pack) and
-badly (rows both ways), runs one unit short of and past a tile, and batches of
+eighths), fairly (tiles in the hardware's order on unpack, rows on pack, or the
+tiles both ways where a token is one unit) and badly (rows both ways), runs one unit short of and past a tile, and batches of
 up to 64, 256 and more sequences."""
 import numpy as np
 import pytest
@@ -29,6 +29,7 @@ SHAPES = {
     "a-third": (2, 256, 4, 11, 0, 5),
     "past-64": (2, 128, 2, 80, 20, 70),
     "past-256": (1, 128, 2, 300, 0, 40),
+    "with-one-unit-tokens": (3, 8, 2, 5, 720, 790),
 }
 
 
