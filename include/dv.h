@@ -21,8 +21,9 @@
  *    on the host before anything is enqueued; on a validation error
  *    (DV_ERR_INVALID, _RANGE, _SPACE, _UNSUPPORTED) nothing is enqueued and no
  *    memory is touched.  DV_ERR_HIP means the runtime refused a launch or
- *    copy; a call that enqueues several (more than 64 sequences, ragged
- *    swaps, owner maps) may then have enqueued the ones before it, so the destination is unspecified until the call succeeds.
+ *    copy; a call that enqueues several (more than 256 sequences, ragged
+ *    swaps, owner maps, slabs of tens of GB) may then have enqueued the ones
+ *    before it, so the destination is unspecified until the call succeeds.
  *  - Asynchrony: work is enqueued on `stream` (a hipStream_t; NULL is the
  *    null stream) and is complete only once that stream has been
  *    synchronised.  Host arrays passed in (ranges, mb_base, block_table) are
@@ -73,9 +74,13 @@ typedef enum {
                               elem_bytes) above 2^33 bytes, a cache whose storage, or
                               whose stream of every layer and sequence at full capacity,
                               reaches 2^48 bytes,
-                              or a launch whose grid would count 2^31 or more
-                              tiles or 16-byte units over 64 consecutive sequences
-                              (checked for the whole call before anything starts) */
+                              or a stream of which 64 consecutive sequences (the first 64,
+                              the next, ...) hold 2^31 or more pieces of one layer's keys
+                              or values: of 16 bytes where no run per head is longer than
+                              4 KB (and for swaps of rows under 64 KB), else of 8 KB of
+                              a dense or split-key run, 64 tokens of a split-key run, or
+                              two heads of a paged block (checked for the whole call
+                              before anything starts) */
   DV_ERR_HIP = -5          /* the HIP runtime refused to enqueue the work */
 } dv_status;
 

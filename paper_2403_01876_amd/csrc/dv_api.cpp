@@ -87,8 +87,9 @@ int layout_of(const dv_cache* c, View* v) {
   if (v->L > (1 << 24) || v->cap > (1 << 24) || v->du > (1 << 16) || v->H * v->du > (1 << 20) ||
       v->cap * v->du > (1ll << 30))
     return DV_ERR_UNSUPPORTED;
-  // The paged kernel flattens (head pair, unit) over two heads of one block:
-  // 2 * block_size * du units must stay well inside int32.
+  // A paged tile may reach past a sequence's last block, and a unit's place in
+  // the head's run is counted from the sequence's first: capacity and one block
+  // together must stay well inside int32.
   if (c->kind == DV_PAGED && v->bs * v->du > (1ll << 29)) return DV_ERR_UNSUPPORTED;
   // Every byte count derived from the descriptor stays far inside 64 bits:
   // its storage and the longest stream it can produce (all layers, every
@@ -164,6 +165,11 @@ bool overlaps_table(const View& v, const void* p, uint64_t n) {
   return v.bt && overlaps(p, n, v.bt, (uint64_t)v.B * v.max_blocks * 4);
 }
 
+// Blocks of the table that hold tokens [t0, t0 + n).
+int64_t blocks_of(const View& v, int64_t t0, int64_t n) {
+  return n > 0 ? (t0 + n + v.bs - 1) / v.bs - t0 / v.bs : 0;
+}
+
 // Whether a paged stream-in with an owner-map workspace scatters in pool
 // order: at most kPoolSeqMax sequences (their ranges travel in the launch's
 // arguments), at least five ninths of the pool's blocks written, and every
@@ -175,19 +181,19 @@ bool overlaps_table(const View& v, const void* p, uint64_t n) {
 // 95 %.
 bool pool_order_applies(const View& v, const std::vector<int32_t>& t0,
                         const std::vector<int32_t>& n, int64_t N) {
-  const int64_t ngrp = (v.H + dv::kPagedHeads - 1) / dv::kPagedHeads;
-  if (v.B > dv::kPoolSeqMax || N >= (1ll << 31) || v.NB * ngrp >= (1ll << 31) ||
+  // 2^30 blocks: a tile's block numbers reach past the pool's last.
+  if (v.B > dv::kPoolSeqMax || N >= (1ll << 31) || v.NB >= (1ll << 30) ||
       v.B * v.max_blocks >= (1ll << 31))
     return false;
-  int64_t tiles = 0;
-  for (int64_t b = 0; b < v.B; ++b)
-    if (n[b] > 0) tiles += ((t0[b] + n[b] + v.bs - 1) / v.bs - t0[b] / v.bs) * ngrp;
-  return 9 * tiles >= 5 * v.NB * ngrp;
+  int64_t blocks = 0;
+  for (int64_t b = 0; b < v.B; ++b) blocks += blocks_of(v, t0[b], n[b]);
+  return 9 * blocks >= 5 * v.NB;
 }
 
 // Fills a launch's sequence table for sequences [g0, g0 + nseq) of the call;
-// items(i) is the number of work items of sequence g0 + i.  Returns the sum
-// of the items (which the caller has checked to be below 2^31).
+// items(i) is the number of work items of sequence g0 + i.  Returns the sum of
+// the items; the table holds it in 32 bits, which is enough for any grid that a
+// launch accepts (below kMaxGroups workgroups).
 template <int N, typename Items>
 int64_t fill_seqs(dv::SeqTable<N>* s, const std::vector<int32_t>& t0,
                   const std::vector<int32_t>& n, int64_t g0, int nseq, Items items) {
@@ -203,11 +209,6 @@ int64_t fill_seqs(dv::SeqTable<N>* s, const std::vector<int32_t>& t0,
   }
   s->tok[N] = (int32_t)tok;
   return total;
-}
-
-// Blocks of the table that hold tokens [t0, t0 + n).
-int64_t blocks_of(const View& v, int64_t t0, int64_t n) {
-  return n > 0 ? (t0 + n + v.bs - 1) / v.bs - t0 / v.bs : 0;
 }
 
 // The owner map of a whole call of at most N sequences in one launch.
@@ -263,12 +264,13 @@ int build_owner_map(const View& v, const std::vector<int32_t>& t0, const std::ve
   return DV_OK;
 }
 
-// The smallest power of two of tiles per workgroup for which the launch's
-// workgroups per slab, fill(steps) of them, have fewer than 2^32 lanes.
+// The smallest power of two of tiles per workgroup for which the launch has
+// fewer than kMaxGroups workgroups per slab, fill(steps) of them (at least one
+// for each of its sequences, of which there are fewer than that).
 template <typename Fill>
 int32_t steps_for(Fill fill, int64_t* tiles) {
   int32_t steps = 1;
-  while ((*tiles = fill(steps)) >= (1ll << 32) / dv::kThreads) steps *= 2;
+  while ((*tiles = fill(steps)) >= dv::kMaxGroups) steps *= 2;
   return steps;
 }
 
@@ -513,6 +515,38 @@ int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
   return DV_OK;
 }
 
+// The largest calls the boundary takes, as the header counts them: over any 64
+// consecutive sequences (from the first, the 65th, ...) fewer than 2^31 16-byte
+// units of one slab for runs of at most kSmallRunUnits, else fewer than 2^31
+// pieces: 512 units of a dense or split-key run, 64 tokens of a split-key one,
+// two heads of a paged block.  The pieces are those of no present kernel: the
+// limit is the caller's, whatever tiles a launch uses, and stays where it is.
+// Launches hold up to 256 sequences and count for themselves: rows and copies
+// below 2^31 units each (fill_rows; one token of 256 sequences is below 2^28),
+// paged tiles below kMaxGroups (steps_for), dense and split-key tiles likewise,
+// or else 64 sequences to a launch, which dv_kernels.hip refuses where even those
+// are too many for a grid.
+bool within_limits(const View& v, const std::vector<int32_t>& t0, const std::vector<int32_t>& n,
+                   bool small) {
+  constexpr int64_t kPieceUnits = 512, kPieceTokens = 64, kPieceHeads = 2;
+  for (int64_t g0 = 0; g0 < v.B; g0 += kSeqPerLaunch) {
+    int64_t pieces = 0, by_token = 0;
+    for (int64_t b = g0; b < std::min<int64_t>(g0 + kSeqPerLaunch, v.B); ++b) {
+      const int64_t k = n[b];
+      if (small)
+        pieces += k * v.H * v.du;
+      else if (v.kind == DV_PAGED)
+        pieces += blocks_of(v, t0[b], k) * ((v.H + kPieceHeads - 1) / kPieceHeads);
+      else
+        pieces += v.H * ((k * v.du + kPieceUnits - 1) / kPieceUnits);
+      if (!small && v.kind == DV_DENSE_KSPLIT)
+        by_token += v.H * ((k + kPieceTokens - 1) / kPieceTokens);
+    }
+    if (std::max(pieces, by_token) >= (1ll << 31)) return false;
+  }
+  return true;
+}
+
 // Enqueue the pack (dir = kPack) or unpack of the validated ranges.  The wire
 // is at `wire`; per (layer, K|V) slab it holds N*H*du units.
 int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector<int32_t>& t0,
@@ -527,29 +561,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
   // flattened short-run kernel instead of the tiled ones.
   const bool small = !single && (int64_t)max_n * v.du <= kSmallRunUnits;
 
-  // Every launch group's grid, checked before anything is enqueued so that a
-  // refusal leaves the stream untouched.  Single tokens need no check: at
-  // most 64 * heads * du < 2^26 units per launch.
-  if (!single) {
-    const int64_t ngrp = (v.H + dv::kPagedHeads - 1) / dv::kPagedHeads;
-    for (int64_t g0 = 0; g0 < v.B; g0 += kSeqPerLaunch) {
-      const int64_t g1 = std::min<int64_t>(g0 + kSeqPerLaunch, v.B);
-      int64_t grid = 0, ktiles = 0;
-      for (int64_t b = g0; b < g1; ++b) {
-        const int64_t a = t0[b], k = n[b];
-        if (k == 0) continue;
-        if (small)
-          grid += k * v.H * v.du;
-        else if (v.kind == DV_PAGED)
-          grid += ((a + k + v.bs - 1) / v.bs - a / v.bs) * ngrp;
-        else
-          grid += v.H * ((k * v.du + dv::kDenseTile - 1) / dv::kDenseTile);
-        ktiles += v.H * ((k + dv::kKsplitTile - 1) / dv::kKsplitTile);
-      }
-      if (!small && v.kind == DV_DENSE_KSPLIT) grid = std::max(grid, ktiles);
-      if (grid >= (1ll << 31)) return DV_ERR_UNSUPPORTED;
-    }
-  }
+  if (!single && !within_limits(v, t0, n, small)) return DV_ERR_UNSUPPORTED;
 
   bool flat = single || small;  // the short-run kernel
   if (v.kind == DV_PAGED && !single && !small) {
@@ -596,7 +608,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
            (dir == dv::kPack || w_slab * 2 * nl * v.du <= 25'000'000);
     if (!flat)
       return v.B > kSeqPerLaunch && N < (1ll << 31) &&
-                     (tiles + v.B) * v.H < (1ll << 32) / dv::kThreads
+                     (tiles + v.B) * v.H < dv::kMaxGroups
                  ? run_split<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
                  : run_split<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
   }
@@ -627,7 +639,7 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
   if (flat)
     return v.B > kSeqPerLaunch ? run_rows<dv::kSeqMany>(dir, v, l0, nl, t0, n, w_slab, wire, st)
                                : run_rows<kSeqPerLaunch>(dir, v, l0, nl, t0, n, w_slab, wire, st);
-  return v.B > kSeqPerLaunch && N < (1ll << 31) && dense_tiles < (1ll << 32) / dv::kThreads
+  return v.B > kSeqPerLaunch && N < (1ll << 31) && dense_tiles < dv::kMaxGroups
              ? run_dense<dv::kSeqMany>(dir, v, l0, nl, t0, n, eighths, w_slab, wire, st)
              : run_dense<kSeqPerLaunch>(dir, v, l0, nl, t0, n, eighths, w_slab, wire, st);
 }

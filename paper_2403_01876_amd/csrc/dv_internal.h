@@ -14,6 +14,10 @@ namespace dv {
 constexpr int kSeqPerLaunch = 64;
 constexpr int kThreads = 256;
 
+// Workgroups in x that a launch has fewer than: a grid's lanes are counted in 32
+// bits.
+constexpr int64_t kMaxGroups = (1ll << 32) / kThreads;
+
 enum Dir : int { kPack = 0, kUnpack = 1 };
 
 // Division by a launch constant d >= 1, exact for 0 <= n < 2^31: with l =
@@ -245,7 +249,6 @@ struct CopyArgs {
 };
 constexpr int kCopyUnroll = 1;
 
-constexpr int kKsplitTile = 64;   // the grid-size rule of the host counts 64-token tiles
 constexpr int kKsplitMaxDu = 32;
 
 // Launchers (dv_kernels.hip).  Each returns the hipError_t of its launch.
@@ -286,10 +289,6 @@ constexpr int kDenseTile = kThreads * kDenseUnroll;
 // 16-byte units per paged tile: two per lane, 8 KB of one pool slab.
 constexpr int kPagedUnroll = 2;
 constexpr int kPagedTile = kThreads * kPagedUnroll;
-
-// The pool-order and grid-size rules of the host count tiles of two heads of
-// one block.
-constexpr int kPagedHeads = 2;
 
 // Pool-order scatters deal their (tile, slab) grid to the 8 XCDs in chunks of
 // this many consecutive tiles (8 pool blocks of one slab at 8 heads; 256 KB for

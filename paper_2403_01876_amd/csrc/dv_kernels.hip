@@ -763,10 +763,12 @@ __global__ void __launch_bounds__(kThreads) copy_kernel(CopyArgs<N> a) {
 namespace {
 
 // Launch with the runtime's own status for this launch (a stale error left by
-// an unrelated earlier call is not picked up, unlike hipGetLastError).
+// an unrelated earlier call is not picked up, unlike hipGetLastError).  A grid too
+// wide for one is refused here as the runtime would refuse it.
 template <typename Args>
 hipError_t launch(const void* fn, dim3 grid, const Args& a, hipStream_t s, size_t lds = 0) {
   if (grid.x == 0 || grid.y == 0) return hipSuccess;
+  if (grid.x >= kMaxGroups) return hipErrorInvalidConfiguration;
   void* args[] = {const_cast<Args*>(&a)};
   return hipLaunchKernel(fn, grid, dim3(kThreads), args, lds, s);
 }

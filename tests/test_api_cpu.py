@@ -504,7 +504,7 @@ def test_extent_limits_at_and_past_the_boundary():
     assert sized(paged(1 << 20), 1 << 24) == (0, 2 * 16 << 24)
     assert sized(paged((1 << 20) + 1), 1)[0] == U
     # one head of a paged block: block_size * head_dim * elem_bytes = 2^33
-    # bytes (2^29 units; the paged kernel counts two heads' units in int32)
+    # bytes (2^29 units: a head's capacity and one block past it, in int32)
     # (within the capacity limits above only for head_dim * elem_bytes >= 2^9)
     blk = lambda bs: dv.Cache(dv.DV_PAGED, 1, 1, 512, 1, [FAKE], block_size=bs,  # noqa: E731
                               num_blocks=4, max_blocks=1, block_tables=[FAKE])

@@ -12,7 +12,7 @@ from paper_2403_01876_amd import dv
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-CACHE, WIRE, TABLE, OWNER = 1 << 44, 1 << 47, 1 << 46, 1 << 42
+CACHE, WIRE, TABLE, OWNER = 1 << 50, 1 << 52, 1 << 54, 1 << 55
 
 
 @pytest.fixture(scope="module")
@@ -158,3 +158,56 @@ def test_dense_runs_that_fill_tiles_badly_go_by_rows(lib, du, L, line):
             "rows" if 100 * n.sum() * du < 45 * full else "dense"), percent
     n = np.where(np.arange(B) % 10, 1, tile)  # mostly empty tiles
     assert kernels(call(lib, "in", c, z, z + n)) == ["rows"]
+
+
+def test_refusals_count_the_header_s_pieces(lib):
+    """Over descriptors near the limit: refused exactly where 64 consecutive
+    sequences hold 2^31 pieces, counted as the header counts them, and before
+    anything is launched; what is launched fits 32 bits."""
+    r = np.random.default_rng(11)
+    seen = {True: 0, False: 0}
+    for i in range(3000):
+        kind = int(r.integers(0, 3))
+        du = int(2 ** r.integers(0, 6))
+        H = int(2 ** (r.uniform(17, 20) - np.log2(du)))
+        B = int(r.choice([1, 64, 65, 130, 300]))
+        n = np.minimum(r.integers(1, int(2 ** r.uniform(2, 16)) + 1, size=B), 1 << 16)
+        n[r.random(B) < 0.2] = 0
+        n[B // 2] = max(2, n[B // 2])
+        t0 = r.integers(0, 20, size=B)
+        bs = int(2 ** r.integers(0, 8))
+        S = int((t0 + n).max())
+        maxb = -(-S // bs)
+        if kind == 0:
+            c = dense(1, H, 8 * du, 2, B, S)
+        elif kind == 1:
+            c = paged(1, H, 8 * du, 2, B, bs, 1 << 20, maxb)
+        else:
+            c = dense(1, H, 8 * du, 2, B, S, dv.DV_DENSE_KSPLIT)
+        if dv.lib.dv_cache_bytes(c.ref, None) != dv.DV_OK:
+            continue
+        small = n.max() * du <= 256
+
+        def pieces(k, first):
+            if small:
+                return k * H * du
+            if kind == 1:
+                return ((first + k + bs - 1) // bs - first // bs) * ((H + 1) // 2) if k else 0
+            return H * (-(-k * du // 512))
+
+        refused = False
+        for g in range(0, B, 64):
+            k, first = n[g:g + 64].astype(object), t0[g:g + 64].astype(object)
+            most = sum(pieces(a, b) for a, b in zip(k, first))
+            if kind == 2 and not small:
+                most = max(most, sum(H * (-(-a // 64)) for a in k))
+            refused = refused or most >= 1 << 31
+        seen[refused] += 1
+        for name in ("out", "in"):
+            ran = call(lib, name, c, t0, t0 + n, dv.DV_ERR_UNSUPPORTED if refused else dv.DV_OK)
+            assert bool(ran) == (not refused)
+            for kernel, f in ran:
+                assert 0 < f.get("units", 1) < 1 << 31 and 0 < f.get("tiles", 1) < 3 << 30, (kernel, f)
+                if kernel in ("table", "pool"):
+                    assert f["tiles"] < 1 << 24
+    assert min(seen.values()) > 100, seen
