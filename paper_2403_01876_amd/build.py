@@ -25,12 +25,12 @@ def _run(cmd):
     subprocess.run(cmd, check=True)
 
 
-def build_libdv(out: str = LIBDV) -> str:
+def build_libdv(out: str = LIBDV, flags=()) -> str:
     srcs = [os.path.join(PKG, "csrc", f) for f in ("dv_kernels.hip", "dv_api.cpp",
                                                     "dv_swapper.cpp", "dv_streamer.cpp",
                                                     "dv_noalloc.hip")]
     tmp = out + ".tmp"
-    _run([HIPCC, *HIP_FLAGS, "-x", "hip", *srcs, "-o", tmp])
+    _run([HIPCC, *HIP_FLAGS, *flags, "-x", "hip", *srcs, "-o", tmp])
     os.replace(tmp, out)
     return out
 

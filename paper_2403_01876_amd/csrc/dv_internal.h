@@ -15,8 +15,13 @@ constexpr int kSeqPerLaunch = 64;
 constexpr int kThreads = 256;
 
 // Workgroups in x that a launch has fewer than: a grid's lanes are counted in 32
-// bits.
+// bits.  (A test's build sets a small limit, so that small shapes take the paths
+// of slabs of 128 GB; more than the sequences of a call.)
+#ifdef DV_MAX_GROUPS
+constexpr int64_t kMaxGroups = DV_MAX_GROUPS;
+#else
 constexpr int64_t kMaxGroups = (1ll << 32) / kThreads;
+#endif
 
 enum Dir : int { kPack = 0, kUnpack = 1 };
 

@@ -162,7 +162,7 @@ def test_unit_numbers_past_2_31():
     the buffers' other bytes are never touched."""
     free, _ = torch.cuda.mem_get_info()
     if free < 200 << 30:
-        pytest.skip("needs 140 GiB of device memory")
+        pytest.skip("needs 200 GiB of free device memory")
     L, H, D, E, bs, blocks = 1, 512, 512, 2, 256, 256
     n = bs * blocks
     slab = H * n * D * E  # bytes, 2^35
