@@ -344,6 +344,7 @@ static void case_swap(hipStream_t st, const int32_t* t0, const int32_t* t1, cons
   /* back into a cleared slot */
   uint8_t* dexp = host_const(dbytes, 0);
   HIPCHECK(hipMemset(slot, 0, dbytes));
+  HIPCHECK(hipDeviceSynchronize()); /* it runs on the null stream, which `st` does not wait for */
   EXPECT(dvo_copy_ranges(&oh, hexp, &od, dexp, 0, L, t0, t1) == DVO_OK, "oracle copy in");
   EXPECT(dv_swap_in(&hst, 0, &dev, 0, 0, L, t0, t1, st) == DV_OK, "dv_swap_in");
   HIPCHECK(hipStreamSynchronize(st));
@@ -374,6 +375,7 @@ static void case_scheduler(hipStream_t st) {
     HIPCHECK(hipMalloc(&slots[i], bytes));
     HIPCHECK(hipMemset(slots[i], 0, bytes));
   }
+  HIPCHECK(hipDeviceSynchronize()); /* as above, for the scheduler's streams */
   for (int x = 0; x < M; ++x) {
     exp[x] = host_filled(bytes, 200 + x);
     HIPCHECK(hipHostMalloc(&mirrors[x], bytes, hipHostMallocDefault));
