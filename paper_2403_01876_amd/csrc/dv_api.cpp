@@ -234,10 +234,11 @@ int build_owner_map(const View& v, const std::vector<int32_t>& t0, const std::ve
                     hipStream_t st) {
   int64_t chunks = 0;
   for (int64_t b = 0; b < v.B; ++b) chunks += (blocks_of(v, t0[b], n[b]) + 63) / 64;
-  if (v.B <= kSeqPerLaunch && chunks <= dv::kOwnerChunks)
-    return hip_fail(launch_owner_map<kSeqPerLaunch>(v, t0, n, st), "owner map launch");
-  if (v.B > kSeqPerLaunch && v.B <= dv::kSeqMany && chunks <= dv::kOwnerChunksMany)
-    return hip_fail(launch_owner_map<dv::kSeqMany>(v, t0, n, st), "owner map launch");
+  const int64_t launches = 1 + (v.B + kSeqPerLaunch - 1) / kSeqPerLaunch;
+  if (v.B <= dv::kSeqMany && chunks <= dv::kOwnerChunks * launches)
+    return hip_fail(v.B <= kSeqPerLaunch ? launch_owner_map<kSeqPerLaunch>(v, t0, n, st)
+                                         : launch_owner_map<dv::kSeqMany>(v, t0, n, st),
+                    "owner map launch");
   dv::OwnerArgs o;
   memset(&o, 0, sizeof o);
   o.owner = v.owner;

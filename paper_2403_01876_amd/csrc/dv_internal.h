@@ -159,13 +159,16 @@ struct OwnerMapArgs {
 };
 constexpr int kOwnerSpan = 512;
 constexpr int kOwnerThreads = 1024;
-// Chunks up to which one launch is used.  Every workgroup reads every entry, so
-// the launches it saves are paid for in large pools.  A pool-order stream-in of
-// one layer, one head, graph-replayed, with a launch to clear and one per 64
-// sequences against one for all: 544 blocks (32 chunks) 6.7 and 5.7 us, 4600
-// blocks (72) 17.6 and 16.5, 19200 blocks (320) 55.2 and 57.3; 200 sequences,
-// 4000 blocks (200) 21.3 and 17.1, 20000 blocks (400) 63.7 and 62.5.
-constexpr int kOwnerChunks = 192, kOwnerChunksMany = 512;
+// One launch is used while its chunks are at most this many for each launch that
+// the other way takes, one to clear and one per 64 sequences: every workgroup
+// reads every entry, so the launches saved are paid for in large pools.  A
+// pool-order stream-in of one layer, one head, graph-replayed, several launches
+// and one: up to 64 sequences (two launches) 544 blocks (32 chunks) 6.7 and 5.7
+// us, 4600 blocks (72) 17.6 and 16.5, 19200 blocks (320) 55.2 and 57.3; 100
+// sequences (three) 400 chunks 12.1 and 14.8; 150 (four) 450 chunks 14.5 and 15.7;
+// 200 (five) 400 chunks 15.7 and 15.0; 220 (five) 440 chunks 16.6 and 15.7; 256
+// (five) 512 chunks 16.6 and 16.8, 768 chunks 20.5 and 24.9.
+constexpr int kOwnerChunks = 96;
 
 // Short runs (decode-step increments of one or a few tokens per sequence):
 // the 16-byte units of a slab in wire order, (sequence, head, token, group),

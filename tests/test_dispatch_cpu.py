@@ -211,3 +211,19 @@ def test_refusals_count_the_header_s_pieces(lib):
                 if kernel in ("table", "pool"):
                     assert f["tiles"] < 1 << 24
     assert min(seen.values()) > 100, seen
+
+
+@pytest.mark.parametrize("B, most", [(1, 192), (64, 192), (65, 288), (128, 288), (150, 384), (256, 480)])
+def test_owner_map_in_one_launch_up_to_96_chunks_for_each_it_saves(lib, B, most):
+    """A chunk is 64 table entries of one sequence."""
+    z = np.zeros(B, np.int32)
+    for chunks in (most, most + 1):
+        blocks = np.full(B, chunks // B) * 64  # of 16 tokens
+        blocks[:chunks % B] += 64
+        blocks = np.maximum(blocks - 63, 1)  # the last chunk of each holds one entry
+        c = paged(1, 1, 512, 2, B, 16, int(blocks.sum()), int(blocks.max()))
+        ran = call(lib, "in", c, z, z + 16 * blocks)
+        if chunks == most:
+            assert kernels(ran) == ["owner-map", "pool"] and ran[0][1]["chunks"] == chunks
+        else:
+            assert kernels(ran) == ["owner-clear"] + ["owner-build"] * (-(-B // 64)) + ["pool"]

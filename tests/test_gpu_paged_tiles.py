@@ -92,11 +92,12 @@ def test_paged_tiles(oracle_lib, shape, unmapped):
 
 
 @pytest.mark.parametrize("B, blocks", [(1, 1), (3, 64), (5, 65), (1, 192 * 64), (1, 192 * 64 + 1),
-                                       (64, 193), (65, 30), (256, 128), (256, 129)])
+                                       (64, 193), (65, 30), (256, 128), (256, 129), (72, 256),
+                                       (73, 256), (240, 128), (241, 128)])
 def test_owner_map_one_launch_or_several(B, blocks):
     """The owner map of pools whose tables have chunks of 64 entries on either
     side of the counts up to which one launch builds it (192 for at most 64
-    sequences, 512 for more), with unmapped entries, ranges that start in
+    sequences, 288 up to 128, 480 from 193 on), with unmapped entries, ranges that start in
     later blocks and blocks that no entry names."""
     bs, H, D = 4, 1, 8
     r = np.random.default_rng(B * 1000 + blocks)
