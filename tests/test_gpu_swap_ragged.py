@@ -1,7 +1,8 @@
 """Swaps of ragged wide rows (one 3-D copy per sequence on the DMA engines),
 byte for byte against the oracle: capacities that differ, ranges that start
 anywhere, sequences without tokens, layer sub-ranges, odd head sizes, and the
-same calls replayed from a HIP graph; and slabs of 2 GB, which keep 2-D copies."""
+same calls replayed from a HIP graph; a cache whose copies span more than 4 GB;
+and slabs of 2 GB, which keep 2-D copies."""
 import numpy as np
 import pytest
 
@@ -86,6 +87,39 @@ def test_slabs_of_two_gigabytes():
         assert torch.equal(a[:, s, :, t0[s]:t1[s]], b[:, s, :, t0[s]:t1[s]])
         b[:, s, :, t0[s]:t1[s]] = 0
     assert not bool(back.any()), "bytes outside the ranges changed"
+
+
+def test_ragged_wide_rows_of_a_large_cache():
+    """Slabs of 302 and 283 MB, 4.8 and 4.5 GB of cache and mirror with pitches of
+    their own: every 3-D copy spans more than 4 GB.  The ranges arrive, in the
+    mirror and back in a second slot, and nothing beside them changes."""
+    L, H, D, E, B, S, M = 8, 72, 128, 2, 8, 2048, 1920
+    w = D * E // 8  # int64 words per token
+    assert 2 * L * B * H * min(S, M) * D * E > 1 << 32
+    slot = torch.empty(2 * L * B * H * S * w, dtype=torch.int64, device=G.DEV).random_()
+    back = torch.full_like(slot, 0x5A5A5A5A5A5A5A5A)
+    mirror = torch.full((2 * L * B * H * M * w,), 0x3C3C3C3C3C3C3C3C, dtype=torch.int64,
+                        pin_memory=True)
+    d = dv.Cache(dv.DV_DENSE, L, H, D, B, [slot, back], max_seq=S)
+    h = dv.Cache(dv.DV_DENSE, L, H, D, B, [mirror], max_seq=M, mem=dv.DV_MEM_HOST_PINNED)
+    t0 = np.array([0, 7, 300, 1919, 0, 64, 900, 0], np.int32)
+    t1 = np.array([1920, 411, 1501, 1920, 0, 700, 1900, 1], np.int32)
+    l0 = 1  # the last layers
+    dv.dv_swap_out(d, 0, h, 0, l0, L, t0, t1)
+    dv.dv_swap_in(h, 0, d, 1, l0, L, t0, t1)
+    torch.cuda.synchronize()
+    host = mirror.to(G.DEV).view(2 * L, B, H, M, w)
+    a, b = (x.view(2 * L, B, H, S, w) for x in (slot, back))
+    for s in range(B):
+        at = slice(int(t0[s]), int(t1[s]))
+        assert torch.equal(host[2 * l0:, s, :, at], a[2 * l0:, s, :, at]), f"mirror, sequence {s}"
+        assert torch.equal(b[2 * l0:, s, :, at], a[2 * l0:, s, :, at]), f"slot, sequence {s}"
+        host[2 * l0:, s, :, at] = 0x3C3C3C3C3C3C3C3C
+        b[2 * l0:, s, :, at] = 0x5A5A5A5A5A5A5A5A
+    assert bool((host == 0x3C3C3C3C3C3C3C3C).all()), "mirror bytes outside the ranges changed"
+    assert bool((back == 0x5A5A5A5A5A5A5A5A).all()), "slot bytes outside the ranges changed"
+    del slot, back, mirror, host
+    torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("B, hi", [(3, 9), (64, 1), (65, 5), (200, 1), (256, 3), (300, 4)])
