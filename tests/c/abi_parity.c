@@ -446,7 +446,7 @@ int main(void) {
     case_stream(st, DV_DENSE_KSPLIT, 3, 5, 64, 6, 300, 0, 3, t0, t1, 12, "split key");
   }
   {
-    /* 70 sequences: two launch groups */
+    /* 70 sequences: the launches for more than 64 */
     int32_t t0[70], t1[70];
     for (int b = 0; b < 70; ++b) {
       t0[b] = (int32_t)lcg_below(40);

@@ -573,9 +573,9 @@ def test_binding_refuses_range_arrays_shorter_than_the_batch():
 
 
 def test_oversized_later_launch_group_is_refused_before_any_launch():
-    """With more than 64 sequences a call runs in launch groups.  When only a
-    later group's grid passes 2^31 units or tiles the call must still refuse
-    before enqueuing the earlier groups: here it returns
+    """The size limit counts 64 consecutive sequences at a time.  When only a
+    later 64 pass 2^31 pieces the call must still refuse before enqueuing
+    anything: here it returns
     DV_ERR_UNSUPPORTED, where a launch attempt (no GPU in this process)
     would have returned DV_ERR_HIP."""
     U = dv.DV_ERR_UNSUPPORTED
@@ -593,10 +593,9 @@ def test_oversized_later_launch_group_is_refused_before_any_launch():
 
     # short runs: 64 sequences x 32 tokens x 2^20 heads = 2^31 units
     both_directions(dense(L=1, H=H, D=8, B=B, S=64), lens(1, 32))
-    # dense tiles: 64 x 2^20 heads x 32 tiles of 512 units
+    # dense: 64 x 2^20 heads x 32 pieces of 512 units
     both_directions(dense(L=1, H=H, D=8, B=B, S=1 << 14), lens(1, 1 << 14))
-    # split key: the key slabs' 64-token tiles pass 2^31 (the value slabs'
-    # 512-unit tiles do not)
+    # split key: the pieces of 64 tokens pass 2^31 (those of 512 units do not)
     both_directions(dense(L=1, H=H, D=8, B=B, S=2048, kind=dv.DV_DENSE_KSPLIT),
                     lens(1, 2048))
     # paged: 64 x 64 blocks x 2^19 head pairs
@@ -608,5 +607,5 @@ def test_oversized_later_launch_group_is_refused_before_any_launch():
     host_c = dense(L=1, H=H, D=8, B=B, S=64, bases=(1 << 44,), mem=dv.DV_MEM_HOST_PINNED)
     assert dv.dv_swap_out(dev_c, 0, host_c, 0, 0, 1, z, lens(1, 32), check=False) == U
     assert dv.dv_swap_in(host_c, 0, dev_c, 0, 0, 1, z, lens(1, 32), check=False) == U
-    # just below the limit the sizing still works: 31 tokens in the later group
+    # just below the limit the sizing still works: 31 tokens in the later 64
     assert dv.dv_packed_bytes(dense(L=1, H=H, D=8, B=B, S=64), 0, 1, z, lens(1, 31)) > 0

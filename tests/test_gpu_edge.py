@@ -59,8 +59,9 @@ def test_many_heads_and_long_runs(oracle_lib):
 
 
 def test_two_hundred_sequences_with_an_empty_group(oracle_lib):
-    """Sequences 64..127 stream nothing: their launch is skipped, later groups
-    still land at the right wire offsets."""
+    """Sequences 64..127 stream nothing: later ones still land at the right wire
+    offsets.  So do those of the third launch where sequences 256..511, the
+    second launch of 256, stream nothing and it is skipped."""
     B = 200
     r = np.random.default_rng(3)
     t0 = r.integers(0, 20, size=B).astype(np.int32)
@@ -72,6 +73,13 @@ def test_two_hundred_sequences_with_an_empty_group(oracle_lib):
     e = (p + 1).astype(np.int32)
     e[64:128] = p[64:128]
     dense_roundtrip(oracle_lib, 2, 2, 64, B, 40, 2, 1, 2, p, e)
+    # runs that fill tiles, an empty launch between two others
+    B = 600
+    t0 = r.integers(0, 20, size=B).astype(np.int32)
+    t1 = (t0 + r.integers(61, 65, size=B)).astype(np.int32)
+    t1[256:512] = t0[256:512]
+    for kind in (dv.DV_DENSE, dv.DV_DENSE_KSPLIT):
+        dense_roundtrip(oracle_lib, 2, 2, 64, B, 88, 2, 0, 2, t0, t1, kind=kind)
 
 
 def test_ranges_at_capacity_end(oracle_lib):

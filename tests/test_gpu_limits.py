@@ -152,7 +152,7 @@ def test_token_capacity_and_size_limits(oracle_lib):
 
 def test_split_key_at_capacity(oracle_lib):
     """Split key with 32 groups per token (the most) and max_seq = 2**24:
-    group g of a head sits g * 2**24 units after group 0; ragged 64-token tiles."""
+    group g of a head sits g * 2**24 units after group 0; a ragged last tile."""
     L, H, D, B, S = 1, 2, 256, 1, 1 << 24
     t0 = np.array([S - 100], np.int32)
     t1 = np.array([S], np.int32)

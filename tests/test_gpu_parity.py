@@ -1,8 +1,8 @@
 """HIP path vs the CPU oracle, byte for byte, on randomized small shapes.
 
-Shapes span several tiles per run (runs longer than one workgroup's 2048
+Shapes span several tiles per run (runs longer than one workgroup's 512
 16-byte units), ragged tails, empty ranges, sub-ranges of layers, more than
-64 sequences (several launches), 1/2/4-byte elements and head_dim 16..256.
+64 sequences, 1/2/4-byte elements and head_dim 16..256.
 Every call goes through the C ABI (paper_2403_01876_amd.dv).
 """
 import numpy as np
@@ -267,9 +267,8 @@ def test_paged_scatter_pool_order_threshold(oracle_lib, written):
 
 @pytest.mark.parametrize("B", [130, 256, 257])
 def test_paged_scatter_pool_order_many_sequences(oracle_lib, B):
-    """Pool order over several launch groups: one owner map for the whole
-    call (sequence indices past 64 included) and one launch over the pool,
-    up to 256 sequences; 257 sequences scatter in table order and leave the
+    """Pool order past 64 sequences: one owner map for the whole call (sequence
+    indices past 64 included) and one launch over the pool, up to 256 sequences; 257 sequences scatter in table order and leave the
     workspace untouched.  Against the oracle over the whole pool, with
     sequences of every length including empty ones."""
     r = np.random.default_rng(4000 + B)
@@ -401,9 +400,8 @@ def test_ksplit_pack_unpack(oracle_lib, seed):
 
 @pytest.mark.parametrize("D", [8, 32, 64, 128, 192, 256])
 def test_ksplit_group_counts(oracle_lib, D):
-    """Every count of 16-byte groups per token the split-key kernel takes in
-    one or several 4-unit passes (1 .. 32 groups; 16 and more get the padded
-    LDS request), with ragged 64-token tiles."""
+    """Counts of 16-byte groups per token from 1 to 32 (tiles of two units per
+    lane, of six for 24 groups), with ragged last tiles."""
     r = np.random.default_rng(D)
     L, H, B, S, E = 2, 3, 4, 150, 2
     lay = oracle.Layout(oracle.KSPLIT, L, H, D, B, seq_cap=S, elem_bytes=E)

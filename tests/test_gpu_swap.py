@@ -67,7 +67,7 @@ def test_swap_out_in_matches_oracle(oracle_lib, seed):
 
 @pytest.mark.parametrize("E", [1, 4])
 def test_swap_kernel_engine_many_sequences_other_element_sizes(oracle_lib, E):
-    """The copy-kernel engine with 100 sequences (two launch groups), 1- and
+    """The copy-kernel engine with 100 sequences (up to 256 a launch), 1- and
     4-byte elements and a layer sub-range, both directions."""
     L, H, B = 3, 2, 100
     D = 64 if E == 4 else 128  # 256 or 128 bytes per token

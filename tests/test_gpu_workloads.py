@@ -319,35 +319,37 @@ def multi_token_case(oracle_lib, w, K):
 def test_multi_token_steps(oracle_lib, idx, K):
     """Decode steps that each add K tokens per sequence (speculative decoding
     accepting several tokens, or replication batched over K steps) on the
-    OPT-13B stage and the LLaMA-2-70B paged pool.  They go through the
-    short-run kernel: one unit per lane below 2^19 units a launch (OPT-13B
-    K = 2, 4; LLaMA K = 2), two units per lane from there on."""
+    OPT-13B stage and the LLaMA-2-70B paged pool.  Every sequence has as many
+    tokens as the next, so they go through the short-run kernel's even form:
+    one unit per lane at every size (2^18 units, from where ragged runs take
+    two, lie between OPT-13B K = 2 and the others)."""
     w = synth.make_workload(idx)
     n = multi_token_case(oracle_lib, w, K)
     units = n // 16
-    assert (units >= 1 << 19) == ((idx, K) not in ((1, 2), (1, 4), (4, 2)))
+    assert (units >= 1 << 18) == ((idx, K) != (1, 2))
     torch.cuda.empty_cache()
 
 
-def short_run_launch_units(kind, L, H, du, nt):
-    """Units of each launch the library makes for these token counts: one
-    launch per group of 64 sequences over all (layer, K|V) slabs; a split-key
-    cache makes two per group (keys, values), each over L slabs."""
-    per_slab = [int(np.sum(nt[g:g + 64])) * H * du for g in range(0, len(nt), 64)]
-    return [u * (L if kind == "ksplit" else 2 * L) for u in per_slab]
+def short_run_launch_units(L, H, du, nt):
+    """Units of each launch the library makes for these token counts, whatever
+    the layout: the sequences with tokens, 64 to a launch in calls of up to 64
+    sequences, else 256, over all (layer, K|V) slabs."""
+    active, most = nt[nt > 0], 64 if len(nt) <= 64 else 256
+    return [int(active[g:g + most].sum()) * H * du * 2 * L for g in range(0, len(active), most)]
 
 
 @pytest.mark.parametrize("kind", ["dense", "paged", "ksplit"])
 @pytest.mark.parametrize("size", ["below", "above", "two-groups"])
 def test_short_runs_random_shapes_across_unroll_threshold(oracle_lib, kind, size):
     """The short-run kernel on random shapes whose launches fall on either
-    side of 2^19 units (one unit per lane below, two from there on), with
-    ragged runs of 0-16 tokens, sentinel receivers and, for "two-groups",
-    more than 64 sequences (two launch groups): stream-out and stream-in
-    against the oracle."""
+    side of 2^18 units (ragged runs take one unit per lane below, two from
+    there on; a split-key cache's go through LDS from there), with runs of
+    0-16 tokens, sentinel receivers and, for "two-groups", more than 256
+    sequences with tokens, the second launch past 2^18 units too: stream-out
+    and stream-in against the oracle."""
     r = np.random.default_rng(9100 + 10 * ["below", "above", "two-groups"].index(size)
                               + ["dense", "paged", "ksplit"].index(kind))
-    L, H, B = {"below": (1, 8, 37), "above": (4, 48, 64), "two-groups": (3, 48, 100)}[size]
+    L, H, B = {"below": (1, 8, 37), "above": (4, 48, 64), "two-groups": (3, 24, 340)}[size]
     D = int(r.choice([64, 128, 256]))
     E = 2
     du = D * E // 16
@@ -356,8 +358,10 @@ def test_short_runs_random_shapes_across_unroll_threshold(oracle_lib, kind, size
     nt = r.integers(0, kmax + 1, size=B)
     nt[int(r.integers(0, B))] = kmax  # at least one run of the longest length
     t1 = (t0 + nt).astype(np.int32)
-    units = short_run_launch_units(kind, L, H, du, nt)
-    assert (units[0] >= 1 << 19) == (size != "below"), units
+    units = short_run_launch_units(L, H, du, nt)
+    assert len(units) == (2 if size == "two-groups" else 1), units
+    assert all((u >= 1 << 18) == (size != "below") for u in units), units
+    assert nt[nt > 0].min() < nt.max()  # ragged
     cap = 40 + kmax
     if kind == "paged":
         bs = int(r.choice([4, 16]))

@@ -111,8 +111,8 @@ def test_noalloc_scatter_replayed_from_a_graph(B):
     """The callers it is for capture it: a gather and a dv_stream_in_noalloc
     scatter captured into a HIP graph and replayed three times, with eager
     work and a fresh sentinel pool between replays; every replay against the
-    oracle.  100 sequences take the pool-order launch over the whole call
-    (more than 64 sequences), 6 the scan-based one."""
+    oracle.  6 sequences take the launches whose lanes hold a sequence each,
+    100 those for up to 256 sequences."""
     orc = oracle.get()
     L, H, D, E, bs = 2, 4, 128, 2, 16
     r = np.random.default_rng(B)
