@@ -272,11 +272,12 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
     bool ok[kPagedUnroll];
 #pragma unroll
     for (int i = 0; i < kPagedUnroll; ++i) {
-      // In pool order a wave's units follow each other (2 KB written in order:
-      // 1801 us against 1835 with the waves' units interleaved, LLaMA-2-70B
-      // pool); in table order they interleave (1 % faster).
-      const uint32_t idx = POOL ? (threadIdx.x & ~63u) * kPagedUnroll + i * 64 + lane
-                                : i * kThreads + threadIdx.x;
+      // On the way in a wave's units follow each other (2 KB written in order:
+      // 1801 us against 1835 with the waves' units interleaved, LLaMA-2-70B pool
+      // in pool order; 1964 against 1981 in table order); on the way out they
+      // interleave (1 % faster).
+      const uint32_t idx = D == kUnpack ? (threadIdx.x & ~63u) * kPagedUnroll + i * 64 + lane
+                                        : i * kThreads + threadIdx.x;
       const bool second = by_wave && off0 + i * 64 + lane >= (uint32_t)a.s_blk;
       const uint32_t z = by_wave ? off0 + i * 64 + lane - (second ? (uint32_t)a.s_blk : 0) : r0 + idx;
       const uint32_t d = a.d_ub.div(z);
