@@ -1,7 +1,8 @@
 // Pack / unpack kernels for gfx950.  Pure data movement: every lane moves
 // 16-byte words with nontemporal global loads and stores (the data is
-// streamed once, so it should not displace L2/MALL contents), no arithmetic
-// touches the payload and no MFMA is involved.
+// streamed once, so it should not displace L2/MALL contents; only the swap
+// kernel's stores are ordinary ones), no arithmetic touches the payload and no
+// MFMA is involved.
 //
 // Work resolution: a launch covers at most 64 sequences, one per lane of a
 // wavefront, or 256, four per lane.  Their ranges travel by value in the kernel
@@ -145,7 +146,9 @@ __global__ void __launch_bounds__(kThreads) dense_runs_kernel(DenseRunArgs<N> a)
 // sequences of 128-4096 tokens, 2.77 GB): 2320 and 2350 us a gather and a
 // scatter, 2.4 TB/s; with tiles of 512 units across blocks 910 and 990 us, 6.1
 // and 5.6 TB/s.  Where a tile was whole before, the LLaMA-2-70B pool (eight
-// heads of a 2-byte cache, 5.54 GB): 1797 and 1801 us, 1841 and 1803 before.
+// heads of a 2-byte cache, 5.54 GB), nothing is gained in use: a gather and a
+// pool-order scatter after each other take 3635 us, 3643 before, within noise
+// (each replayed by itself 1784 and 1759 us, 1827 and 1776 before).
 //
 // ONE: a tile never leaves its block (the block is a multiple of the tile),
 // so block, table entry and sequence are uniform over the workgroup.  WIDE:
@@ -334,8 +337,8 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
       // One access in flight per wave: load, store, and the store's end before
       // the next load.  With the chip full of waves that is enough, and random
       // blocks are served better: gather and pool-order scatter of the
-      // LLaMA-2-70B pool 1797 and 1801 us; without the last wait 1850 and 1803,
-      // with two loads in flight 1885 and 1870.
+      // LLaMA-2-70B pool, replayed, 1784 and 1759 us; without the last wait 1839
+      // and 1780, with two loads in flight 1870 and 1850.
 #pragma unroll
       for (int i = 0; i < kPagedUnroll; ++i) {
         if (ok[i])
