@@ -486,14 +486,19 @@ int run_split(int dir, const View& v, int32_t l0, uint32_t nl, const std::vector
   if (v.S % 8 == 0) {  // then slabs, heads and groups are whole lines apart
     a.line0 = (int32_t)((reinterpret_cast<uintptr_t>(v.base) >> 4) & 7);
     a.line_mask = 7;
-  } else if (dir == dv::kUnpack && v.du >= dv::kSplitEightDu) {
-    const int64_t tile = dv::split_tile(v.du, 8);
-    int64_t tok = 0, tiles = 0;
+  } else if (dir == dv::kUnpack && units == 2 && v.du >= dv::kSplitEightDu &&
+             w_slab * 2 * nl >= dv::kSplitEightMin) {
+    // Eight units per lane save a ninth of the time that two take, but a run of
+    // several tiles loses three quarters of a small tile's time to its last one.
+    const int64_t small = dv::split_tile(v.du, 2), tile = dv::split_tile(v.du, 8);
+    int64_t tok = 0, smalls = 0, tiles = 0, several = 0;
     for (int32_t k : n) {
       tok += k;
+      smalls += (k + small - 1) / small;
       tiles += (k + tile - 1) / tile;
+      several += k > tile;
     }
-    if (3 * tok >= tiles * tile) units = 8;
+    if (3 * tok >= tiles * tile && 11 * smalls > 75 * several) units = 8;
   }
   a.tile = dv::split_tile(v.du, units);
   a.d_du = dv::fast_div((uint32_t)v.du);
@@ -595,18 +600,24 @@ int run_stream(int dir, const View& v, int32_t l0, int32_t l1, const std::vector
   if (v.kind == DV_DENSE_KSPLIT && !flat) {
     // Where tiles of one head each would be less than three quarters full, rows
     // across heads and sequences: always on the way out (up to 22 tokens of 16
-    // groups 44 us by tiles, 32 by rows), but on the way in only up to 400 MB over
-    // the groups per token.  A workgroup's rows of a key slab are written in
-    // pieces of lines, the shorter the wider the tokens.  Tiles and rows, 64
-    // sequences: 32 groups, 10-20 tokens, 10 MB 7.4 and 6.6 us, 20 MB 12.2 and
-    // 12.8, 101 MB 48 and 59, 391 MB 184 and 230; 16 groups, 10-60 tokens, 10 MB
-    // 6.1 and 5.6, 24 MB 11.7 and 12.4, 379 MB 147 and 181; 8 groups, 23-47
-    // tokens, 35 MB 16.3 and 15.6, 106 MB 43.8 and 45.2, 393 MB 156 and 177.
+    // groups 44 us by tiles, 32 by rows), on the way in up to 1.6 GB over the
+    // groups per token.  A workgroup's rows of a key slab are written in pieces of
+    // lines, the shorter the wider the tokens, and past the caches those cost what
+    // whole lines do.  Tiles and rows, 64 sequences: 32 groups, 10-20 tokens, 10 MB
+    // 7.4 and 6.6 us, 20 MB 12.2 and 12.8, 60 MB 30.7 and 35.6, 391 MB 184 and 230;
+    // 16 groups, 10-60 tokens, 24 MB 11.7 and 12.4, 96 MB 40.8 and 45.8, 379 MB 147
+    // and 181, 33 tokens, 110 MB 52.8 and 44.6; 10 groups, 62 tokens, 77 MB 37.3 and
+    // 32.5; 8 groups, 23-47 tokens, 106 MB 43.8 and 45.2, 393 MB 156 and 177; 3
+    // groups, 102 tokens, 366 MB 135 and 123.  Emptier tiles lose again, 400 MB: 8
+    // groups, 37 % full 203 and 191, 44 % 174 and 185; 12 groups, 33 % 240 and 232,
+    // 41 % 206 and 215; 16 groups, 29 % 256 and 248, 41 % 198 and 229; 24 groups,
+    // 17 % 287 and 252, 25 % 212 and 230; 32 groups, 32 % 246 and 277.
     const int64_t tile = dv::split_tile(v.du, dv::split_units(v.du));
     int64_t tiles = 0;
     for (int64_t b = 0; b < v.B; ++b) tiles += (n[b] + tile - 1) / tile;
     flat = 4 * N < 3 * tiles * tile && w_slab < (1ll << 31) &&
-           (dir == dv::kPack || w_slab * 2 * nl * v.du <= 25'000'000);
+           (dir == dv::kPack || v.du < 8 || w_slab * 2 * nl * v.du <= 100'000'000 ||
+            80 * N < (40 - v.du) * tiles * tile);
     if (!flat)
       return v.B > kSeqPerLaunch && N < (1ll << 31) &&
                      (tiles + v.B) * v.H < dv::kMaxGroups

@@ -227,15 +227,15 @@ struct SplitArgs {
 // with six, 261 and 283 with two, 263 and 281 with four.
 inline int32_t split_tile(int64_t du, int units) { return (int32_t)(units * kThreads / du & ~7); }
 inline int split_units(int64_t du) { return 5 * split_tile(du, 2) * du >= 4 * 2 * kThreads ? 2 : 6; }
-// Eight for a stream-in from this many groups per token on where max_seq is not
-// whole lines, so that every tile ends inside some, if its runs fill those tiles
-// a third.  Two (as with whole lines) and eight units per lane, 20 heads: 32
-// groups, 50-62 tokens 120 and 109 us, 28-36 tokens 150 and 133, 0-47 tokens 145
-// and 135 (as good as two when they fill less), 20 groups, 36-50 tokens 125 and
-// 119, 60-100 tokens 126 and 120; 24 groups, where two is six: 70-75 tokens 122
-// and 106, 28-36 tokens 136 and 138.  16 groups of 300-1100 tokens do not gain
-// (136.6 with two, 138.5 with four, 136.8 with six).
-constexpr int64_t kSplitEightDu = 20;
+// Eight instead of two for a stream-in from this many groups per token on where
+// max_seq is not whole lines, so that every tile ends inside some (run_split has
+// the rest of the rule).  Two and eight, 20 heads, launches of 300 MB: 32 groups,
+// 50-62 tokens 120 and 109 us, 20-30 tokens 152 and 134, 0-47 tokens 145 and 135 (as
+// good as two when they fill less than a third), 300-1100 tokens 102 and 98, but
+// 70-75 tokens, a second tile for the last few, 115 and 120; 20 groups, 36-50 tokens
+// 125 and 119; 16 groups, 300-1100 tokens 137 and 137.  Smaller launches: 20 MB 9.1
+// and 8.3, 9 MB 5.5 and 5.7, 3 MB 3.0 and 3.6.
+constexpr int64_t kSplitEightDu = 20, kSplitEightMin = 1 << 20;
 constexpr size_t kSplitLdsFor4 = 39 * 1024;  // 4 per CU fit in 160 KB, 5 do not
 
 // Cache-to-cache copy of the same logical positions between two dense caches

@@ -109,33 +109,43 @@ def test_ranges_under_three_quarters_of_their_blocks_go_by_rows(lib, name, owner
     assert kernels(call(lib, name, big, [0], [2048])) == ["table"]
 
 
-@pytest.mark.parametrize("du, tile, odd_in", [(16, 32, 32), (20, 24, 96), (24, 64, 80), (32, 16, 64)])
+@pytest.mark.parametrize("du, tile, odd_in", [(16, 32, 32), (20, 24, 96), (24, 64, 64), (32, 16, 64)])
 def test_split_tiles_for_capacities_that_are_not_whole_lines(lib, du, tile, odd_in):
-    """Tokens per tile: eight units per lane instead of two or six for a
-    stream-in of wide tokens into a capacity that is no multiple of 8, where its
-    runs fill such tiles a third."""
+    """Tokens per tile: eight units per lane instead of two for a large stream-in
+    of wide tokens into a capacity that is no multiple of 8, unless its runs
+    leave more than two thirds of such tiles empty or just pass one."""
     z = np.zeros(3, np.int32)
-    cases = [(2048, "out", 1000, tile), (2048, "in", 1000, tile), (2049, "out", 1000, tile),
-             (2049, "in", 1000, odd_in)]
+    cases = [(2048, "out", 1000, tile, 40), (2048, "in", 1000, tile, 40),
+             (2049, "out", 1000, tile, 40), (2049, "in", 1000, odd_in, 40)]
     if odd_in > tile:
-        cases += [(2049, "in", (odd_in - 1) // 3, tile), (2049, "in", -(-odd_in // 3), odd_in)]
-    for S, name, n, want in cases:
-        c = dense(40, 64, 8 * du, 2, 3, S, dv.DV_DENSE_KSPLIT)
+        cases += [(2049, "in", (odd_in - 1) // 3, tile, 200), (2049, "in", -(-odd_in // 3), odd_in, 200),
+                  (2049, "in", odd_in, odd_in, 200), (2049, "in", odd_in + 1, tile, 200),
+                  (2049, "in", 6 * tile, tile, 200), (2049, "in", 6 * tile + 1, odd_in, 200)]
+    for S, name, n, want, L in cases:
+        c = dense(L, 64, 8 * du, 2, 3, S, dv.DV_DENSE_KSPLIT)
         ran = call(lib, name, c, z, z + n)
         assert kernels(ran) == ["split"] and ran[0][1]["tile"] == want, (S, name, n, ran)
+    if odd_in > tile:  # 2^20 units, and fewer
+        n = np.array([1000, 0, 0], np.int32)
+        for H, want in ((-(-(1 << 20) // (2 * 1000 * du)), odd_in),
+                        ((1 << 20) // (2 * 1000 * du), tile)):
+            ran = call(lib, "in", dense(1, H, 8 * du, 2, 3, 2049, dv.DV_DENSE_KSPLIT), z, z + n)
+            assert ran[0][1]["tile"] == want, (H, ran)
 
 
-@pytest.mark.parametrize("du", [8, 16, 32])
+@pytest.mark.parametrize("du", [4, 8, 16, 32])
 def test_large_split_key_stream_ins_of_short_runs_go_by_tiles(lib, du):
     """Runs that fill a tile three fifths: rows on the way out at every size, on
-    the way in up to 25 million units times groups per token."""
+    the way in up to 100 million units times groups per token, and at every size
+    for fewer than eight groups."""
     n = 512 // du * 3 // 5
     z = np.zeros(10, np.int32)
-    most = 25_000_000 // (2 * 5 * 10 * n * du * du)  # layers
+    most = 100_000_000 // (2 * 5 * 10 * n * du * du)  # layers
     for L in (most, most + 1):
-        c = dense(L, 5, 8 * du, 2, 10, 64, dv.DV_DENSE_KSPLIT)
+        c = dense(L, 5, 8 * du, 2, 10, 96, dv.DV_DENSE_KSPLIT)
         assert kernels(call(lib, "out", c, z, z + n)) == ["split-rows"]
-        assert kernels(call(lib, "in", c, z, z + n)) == ["split-rows" if L == most else "split"]
+        by_rows = L == most or du < 8
+        assert kernels(call(lib, "in", c, z, z + n)) == ["split-rows" if by_rows else "split"]
 
 
 @pytest.mark.parametrize("du, L, line", [(1, 1, 70), (1, 40, 92), (4, 1, 92)])
@@ -227,3 +237,25 @@ def test_owner_map_in_one_launch_up_to_96_chunks_for_each_it_saves(lib, B, most)
             assert kernels(ran) == ["owner-map", "pool"] and ran[0][1]["chunks"] == chunks
         else:
             assert kernels(ran) == ["owner-clear"] + ["owner-build"] * (-(-B // 64)) + ["pool"]
+
+
+@pytest.mark.parametrize("du, tile", [(8, 64), (12, 40), (16, 32), (24, 64), (32, 16)])
+def test_large_split_key_stream_ins_that_leave_tiles_empty_go_by_rows(lib, du, tile):
+    """Every run one tile, with as many tokens on average as the rule asks for,
+    and one fewer in all."""
+    B = 100
+    z = np.zeros(B, np.int32)
+    need = -(-(40 - du) * B * tile // 80)  # tokens of all sequences
+    n = z + 1
+    n[0] = tile  # past the short-run kernel
+    for b in range(1, B):
+        n[b] += min(tile - 1, max(0, need - int(n.sum())))
+    assert int(n.sum()) >= need
+    for less, want in ((0, "split"), (1, "split-rows")):
+        m = n.copy()
+        if less and int(m.sum()) != need:
+            continue  # wide tokens: even runs of one token fill that much
+        m[1] -= less
+        c = dense(2000, 5, 8 * du, 2, B, 64, dv.DV_DENSE_KSPLIT)
+        assert kernels(call(lib, "in", c, z, z + m)) == [want], (du, int(m.sum()), need)
+        assert kernels(call(lib, "out", c, z, z + m)) == ["split-rows"]
