@@ -429,7 +429,7 @@ __global__ void __launch_bounds__(kThreads) owner_build_kernel(OwnerArgs a) {
 // Finds rows [row0, row0 + rows) of a launch's slab, one per lane, shared out by
 // waves: store(row - row0, sequence, head, token) leaves them in LDS.  The
 // caller synchronises.
-template <int N, typename Args, typename F>
+template <int N, bool SEARCH, typename Args, typename F>
 __device__ __forceinline__ void find_rows(const Args& a, uint32_t row0, uint32_t rows, F store) {
   const int lane = lane_id();
   // Every lane of a wave that has rows takes one (the last one again past the
@@ -444,11 +444,13 @@ __device__ __forceinline__ void find_rows(const Args& a, uint32_t row0, uint32_t
       const int tok = a.tok[lane];
       b = __popcll(__ballot(tok <= qlo)) - 1;
       b1 = __popcll(__ballot(tok <= qhi)) - 1;
-      // The wave's rows lie in sequences [b, b1]: a step for each, or from five
-      // on a search (27 sequences of 1-2 tokens, one head, 8 layers: 3.0 us by
-      // steps, 2.4 by search; launches of few sequences to a wave are the same).
+      // The wave's rows lie in sequences [b, b1]: a step for each, or past eight
+      // a search (27 sequences of 1-2 tokens, one head, 8 layers: 3.1 us by
+      // steps, 2.4 by search; 6 sequences 2.0 and 2.1).  The split-key rows,
+      // launches of 4 MB and more whose waves hold few, go without (one sequence
+      // of 16 tokens, 44 heads, 10 MB: 4.8 us, 5.2 with the search compiled in).
       const int steps = b1 - b;
-      if (steps <= 4) {
+      if (!SEARCH || steps <= 8) {
         const int b0 = b;
         for (int i = b0 + 1; i <= b1; ++i) b += __builtin_amdgcn_readlane(tok, i) <= (int)q;
       } else {
@@ -525,7 +527,7 @@ __global__ void __launch_bounds__(kThreads) rows_kernel(RowArgs<N> a) {
   const uint32_t row0 = EVEN ? 0 : a.d_du.div(first);
   if constexpr (!EVEN) {
     const uint32_t rows = a.d_du.div(last) - row0 + 1;
-    find_rows<N>(a, row0, rows, [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
+    find_rows<N, true>(a, row0, rows, [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
       s_off[i] = row_offset(seq, h, s);
     });
     __syncthreads();
@@ -579,7 +581,7 @@ __global__ void __launch_bounds__(kThreads) split_rows_kernel(RowArgs<N> a) {
   int64_t* s_off = (int64_t*)(lds + a.tile * pitch);
   const uint32_t row0 = blockIdx.x * a.tile;
   const uint32_t rows = min((uint32_t)a.tile, a.d_du.div(a.total) - row0);
-  find_rows<N>(a, row0, rows, [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
+  find_rows<N, false>(a, row0, rows, [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
     s_off[i] = (int64_t)seq * a.s_b + (int64_t)h * a.s_h + (int64_t)s * s_tok;
   });
   __syncthreads();
@@ -738,12 +740,12 @@ __global__ void __launch_bounds__(kThreads) copy_kernel(CopyArgs<N> a) {
   const uint32_t first = blockIdx.x * (kThreads * U);
   const uint32_t last = min(first + kThreads * U, (uint32_t)a.total) - 1;
   const uint32_t row0 = a.d_du.div(first);
-  find_rows<N>(a, row0, a.d_du.div(last) - row0 + 1,
-               [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
-                 const int64_t e = (int64_t)s * a.du;
-                 s_src[i] = (int64_t)seq * a.s_b + (int64_t)h * a.s_h + e;
-                 s_dst[i] = (int64_t)seq * a.d_b + (int64_t)h * a.d_h + e;
-               });
+  find_rows<N, true>(a, row0, a.d_du.div(last) - row0 + 1,
+                     [&](uint32_t i, int seq, uint32_t h, uint32_t s) {
+                       const int64_t e = (int64_t)s * a.du;
+                       s_src[i] = (int64_t)seq * a.s_b + (int64_t)h * a.s_h + e;
+                       s_dst[i] = (int64_t)seq * a.d_b + (int64_t)h * a.d_h + e;
+                     });
   __syncthreads();
   const int64_t slab = a.slab0 + (int64_t)blockIdx.y;
   const u32x4* src = (const u32x4*)a.src + slab * a.s_slab;

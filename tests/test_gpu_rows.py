@@ -34,9 +34,10 @@ SHAPES = {
     "longest-runs": (2, 2, 256, 5, (7, 8), 1.0),
     "two-units-per-lane": (3, 24, 128, 30, (1, 16), 1.0),
     "two-units-past-64": (2, 16, 128, 130, (1, 16), 1.0),
-    # sequences that a wave's 64 rows lie in: 40 to 45, four to six
+    # sequences that a wave's 64 rows lie in: 40 to 45, four to six, eight to ten
     "wave-of-forty": (2, 1, 8, 64, (1, 2), 1.0),
     "wave-of-five": (2, 1, 8, 60, (11, 20), 1.0),
+    "wave-of-nine": (2, 1, 8, 60, (6, 9), 1.0),
 }
 
 
