@@ -154,12 +154,14 @@ __global__ void __launch_bounds__(kThreads) dense_runs_kernel(DenseRunArgs<N> a)
 // so block, table entry and sequence are uniform over the workgroup.  WIDE:
 // unit numbers may pass 2^31, and a workgroup may take several tiles; kept
 // apart so that the ordinary kernels run straight down, with their arguments
-// fetched together.
+// fetched together.  TWO: blocks of a wave's units and more, looked up by the wave
+// (launch_paged has the rule).
 // ---------------------------------------------------------------------------
-template <int D, bool POOL, bool ONE, bool WIDE, int N>
+template <int D, bool POOL, bool ONE, bool WIDE, bool TWO, int N>
 __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
   static_assert(!POOL || D == kUnpack, "pool order is for stream-in");
   static_assert(!(ONE && WIDE), "wide launches look every unit up");
+  static_assert(!TWO || (POOL && !ONE), "a wave's two blocks are looked up in pool order");
   const int lane = lane_id();
   const uint32_t ub = a.ub, heads = a.heads;
   // Tiles within one block keep the hardware's round-robin dealing in table
@@ -243,24 +245,16 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
       if (blk1 < 0 || blk1 >= a.num_blocks) return;  // unmapped block: skipped
     }
 
-    // Pool order, more than 64 sequences: a wave's units follow each other, so
-    // unless blocks are smaller than that they lie in two of them at most.  Both
-    // are looked up once for the wave and a lane takes one.  A look-up per lane
-    // ends in three loads of its own from the arguments: 193 sequences, blocks of
-    // 1792 units, 430 MB, three fifths of the pool, 168.6 us against 150.2; 100
-    // of 128 units, 2.09 GB, 750 against 696; 80 of 1280 units, the whole pool,
-    // 2.23 GB, 729 against 737.  (Up to 64 the ranges are in the lanes: 526
-    // against 548 with the whole pool written, 342 against 333 with three fifths.)
-    constexpr bool kTwo = POOL && !ONE && N != kSeqPerLaunch;
+    // TWO: a wave's units follow each other, so they lie in two blocks at most.
+    // Both are looked up once for the wave and a lane takes one.
     uint32_t off0 = 0;  // the wave's first unit in its block
-    Seq two[kTwo ? 2 : 1] = {};  // k: the logical block; n: 0 where there is none
-    const bool by_wave = kTwo && a.s_blk >= 64 * kPagedUnroll && a.s_blk <= (1 << 30);
-    if (by_wave) {
+    Seq two[TWO ? 2 : 1] = {};  // k: the logical block; n: 0 where there is none
+    if constexpr (TWO) {
       const uint32_t w0 = __builtin_amdgcn_readfirstlane(r0 + (threadIdx.x & ~63u) * kPagedUnroll);
       const uint32_t d = a.d_ub.div(w0), dj = a.d_heads.div(h0 + d);
       off0 = (h0 + d - dj * heads) * ub + (w0 - d * ub);
 #pragma unroll
-      for (int i = 0; i < (kTwo ? 2 : 0); ++i) {
+      for (int i = 0; i < 2; ++i) {
         const uint32_t blk = j0 + dj + i, last = a.num_blocks - 1;
         const int own = __builtin_amdgcn_readfirstlane(a.owner[min(blk, last)]);
         const int b = a.d_max.div(max(own, 0));
@@ -281,17 +275,17 @@ __global__ void __launch_bounds__(kThreads) paged_kernel(PagedArgs<N> a) {
       // interleave (1 % faster).
       const uint32_t idx = D == kUnpack ? (threadIdx.x & ~63u) * kPagedUnroll + i * 64 + lane
                                         : i * kThreads + threadIdx.x;
-      const bool second = by_wave && off0 + i * 64 + lane >= (uint32_t)a.s_blk;
-      const uint32_t z = by_wave ? off0 + i * 64 + lane - (second ? (uint32_t)a.s_blk : 0) : r0 + idx;
+      const bool second = TWO && off0 + i * 64 + lane >= (uint32_t)a.s_blk;
+      const uint32_t z = TWO ? off0 + i * 64 + lane - (second ? (uint32_t)a.s_blk : 0) : r0 + idx;
       const uint32_t d = a.d_ub.div(z);
       const uint32_t e = z - d * ub;
       uint32_t h = h0 + d;
       Seq s = u;
       int j = j1;
       ok[i] = true;
-      if (by_wave) {
+      if constexpr (TWO) {
         h = d;
-        s = two[kTwo && second];
+        s = two[second];
         j = s.k;
         po[i] = (int64_t)(f + idx);
       } else if constexpr (ONE) {
@@ -795,10 +789,12 @@ template hipError_t launch_dense_runs<kSeqMany>(int, const DenseRunArgs<kSeqMany
 namespace {
 
 template <int N, bool ONE, bool WIDE>
-const void* paged_fn(int dir, bool pool) {
-  if (pool) return (const void*)&paged_kernel<kUnpack, true, ONE, WIDE, N>;
-  return dir == kPack ? (const void*)&paged_kernel<kPack, false, ONE, WIDE, N>
-                      : (const void*)&paged_kernel<kUnpack, false, ONE, WIDE, N>;
+const void* paged_fn(int dir, bool pool, bool two) {
+  if constexpr (!ONE && N != kSeqPerLaunch)
+    if (pool && two) return (const void*)&paged_kernel<kUnpack, true, false, WIDE, true, N>;
+  if (pool) return (const void*)&paged_kernel<kUnpack, true, ONE, WIDE, false, N>;
+  return dir == kPack ? (const void*)&paged_kernel<kPack, false, ONE, WIDE, false, N>
+                      : (const void*)&paged_kernel<kUnpack, false, ONE, WIDE, false, N>;
 }
 
 }  // namespace
@@ -807,9 +803,17 @@ template <int N>
 hipError_t launch_paged(int dir, const PagedArgs<N>& a, bool wide, uint32_t nslabs,
                         hipStream_t s) {
   const bool pool = a.owner != nullptr;
-  const void* fn = wide                          ? paged_fn<N, false, true>(dir, pool)
-                   : a.s_blk % kPagedTile == 0 ? paged_fn<N, true, false>(dir, pool)
-                                               : paged_fn<N, false, false>(dir, pool);
+  // Pool order, more than 64 sequences, tiles across blocks: a look-up per lane
+  // ends in three loads of its own from the arguments.  Look-ups by lane and by
+  // wave: 193 sequences, blocks of 1792 units, three fifths of the pool, 430 MB,
+  // 168.6 and 150.2 us; 100 of 128 units, 2.09 GB, 750 and 696; 80 of 1280 units,
+  // the whole pool, 2.23 GB, 729 and 737.  (Up to 64 the ranges are in the lanes:
+  // 526 and 548 with the whole pool written, 342 and 333 with three fifths.)
+  // Smaller blocks are more than two to a wave, larger ones past 32 bits.
+  const bool two = a.s_blk >= 64 * kPagedUnroll && a.s_blk <= (1 << 30);
+  const void* fn = wide                          ? paged_fn<N, false, true>(dir, pool, two)
+                   : a.s_blk % kPagedTile == 0 ? paged_fn<N, true, false>(dir, pool, two)
+                                               : paged_fn<N, false, false>(dir, pool, two);
   return launch(fn, dim3(a.tiles, nslabs), a, s);
 }
 template hipError_t launch_paged<kSeqPerLaunch>(int, const PagedArgs<kSeqPerLaunch>&, bool,
