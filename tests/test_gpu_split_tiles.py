@@ -77,7 +77,7 @@ def test_split_tiles_that_end_on_lines(oracle_lib, groups, shift):
 
 @pytest.mark.parametrize("whole_lines", [False, True])
 def test_split_runs_of_few_tokens_in_a_large_stream(oracle_lib, whole_lines):
-    """86 MB of 5-20 tokens, 32 groups: rows out, badly filled tiles in."""
+    """98 MB of 5-20 tokens, 32 groups: rows out, badly filled tiles in."""
     r = np.random.default_rng(4)
     n = r.integers(5, 21, size=40)
     check(oracle_lib, 4, 42, 256, 2, r.integers(0, 30, size=40), n, whole_lines, 5)
