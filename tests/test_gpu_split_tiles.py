@@ -54,10 +54,23 @@ def test_split_tiles(oracle_lib, groups):
     tile = two if two * groups * 5 >= 4 * 512 else six  # tokens
     n = np.array([3 * tile, 4 * tile + 1, 4 * tile - 1, 0, 4 * tile])
     check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 13], n)
-    # eight units per lane on the way in, for 20 groups and more
+    if groups >= 20:  # past 16 MB, where two units become eight on the way in
+        eight = 2048 // groups & ~7
+        n = np.array([3 * eight, eight // 2, eight + 1, 0, 2 * eight - 1])
+        check(oracle_lib, 16, 3, 8 * groups, 2, [0, 1, 8, 2, 12], n)
+
+
+@pytest.mark.parametrize("groups", [20, 32])
+def test_split_tiles_of_eight_units_past_64_sequences(oracle_lib, groups):
+    """20 and 22 MB into a capacity that is not whole lines: runs around one tile
+    of eight units per lane and ragged ones, in one launch of 71 sequences."""
+    r = np.random.default_rng(groups)
     eight = 2048 // groups & ~7
-    n = np.array([3 * eight, eight // 2, eight + 1, 0, 2 * eight - 1])
-    check(oracle_lib, 2, 3, 8 * groups, 2, [0, 1, 8, 2, 12], n)
+    n = r.integers(eight // 3, eight + 1, size=71)
+    n[:6] = eight - 1, eight, eight + 1, 0, 2 * eight, 1
+    t0 = r.integers(0, 9, size=71)
+    t0[4] = 9  # then the capacity is 2 * eight + 12
+    check(oracle_lib, 1, 7, 8 * groups, 2, t0, n)
 
 
 @pytest.mark.parametrize("groups", [1, 5, 16, 24, 32])
